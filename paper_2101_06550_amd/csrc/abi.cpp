@@ -45,6 +45,10 @@ struct BandPlan {
   ChunkTables chunk16;
   bool has_chunk16 = false;
   DevChunk dchunk16;
+  // lengths that do not split into 32-point chunks
+  RaggedTables ragged;
+  bool has_ragged = false;
+  DevRagged dragged;
   void* dmem = nullptr;
   int device = 0;
 
@@ -67,6 +71,9 @@ int upload(BandPlan* p) {
   const size_t o_h32 = off; off = align256(off + p->chunk16.rec32.size() * sizeof(float));
   const size_t o_hb = off; off = align256(off + p->chunk16.blocks.size() * sizeof(double));
   const size_t o_hb32 = off; off = align256(off + p->chunk16.blocks32.size() * sizeof(float));
+  const size_t o_r = off; off = align256(off + p->ragged.rec.size() * sizeof(double));
+  const size_t o_rl = off; off = align256(off + p->ragged.recl.size() * sizeof(double));
+  const size_t o_rb = off; off = align256(off + p->ragged.blocks.size() * sizeof(double));
   if (hipGetDevice(&p->device) != hipSuccess) return CHX_EHIP;
   if (hipMalloc(&p->dmem, off > 0 ? off : 256) != hipSuccess) {
     p->dmem = nullptr;
@@ -86,6 +93,9 @@ int upload(BandPlan* p) {
   put(o_h32, p->chunk16.rec32.data(), p->chunk16.rec32.size() * sizeof(float));
   put(o_hb, p->chunk16.blocks.data(), p->chunk16.blocks.size() * sizeof(double));
   put(o_hb32, p->chunk16.blocks32.data(), p->chunk16.blocks32.size() * sizeof(float));
+  put(o_r, p->ragged.rec.data(), p->ragged.rec.size() * sizeof(double));
+  put(o_rl, p->ragged.recl.data(), p->ragged.recl.size() * sizeof(double));
+  put(o_rb, p->ragged.blocks.data(), p->ragged.blocks.size() * sizeof(double));
   if (hipMemcpy(p->dmem, host.data(), host.size(), hipMemcpyHostToDevice) != hipSuccess)
     return CHX_EHIP;
   auto* base = static_cast<unsigned char*>(p->dmem);
@@ -122,6 +132,20 @@ int upload(BandPlan* p) {
     d.rec32 = reinterpret_cast<const float*>(base + o_h32);
     d.blocks = reinterpret_cast<const double*>(base + o_hb);
     d.blocks32 = reinterpret_cast<const float*>(base + o_hb32);
+  }
+  if (p->has_ragged) {
+    DevRagged& d = p->dragged;
+    d.n = p->n;
+    d.P = p->P;
+    d.m = p->ragged.m;
+    d.r = p->ragged.r;
+    d.S = p->ragged.S;
+    d.dlo = p->ragged.dlo;
+    d.dcount = p->ragged.dcount;
+    for (int k = 0; k < 5; ++k) d.coef[k] = p->coef[k];
+    d.rec = reinterpret_cast<const double*>(base + o_r);
+    d.recl = reinterpret_cast<const double*>(base + o_rl);
+    d.blocks = reinterpret_cast<const double*>(base + o_rb);
   }
   return CHX_OK;
 }
@@ -180,14 +204,21 @@ int make_plan(int P, int n, const double* coef, int periodic, PlanT** out,
   band.P = P;
   band.periodic = p->periodic != 0;
   for (int k = 0; k < 2 * P + 1; ++k) band.coef[k] = coef[k];
-  int rc = build_whole(band, n, &p->whole);
+  CyclicFactor cyc;
+  int rc = p->periodic ? cyc.make(band, n) : CHX_OK;
+  if (rc == CHX_OK) rc = build_whole(band, n, &p->whole, p->periodic ? &cyc : nullptr);
   if (rc == CHX_OK && p->periodic && n % kChunk == 0) {
-    rc = build_chunk(band, n, kChunk, &p->chunk);
+    rc = build_chunk(band, n, kChunk, &p->chunk, &cyc);
     p->has_chunk = (rc == CHX_OK);
     if (rc == CHX_EINVAL) rc = CHX_OK;  // shape not eligible: keep the whole-system path
   }
+  if (rc == CHX_OK && p->periodic && !p->has_chunk) {
+    rc = build_ragged(band, n, kChunk, &p->ragged, &cyc);
+    p->has_ragged = (rc == CHX_OK);
+    if (rc == CHX_EINVAL) rc = CHX_OK;  // too short: the whole-system path
+  }
   if (rc == CHX_OK && chunk16 && p->has_chunk && n % 16 == 0) {
-    const int rc16 = build_chunk(band, n, 16, &p->chunk16);
+    const int rc16 = build_chunk(band, n, 16, &p->chunk16, &cyc);
     p->has_chunk16 = (rc16 == CHX_OK);
     if (rc16 != CHX_OK && rc16 != CHX_EINVAL) rc = rc16;
   }
@@ -278,6 +309,33 @@ hipError_t solve_refined(const BandPlan* p, int batch, double* x, long ld, int l
   return e;
 }
 
+// FP64 solves in place.  Interleaved: one launch where a workgroup holds whole
+// systems, the chunked passes for longer ones, one thread per system where
+// neither applies (no tables, or no rho for the chunked passes).  Contiguous: rows through LDS up to 256 chunks.
+hipError_t solve_il(const BandPlan* p, double* x, long ld, int batch, double* rho,
+                    hipStream_t st) {
+  if (p->has_chunk && il_fused_systems(p->dchunk.S, batch) > 0)
+    return launch_il_fused(p->dchunk, -1, x, ld, batch, 1, 0.0, 0.0, st);
+  if (p->has_chunk && rho)
+    return p->P == 2 ? launch_chunked_il<2>(p->dchunk, x, ld, batch, rho, st)
+                     : launch_chunked_il<1>(p->dchunk, x, ld, batch, rho, st);
+  if (p->has_ragged && il_fused_systems(p->dragged.S, batch) > 0)
+    return launch_il_fused(p->dragged, -1, x, ld, batch, 1, 0.0, 0.0, st);
+  return p->P == 2 ? launch_whole<2>(p->dwhole, x, 1, ld, batch, st)
+                   : launch_whole<1>(p->dwhole, x, 1, ld, batch, st);
+}
+
+hipError_t solve_rows(const BandPlan* p, double* x, long ld, int batch, bool stream_in,
+                      hipStream_t st) {
+  if (p->has_chunk && p->chunk.S <= 256)
+    return p->P == 2 ? launch_rows_lds<2>(p->dchunk, x, ld, batch, st, stream_in)
+                     : launch_rows_lds<1>(p->dchunk, x, ld, batch, st, stream_in);
+  if (p->has_ragged && rows_ragged_fits(p->dragged))
+    return launch_rows_ragged(p->dragged, x, ld, batch, st);
+  return p->P == 2 ? launch_whole<2>(p->dwhole, x, ld, 1, batch, st)
+                   : launch_whole<1>(p->dwhole, x, ld, 1, batch, st);
+}
+
 int solve(const BandPlan* p, int batch, void* x, long ld, int layout, int dtype, int refine,
           void* ws, size_t ws_bytes, chx_stream s) {
   if (!p) return CHX_EINVAL;
@@ -301,21 +359,9 @@ int solve(const BandPlan* p, int batch, void* x, long ld, int layout, int dtype,
     e = (p->P == 2) ? solve_refined<2>(p, batch, xd, ld, layout, refine, wsb, w, st)
                     : solve_refined<1>(p, batch, xd, ld, layout, refine, wsb, w, st);
   } else if (layout == CHX_INTERLEAVED) {
-    if (p->has_chunk) {
-      e = (p->P == 2) ? launch_chunked_il<2>(p->dchunk, xd, ld, batch, static_cast<double*>(ws), st)
-                      : launch_chunked_il<1>(p->dchunk, xd, ld, batch, static_cast<double*>(ws), st);
-    } else {
-      e = (p->P == 2) ? launch_whole<2>(p->dwhole, xd, 1, ld, batch, st)
-                      : launch_whole<1>(p->dwhole, xd, 1, ld, batch, st);
-    }
+    e = solve_il(p, xd, ld, batch, static_cast<double*>(ws), st);
   } else {
-    if (p->has_chunk && p->chunk.S <= 256) {
-      e = (p->P == 2) ? launch_rows_lds<2>(p->dchunk, xd, ld, batch, st, true)
-                      : launch_rows_lds<1>(p->dchunk, xd, ld, batch, st, true);
-    } else {
-      e = (p->P == 2) ? launch_whole<2>(p->dwhole, xd, ld, 1, batch, st)
-                      : launch_whole<1>(p->dwhole, xd, ld, 1, batch, st);
-    }
+    e = solve_rows(p, xd, ld, batch, true, st);
   }
   return e == hipSuccess ? CHX_OK : CHX_EHIP;
 }
@@ -722,6 +768,14 @@ int batch1d_step(chx_batch1d b, int batch, double* x, long ld, int nsteps, void*
   double* y0 = reinterpret_cast<double*>(base);
   double* y1 = reinterpret_cast<double*>(base + field);
   double* rho = reinterpret_cast<double*>(base + 2 * field);
+  // systems that a workgroup holds take all steps of the call in one launch
+  const BandPlan* p = b->plan;
+  if (p->has_chunk && il_fused_systems(p->dchunk.S, batch) > 0)
+    return launch_il_fused(p->dchunk, b->kind, x, ld, batch, nsteps, b->s, b->al,
+                           static_cast<hipStream_t>(s)) == hipSuccess ? CHX_OK : CHX_EHIP;
+  if (p->has_ragged && il_fused_systems(p->dragged.S, batch) > 0)
+    return launch_il_fused(p->dragged, b->kind, x, ld, batch, nsteps, b->s, b->al,
+                           static_cast<hipStream_t>(s)) == hipSuccess ? CHX_OK : CHX_EHIP;
   const hipError_t e =
       launch_batch1d_steps(b->kind, b->plan->has_chunk, b->plan->dchunk, b->plan->dwhole, x, ld,
                            batch, b->n, b->s, b->al, nsteps, y0, y1, rho,
@@ -1781,12 +1835,12 @@ static int run_steps(chx_ch h, double* c, long ld, int nsteps, double* diag_out,
       }
       if (ok()) {
         B();
-        e = launch_whole<2>(h->py->dwhole, r, 1, nx, nx, st);
+        e = solve_il(h->py, r, nx, nx, nullptr, st);
         E(0);
       }
       if (ok()) {
         B();
-        e = launch_whole<2>(h->px->dwhole, r, nx, 1, ny, st);
+        e = solve_rows(h->px, r, nx, ny, false, st);
         E(2);
       }
       if (ok()) {
@@ -1857,7 +1911,6 @@ int ch_adi_step_p2(chx_ch h, double* c, double* cprev, long ld, int nsteps, doub
   double* rho = reinterpret_cast<double*>(base + h->off_rho);
   double* part = reinterpret_cast<double*>(base + h->off_part);
   const bool col_chunk = h->py->has_chunk;
-  const bool row_lds = h->px->has_chunk && h->px->chunk.S <= 256;
   hipError_t e = hipSuccess;
   // v = L_y^{-1} L_x^{-1} r in place: columns (interleaved), then rows
   // (chunked columns: the chunk correction is left to whoever reads r next)
@@ -1868,10 +1921,8 @@ int ch_adi_step_p2(chx_ch h, double* c, double* cprev, long ld, int nsteps, doub
   auto solve_in_place = [&](double* r) {
     hipError_t e2 = col_chunk ? launch_reduced_il<2>(h->py->dchunk, rho, nx, r, nx, kChunk,
                                                      kChunk - 2, st)
-                              : launch_whole<2>(h->py->dwhole, r, 1, nx, nx, st);
-    if (e2 == hipSuccess)
-      e2 = row_lds ? launch_rows_lds<2>(h->px->dchunk, r, nx, ny, st)
-                   : launch_whole<2>(h->px->dwhole, r, nx, 1, ny, st);
+                              : solve_il(h->py, r, nx, nx, nullptr, st);
+    if (e2 == hipSuccess) e2 = solve_rows(h->px, r, nx, ny, false, st);
     return e2;
   };
   // The states rotate through c, cprev and w: each later step advances the

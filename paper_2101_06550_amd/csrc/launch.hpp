@@ -28,6 +28,28 @@ struct DevChunk {
   int red_shape = 0;                // separator-kernel tile shape (index into the candidates)
 };
 
+// Device copy of RaggedTables (chunks of m, a last one of r).
+struct DevRagged {
+  int n = 0, P = 2, M = kChunk, m = 0, r = 0, S = 0, dlo = 0, dcount = 0;
+  double coef[5] = {};
+  const double* rec = nullptr;     // device, (M - P) * 8
+  const double* recl = nullptr;    // device, (M - P) * 8: the last chunk's
+  const double* blocks = nullptr;  // device, 3 * dcount * 4
+};
+
+// One-launch interleaved solve (kind -1) or nsteps steps of a batched 1D
+// scheme (kind 0 .. 2) in place on x (fused.hip): a workgroup holds every
+// chunk of il_fused_systems(S, batch) systems; 0 where S is too large.
+int il_fused_systems(int S, int batch);
+hipError_t launch_il_fused(const DevChunk& c, int kind, double* x, long ld, int batch, int nsteps,
+                           double s, double al, hipStream_t st);
+hipError_t launch_il_fused(const DevRagged& c, int kind, double* x, long ld, int batch, int nsteps,
+                           double s, double al, hipStream_t st);
+
+// Contiguous rows of any length in place (fused.hip), at most 256 chunks.
+bool rows_ragged_fits(const DevRagged& c);
+hipError_t launch_rows_ragged(const DevRagged& c, double* x, long ld, int rows, hipStream_t st);
+
 // Number of candidate tile shapes of the separator kernel, and the LDS one
 // launch of shape `shape` needs (elem = sizeof the sweep type; diag = the
 // launch also finishes the diagnostics sum).

@@ -140,21 +140,26 @@ int bordered_factor(const Band& b, int n, Bordered* out) {
   if (rc) return rc;
   out->Z.assign(P, std::vector<LD>(mi));
   out->q.assign(P, std::vector<LD>(mi));
+  // the couplings are a few entries at the ends: band offset o of row i meets
+  // column (i + o) mod n
+  auto ring = [&](int i) { return ((i % n) + n) % n; };
+  std::vector<std::vector<LD>> hrow(P, std::vector<LD>(mi, 0));
   for (int a = 0; a < P; ++a) {
-    std::vector<LD> kcol(mi), hrow(mi);
-    for (int i = 0; i < mi; ++i) {
-      kcol[i] = cyc_entry(b, n, i, mi + a);
-      hrow[i] = cyc_entry(b, n, mi + a, i);
+    std::vector<LD> kcol(mi, 0);
+    for (int o = -P; o <= P; ++o) {
+      const int i = ring(mi + a - o), j = ring(mi + a + o);
+      if (i < mi) kcol[i] += b.coef[o + P];
+      if (j < mi) hrow[a][j] += b.coef[o + P];
     }
     out->Z[a] = lr_solve(out->E, kcol);
-    out->q[a] = lr_solve_transposed(out->E, hrow);
+    out->q[a] = lr_solve_transposed(out->E, hrow[a]);
   }
   LD M[4] = {0, 0, 0, 0};
   for (int a = 0; a < P; ++a)
     for (int c = 0; c < P; ++c) {
       LD v = cyc_entry(b, n, mi + a, mi + c);
-      std::vector<LD> hrow(mi);
-      for (int i = 0; i < mi; ++i) v -= cyc_entry(b, n, mi + a, i) * out->Z[c][i];
+      for (int i = 0; i < mi; ++i)
+        if (hrow[a][i] != 0) v -= hrow[a][i] * out->Z[c][i];
       M[a * P + c] = v;
     }
   LD inv[4];
@@ -195,17 +200,31 @@ void fill_rec(const LR& E, int i, double* rec) {
 
 }  // namespace
 
-int circulant_inverse_column(const Band& band, int n, std::vector<long double>* g) {
+struct CyclicFactor::Impl {
   Bordered B;
-  int rc = bordered_factor(band, n, &B);
-  if (rc) return rc;
-  std::vector<LD> e0(n, 0);
-  e0[0] = 1;
-  *g = bordered_solve(band, n, B, e0);
-  return CHX_OK;
+  bool have_g = false;
+  std::vector<LD> g;
+};
+CyclicFactor::CyclicFactor() : impl(new Impl) {}
+CyclicFactor::~CyclicFactor() { delete impl; }
+
+int CyclicFactor::make(const Band& b, int size) {
+  band = b;
+  n = size;
+  return bordered_factor(b, size, &impl->B);
 }
 
-int build_whole(const Band& band, int n, WholeTables* out) {
+const std::vector<long double>& CyclicFactor::inverse_column() {
+  if (!impl->have_g) {
+    std::vector<LD> e0(n, 0);
+    e0[0] = 1;
+    impl->g = bordered_solve(band, n, impl->B, e0);
+    impl->have_g = true;
+  }
+  return impl->g;
+}
+
+int build_whole(const Band& band, int n, WholeTables* out, CyclicFactor* cyc) {
   const int P = band.P;
   out->n = n;
   out->P = P;
@@ -217,9 +236,13 @@ int build_whole(const Band& band, int n, WholeTables* out) {
     out->rec.assign((size_t)n * kRec, 0.0);
     for (int i = 0; i < n; ++i) fill_rec(E, i, &out->rec[(size_t)i * kRec]);
   } else {
-    Bordered B;
-    int rc = bordered_factor(band, n, &B);
-    if (rc) return rc;
+    CyclicFactor own;
+    if (!cyc) {
+      int rc = own.make(band, n);
+      if (rc) return rc;
+      cyc = &own;
+    }
+    const Bordered& B = cyc->impl->B;
     const int mi = n - P;
     out->mi = mi;
     out->rec.assign((size_t)mi * kRec, 0.0);
@@ -240,7 +263,7 @@ int build_whole(const Band& band, int n, WholeTables* out) {
   return CHX_OK;
 }
 
-int build_chunk(const Band& band, int n, int m, ChunkTables* out) {
+int build_chunk(const Band& band, int n, int m, ChunkTables* out, CyclicFactor* cyc) {
   const int P = band.P;
   if (!band.periodic || m < 3 * P || n % m != 0) return CHX_EINVAL;
   const int S = n / m, mi = m - P;
@@ -268,9 +291,13 @@ int build_chunk(const Band& band, int n, int m, ChunkTables* out) {
   for (int p = 0; p < mi; ++p) fill_rec(E, p, &out->rec[(size_t)p * kRec]);
 
   // Reduced system: the separator-separator block of the circulant A^{-1}.
-  std::vector<LD> g;
-  rc = circulant_inverse_column(band, n, &g);
-  if (rc) return rc;
+  CyclicFactor own;
+  if (!cyc) {
+    rc = own.make(band, n);
+    if (rc) return rc;
+    cyc = &own;
+  }
+  const std::vector<LD>& g = cyc->inverse_column();
   auto blk = [&](int d, int a, int c) -> LD {
     long long idx = (long long)(-(long long)d * m + a - c);
     idx %= n;
@@ -311,6 +338,104 @@ int build_chunk(const Band& band, int n, int m, ChunkTables* out) {
   }
   out->rec32.assign(out->rec.begin(), out->rec.end());
   out->blocks32.assign(out->blocks.begin(), out->blocks.end());
+  return CHX_OK;
+}
+
+bool ragged_split(int P, int n, int M, int* m, int* r, int* S) {
+  const int rmin = 3 * P;
+  if (n < rmin) return false;
+  for (int s = (n + M - 1) / M; s * rmin <= n; ++s)
+    for (int q = std::min(M, n); q >= rmin; --q) {
+      const int rem = n - (s - 1) * q;
+      if (rem > q) break;
+      if (rem < rmin) continue;
+      *m = q;
+      *r = rem;
+      *S = s;
+      return true;
+    }
+  return false;
+}
+
+int build_ragged(const Band& band, int n, int M, RaggedTables* out, CyclicFactor* cyc) {
+  const int P = band.P;
+  int m, r, S;
+  if (!band.periodic || !ragged_split(P, n, M, &m, &r, &S)) return CHX_EINVAL;
+  const int mi = m - P;
+  out->n = n; out->P = P; out->M = M; out->m = m; out->r = r; out->S = S;
+
+  LR E;
+  int rc = lr_factor(band, mi, &E);
+  if (rc) return rc;
+  // LR factors and, for an interior of len unknowns, its spike vectors
+  auto fill = [&](int len, std::vector<double>* rec) {
+    rec->assign((size_t)(M - P) * kRec, 0.0);
+    LR El;
+    if (lr_factor(band, len, &El)) return;  // a leading block of E: its pivots are E's
+    for (int p = 0; p < len; ++p) fill_rec(El, p, &(*rec)[(size_t)p * kRec]);
+    for (int a = 0; a < P; ++a) {
+      std::vector<LD> kl(len, 0), kr(len, 0);
+      for (int p = 0; p < len; ++p) {
+        const int ol = (a - P) - p, orr = len + a - p;
+        if (ol >= -P && ol <= P) kl[p] = band.coef[ol + P];
+        if (orr >= -P && orr <= P) kr[p] = band.coef[orr + P];
+      }
+      const std::vector<LD> zl = lr_solve(El, kl), zr = lr_solve(El, kr);
+      for (int p = 0; p < len; ++p) {
+        (*rec)[(size_t)p * kRec + 4 + a] = (double)zl[p];
+        (*rec)[(size_t)p * kRec + 6 + a] = (double)zr[p];
+      }
+    }
+  };
+  fill(mi, &out->rec);
+  fill(r - P, &out->recl);
+
+  CyclicFactor own;
+  if (!cyc) {
+    rc = own.make(band, n);
+    if (rc) return rc;
+    cyc = &own;
+  }
+  const std::vector<LD>& g = cyc->inverse_column();
+  auto blk = [&](int fam, int d, int a, int c) -> LD {
+    const int shift = fam == 0 ? 0 : fam == 1 ? m - r : r - m;
+    long long idx = (long long)a - c - ((long long)d * m + shift);
+    idx %= n;
+    if (idx < 0) idx += n;
+    return g[(size_t)idx];
+  };
+  // the window: every chunk, or the fewest offsets on either side beyond
+  // which the blocks of all families total at most 2^-60 of the largest
+  auto norm = [&](int d) {
+    LD v = 0;
+    for (int fam = 0; fam < 3; ++fam)
+      for (int a = 0; a < P; ++a)
+        for (int c = 0; c < P; ++c) v = std::max(v, std::fabs(blk(fam, d, a, c)));
+    return v;
+  };
+  std::vector<LD> nb(S);  // by distance in chunks along the nearer way
+  for (int w = 0; w < S; ++w) nb[w] = std::max(norm(w), norm(-w));
+  const LD thresh = std::ldexp((LD)1, -60) * nb[0];
+  int W = 0;
+  for (;; ++W) {
+    LD tail = 0;
+    for (int w = W + 1; w <= S / 2; ++w) tail += 2 * nb[w];
+    if (tail <= thresh || 2 * W + 1 >= S) break;
+  }
+  if (2 * W + 1 >= S) {
+    out->dlo = -((S - 1) / 2);
+    out->dcount = S;
+  } else {
+    out->dlo = -W;
+    out->dcount = 2 * W + 1;
+  }
+  out->blocks.assign((size_t)3 * out->dcount * 4, 0.0);
+  for (int fam = 0; fam < 3; ++fam)
+    for (int t = 0; t < out->dcount; ++t)
+      for (int a = 0; a < P; ++a)
+        for (int c = 0; c < P; ++c)
+          out->blocks[((size_t)fam * out->dcount + t) * 4 + a * 2 + c] =
+              (double)blk(fam, out->dlo + t, a, c);
   return CHX_OK;
 }
 

@@ -60,11 +60,44 @@ struct ChunkTables {
   double max_dropped = 0.0;   // largest |entry| of a dropped block (0 if none)
 };
 
-// Status codes mirror chx.h.
-int build_whole(const Band& band, int n, WholeTables* out);
-int build_chunk(const Band& band, int n, int m, ChunkTables* out);
+// Chunk tables of a cyclic system of any length: S chunks, the first S - 1 of
+// m <= M unknowns and the last of r (3P <= r <= m).  Every chunk's interior
+// matrix is a leading block of one Toeplitz matrix, so all share the LR
+// factors; the spike vectors of the last chunk are its own (recl).  The
+// separator-separator block of A^{-1} depends on the distance between two
+// separators along the ring, d m from chunk k to chunk k + d unless the way
+// passes the short chunk, which takes m - r off: family 0 of the blocks holds
+// distance d m, family 1 d m + (m - r), family 2 d m - (m - r).
+struct RaggedTables {
+  int n = 0, P = 2, M = 0, m = 0, r = 0, S = 0;
+  std::vector<double> rec, recl;  // (M - P) * kRec each, zero beyond the interior
+  int dlo = 0, dcount = 0;
+  std::vector<double> blocks;     // 3 * dcount * 4, family-major
+};
 
-// First column of A^{-1} for the cyclic band matrix (long double solve).
-int circulant_inverse_column(const Band& band, int n, std::vector<long double>* g);
+// The bordered factorisation of a cyclic matrix and the first column of its
+// inverse, made once and shared by the tables of one plan.
+struct CyclicFactor {
+  struct Impl;
+  CyclicFactor();
+  ~CyclicFactor();
+  CyclicFactor(const CyclicFactor&) = delete;
+  CyclicFactor& operator=(const CyclicFactor&) = delete;
+  int make(const Band& b, int size);
+  const std::vector<long double>& inverse_column();
+  Band band;
+  int n = 0;
+  Impl* impl;
+};
+
+// Status codes mirror chx.h.  cyc: the matrix's factorisation if the caller
+// has it (made here otherwise).
+int build_whole(const Band& band, int n, WholeTables* out, CyclicFactor* cyc = nullptr);
+int build_chunk(const Band& band, int n, int m, ChunkTables* out, CyclicFactor* cyc = nullptr);
+// Chunk lengths for n unknowns: the fewest chunks of at most M, and of those
+// splits the longest m whose remainder r is at least 3P.  False if there is
+// none (n < 3P).
+bool ragged_split(int P, int n, int M, int* m, int* r, int* S);
+int build_ragged(const Band& band, int n, int M, RaggedTables* out, CyclicFactor* cyc = nullptr);
 
 }  // namespace chx
