@@ -361,7 +361,12 @@ int ch_adi_step_timed(chx_ch h, double* c_inout, long ld, int nsteps,
                       double* diag_out, void* ws, size_t ws_bytes, chx_stream s,
                       int sample_every, double* phase_ms, int* phase_launches);
 
-/* Kernel choices of the FP64 step (autotuning).
+/* Kernel choices of the FP64 step (autotuning).  Unforced P1 handles of up to
+ * 2^20 points and 1024 rows, and of any size that the chunked passes do not
+ * take (as far as one workgroup holds a few of its columns), step by two
+ * launches of their own: whole columns, then rows.  Setting any choice but
+ * CHX_TUNE_GRAPH turns that off for a grid that the chunked passes take, and
+ * the choices below then apply; the two agree to rounding.
  * CHX_TUNE_SMALL_PATH: grids with nx % 64 == 0, ny % 32 == 0, nx ny <= 16384
  *   and an LDS footprint of 9.25 bytes per point (151.5 KB at 128 x 128) that
  *   the device's per-workgroup LDS holds run every step of a call in ONE

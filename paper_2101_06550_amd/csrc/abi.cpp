@@ -137,8 +137,10 @@ int upload(BandPlan* p) {
     DevRagged& d = p->dragged;
     d.n = p->n;
     d.P = p->P;
+    d.M = p->ragged.M;
     d.m = p->ragged.m;
     d.r = p->ragged.r;
+    d.even = d.m == d.M && d.r == d.M;
     d.S = p->ragged.S;
     d.dlo = p->ragged.dlo;
     d.dcount = p->ragged.dcount;
@@ -185,9 +187,11 @@ bool finite_all(const double* v, int n) {
 }
 
 // Build (host) and upload (device) a band plan.
+// ragged: chunk length of the ragged tables (0: 32 for the lengths that do not
+// split into 32-point chunks).
 template <class PlanT>
 int make_plan(int P, int n, const double* coef, int periodic, PlanT** out,
-              bool chunk16 = false) {
+              bool chunk16 = false, int ragged = 0) {
   if (!out) return CHX_EINVAL;
   *out = nullptr;
   const int nmin = (P == 2) ? 5 : 3;
@@ -212,8 +216,8 @@ int make_plan(int P, int n, const double* coef, int periodic, PlanT** out,
     p->has_chunk = (rc == CHX_OK);
     if (rc == CHX_EINVAL) rc = CHX_OK;  // shape not eligible: keep the whole-system path
   }
-  if (rc == CHX_OK && p->periodic && !p->has_chunk) {
-    rc = build_ragged(band, n, kChunk, &p->ragged, &cyc);
+  if (rc == CHX_OK && p->periodic && (ragged > 0 || !p->has_chunk)) {
+    rc = build_ragged(band, n, ragged > 0 ? ragged : kChunk, &p->ragged, &cyc);
     p->has_ragged = (rc == CHX_OK);
     if (rc == CHX_EINVAL) rc = CHX_OK;  // too short: the whole-system path
   }
@@ -315,11 +319,11 @@ hipError_t solve_refined(const BandPlan* p, int batch, double* x, long ld, int l
 hipError_t solve_il(const BandPlan* p, double* x, long ld, int batch, double* rho,
                     hipStream_t st) {
   if (p->has_chunk && il_fused_systems(p->dchunk.S, batch) > 0)
-    return launch_il_fused(p->dchunk, -1, x, ld, batch, 1, 0.0, 0.0, st);
+    return launch_il_fused(as_ragged(p->dchunk), -1, x, ld, batch, 1, 0.0, 0.0, st);
   if (p->has_chunk && rho)
     return p->P == 2 ? launch_chunked_il<2>(p->dchunk, x, ld, batch, rho, st)
                      : launch_chunked_il<1>(p->dchunk, x, ld, batch, rho, st);
-  if (p->has_ragged && il_fused_systems(p->dragged.S, batch) > 0)
+  if (p->has_ragged && p->dragged.M == kChunk && il_fused_systems(p->dragged.S, batch) > 0)
     return launch_il_fused(p->dragged, -1, x, ld, batch, 1, 0.0, 0.0, st);
   return p->P == 2 ? launch_whole<2>(p->dwhole, x, 1, ld, batch, st)
                    : launch_whole<1>(p->dwhole, x, 1, ld, batch, st);
@@ -330,8 +334,9 @@ hipError_t solve_rows(const BandPlan* p, double* x, long ld, int batch, bool str
   if (p->has_chunk && p->chunk.S <= 256)
     return p->P == 2 ? launch_rows_lds<2>(p->dchunk, x, ld, batch, st, stream_in)
                      : launch_rows_lds<1>(p->dchunk, x, ld, batch, st, stream_in);
-  if (p->has_ragged && rows_ragged_fits(p->dragged))
-    return launch_rows_ragged(p->dragged, x, ld, batch, st);
+  if (p->has_ragged && rows_any_fits(p->dragged))
+    return launch_rows_any(p->dragged, x, ld, x, ld, batch, nullptr,
+                           (long)batch * p->n >= 1L << 21, st);
   return p->P == 2 ? launch_whole<2>(p->dwhole, x, ld, 1, batch, st)
                    : launch_whole<1>(p->dwhole, x, ld, 1, batch, st);
 }
@@ -380,6 +385,9 @@ struct chx_ch_s {
   bool fast = false;
   bool small_ok = false;  // the single-workgroup LDS-resident path fits
   bool small = false;     // ... and is in use
+  // two launches per step (whole columns, rows), each direction in this plan
+  // (the plans' ragged tables)
+  bool pair = false;
   int split = -1;         // split row pass shape (-1: plain separators + rows,
                           // kSplitOverlap: separators beside the interior rows)
   int col_order = 0;      // tile order of the column pass (CHX_TUNE_COLUMN_ORDER)
@@ -771,7 +779,7 @@ int batch1d_step(chx_batch1d b, int batch, double* x, long ld, int nsteps, void*
   // systems that a workgroup holds take all steps of the call in one launch
   const BandPlan* p = b->plan;
   if (p->has_chunk && il_fused_systems(p->dchunk.S, batch) > 0)
-    return launch_il_fused(p->dchunk, b->kind, x, ld, batch, nsteps, b->s, b->al,
+    return launch_il_fused(as_ragged(p->dchunk), b->kind, x, ld, batch, nsteps, b->s, b->al,
                            static_cast<hipStream_t>(s)) == hipSuccess ? CHX_OK : CHX_EHIP;
   if (p->has_ragged && il_fused_systems(p->dragged.S, batch) > 0)
     return launch_il_fused(p->dragged, b->kind, x, ld, batch, nsteps, b->s, b->al,
@@ -1386,6 +1394,34 @@ extern "C" {
 static_assert(kNumRedShapes == CHX_NUM_REDUCED_SHAPES, "shape count mismatch");
 static_assert(kNumSplitShapes == CHX_NUM_SPLIT_SHAPES, "shape count mismatch");
 
+// Grids of at most this many points, and columns of at most this many, step by
+// whole columns and rows also where the chunked passes could: two launches of
+// short chunks against three of longer ones and a final pass, which up to here
+// are latency, not bytes (eight steps a call: 256 x 256 78 us against 134, 512
+// x 512 102 against 155, 1024 x 1024 184 against 199; 256 x 2048 189 against
+// 176: long columns leave few workgroups).
+constexpr long kPairPoints = 1L << 20;
+constexpr int kPairColumn = 1024;
+// ... and of this many take their final mass and energy in one launch.
+constexpr long kDiagSmall = 1L << 15;
+
+// Chunk length of the two-launch step for columns (of an nx-point wide grid)
+// or rows of n points: the shortest whose chunks a workgroup holds, since the
+// chain of one chunk is what a step of a small grid waits for; 8 points for
+// lengths they divide or a few of them cover (a short last chunk costs each
+// separator sum its scalar loads: 700 x 700 24.3 us per step with 8, 22.6 with
+// 16; 1000 x 1000, even in 8, 22.6 against 29.3 with 16 and 36.6 with 32).
+// 0 if none fits.
+static int pair_chunk(int n, bool column, int nx) {
+  for (int M : {8, 16, kChunk}) {
+    int m, r, S;
+    if (M == 8 && n % 8 != 0 && n > 256) continue;
+    if (!ragged_split(2, n, M, &m, &r, &S)) continue;
+    if (column ? column_whole_columns(nx, S) > 0 : S <= 256) return M;
+  }
+  return 0;
+}
+
 int ch_create(const chx_ch_params* prm, chx_ch* out) {
   if (!prm || !out) return CHX_EINVAL;
   *out = nullptr;
@@ -1412,8 +1448,19 @@ int ch_create(const chx_ch_params* prm, chx_ch* out) {
   // FP64 P1 handles also carry 16-point chunk tables: on small grids the
   // shorter serial sweeps may beat the 32-point ones (the tuner decides)
   const bool c16 = q.scheme == CHX_SCHEME_P1 && q.dtype == CHX_F64;
-  int rc = make_plan(2, q.nx, cxs, 1, &h->px, c16);
-  if (rc == CHX_OK) rc = make_plan(2, q.ny, cys, 1, &h->py, c16);
+  // whole columns and rows (odd grids as far as a workgroup holds their
+  // columns, and the smaller of the others)
+  const bool chunked = q.nx % 64 == 0 && q.ny % kChunk == 0 && q.nx / kChunk <= 256;
+  int pair_y = 0, pair_x = 0;
+  if (c16 && (!chunked || ((long)q.nx * q.ny <= kPairPoints && q.ny <= kPairColumn))) {
+    pair_y = pair_chunk(q.ny, true, q.nx);
+    pair_x = pair_chunk(q.nx, false, q.nx);
+    h->pair = pair_y > 0 && pair_x > 0;
+    if (!h->pair) pair_y = pair_x = 0;
+  }
+  int rc = make_plan(2, q.nx, cxs, 1, &h->px, c16, pair_x);
+  if (rc == CHX_OK) rc = make_plan(2, q.ny, cys, 1, &h->py, c16, pair_y);
+  h->pair = h->pair && rc == CHX_OK && h->px->has_ragged && h->py->has_ragged;
   if (rc != CHX_OK) {
     delete h;
     return rc;
@@ -1448,6 +1495,8 @@ int ch_create(const chx_ch_params* prm, chx_ch* out) {
     delete h;
     return CHX_EREFINE;
   }
+  h->small_ok = h->fast && q.dtype == CHX_F64 && ch_small_fits(q.nx, q.ny, device_max_lds());
+  h->small = h->small_ok;
   const size_t field = align256((size_t)q.nx * q.ny * sizeof(double));
   const long diag_parts = ch_diag_partial_blocks(q.nx, q.ny);
   size_t off = 0;
@@ -1485,6 +1534,8 @@ int ch_create(const chx_ch_params* prm, chx_ch* out) {
     }
     h->part_count = diag_parts;
   }
+  if (h->pair)
+    h->part_count = std::max(h->part_count, column_whole_blocks(q.nx, h->py->dragged.S));
   h->off_part = off;
   off += align256((size_t)h->part_count * 2 * sizeof(double));
   h->ws_total = off;
@@ -1494,8 +1545,6 @@ int ch_create(const chx_ch_params* prm, chx_ch* out) {
     delete h;
     return CHX_EHIP;
   }
-  h->small_ok = h->fast && q.dtype == CHX_F64 && ch_small_fits(q.nx, q.ny, device_max_lds());
-  h->small = h->small_ok;
   if (h->fast && q.dtype == CHX_F64) {
     if (hipStreamCreateWithFlags(&h->side, hipStreamNonBlocking) != hipSuccess ||
         hipEventCreateWithFlags(&h->ev_fork, hipEventDisableTiming) != hipSuccess ||
@@ -1541,6 +1590,7 @@ int ch_get_tuning(chx_ch h, int what, int* value) {
 int ch_set_tuning(chx_ch h, int what, int value) {
   if (!h) return CHX_EINVAL;
   h->drop_graph();  // a captured call holds the old choices
+  if (what != CHX_TUNE_GRAPH && h->fast) h->pair = false;
   switch (what) {
     case CHX_TUNE_GRAPH:
       if (value != 0 && value != 1) return CHX_EINVAL;
@@ -1726,6 +1776,35 @@ static int run_steps(chx_ch h, double* c, long ld, int nsteps, double* diag_out,
     }
     if (tm && tm->failed) return CHX_EHIP;
     return ok() ? CHX_OK : CHX_EHIP;
+  } else if (h->pair && !noise) {
+    // whole columns into the workspace, rows back into the field; the rows'
+    // launch also finishes the diagnostics of the state before the step
+    double* r = reinterpret_cast<double*>(base + (h->fast ? h->off_b0 : h->off_r));
+    DiagTail tail;
+    tail.part = part;
+    tail.n = column_whole_blocks(nx, h->py->dragged.S);
+    tail.scale = h->K.dxdy;
+    for (int n = 0; n < nsteps && ok(); ++n) {
+      if (tm) tm->step(n);
+      B();
+      e = launch_column_whole(h->py->dragged, c, ld, r, nx, nx, ny, h->K, diag_out ? part : nullptr,
+                              st);
+      E(0);
+      if (ok()) {
+        tail.out = diag_out ? diag_out + 2 * n : nullptr;
+        B();
+        e = launch_rows_any(h->px->dragged, r, nx, c, ld, ny, diag_out ? &tail : nullptr, false, st);
+        E(2);
+      }
+    }
+    if (ok() && diag_out && (long)nx * ny <= kDiagSmall) {
+      if (tm) tm->on = true;
+      B();
+      e = launch_diag_small(c, ld, nx, ny, h->K, diag_out + 2 * nsteps, st);
+      E(3);
+      if (tm && tm->failed) return CHX_EHIP;
+      return ok() ? CHX_OK : CHX_EHIP;
+    }
   } else if (h->small) {
     // one workgroup, field resident in LDS for all steps; it also writes the
     // diagnostics of every state, the final one included

@@ -33,13 +33,6 @@ constexpr int M = kChunk;
 constexpr int P = 2;
 constexpr int MI = M - P;
 
-// Wave-level fixed-order butterfly sum (deterministic).
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
-
 // Block (256 threads) fixed-order sum of two values; result valid in thread 0.
 __device__ __forceinline__ void block_sum2(double& a, double& b, double* sh) {
   a = wave_sum(a);

@@ -38,6 +38,19 @@ hipError_t launch_ch2_update(const double* c, long ldc, const double* cp, long l
                              const double* v, long ldv, double* out, double* out_prev, long ld,
                              int nx, int ny, const DevChunk* recon, hipStream_t st);
 
+// Right-hand side and column solves of one step, columns solved and corrected
+// (fused.hip): src -> dst, which must not be src.  dpart: (mass, energy)
+// partials of src, one pair per workgroup (column_whole_blocks).
+// column_whole_columns: columns per workgroup, 0 where they are too long.
+int column_whole_columns(int nx, int S);
+long column_whole_blocks(int nx, int S);
+hipError_t launch_column_whole(const DevRagged& c, const double* src, long lds, double* dst,
+                               long ldd, int nx, int ny, const ChCoef& K, double* dpart,
+                               hipStream_t st);
+// Mass and energy of a small field in one launch of one workgroup.
+hipError_t launch_diag_small(const double* c, long ld, int nx, int ny, const ChCoef& K,
+                             double* out, hipStream_t st);
+
 // q != nullptr: the Cahn-Hilliard-Cook increment (pitch nx) is added to the
 // right-hand side.
 // Cahn-Hilliard-Cook forcing drawn inside a kernel: generator state

@@ -46,6 +46,13 @@ __device__ __forceinline__ int wrap_once(int j, int S) {
   return j;
 }
 
+// Wave-level fixed-order butterfly sum (deterministic).
+__device__ __forceinline__ double wave_sum(double v) {
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+  return v;
+}
+
 // Streaming 16-byte global accesses (non-temporal: the data is touched once
 // per pass).  On gfx950 a plain copy moves 6.5 TB/s with non-temporal loads
 // and stores against 5.6 TB/s with ordinary ones; in the step's passes the

@@ -27,14 +27,14 @@
 // chunk's own last row.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
+#include "ch_launch.hpp"
 #include "common.hpp"
-#include "launch.hpp"
 
 namespace chx {
 
 namespace {
-
-constexpr int M = kChunk;
 
 // Family of the reduced block that takes chunk j (unwrapped) to chunk k.
 __device__ __forceinline__ int rag_family(int k, int j, int S) {
@@ -72,7 +72,7 @@ __device__ __forceinline__ int fresh(int v) {
 
 // Sweep of a chunk whose interior is f[0 .. li): y in place, zero beyond; t1
 // and t2 the interior's last two unknowns (y[li - 1], y[li - 2]).
-template <int P>
+template <int P, int M>
 __device__ __forceinline__ void ragged_sweep(double (&f)[M], int li, TabD rec, double eps,
                                              double& t1, double& t2) {
   constexpr int MI = M - P;
@@ -98,7 +98,7 @@ __device__ __forceinline__ void ragged_sweep(double (&f)[M], int li, TabD rec, d
 // pa: the separators' reduced right-hand sides but for the next chunk's part;
 // pb: this chunk's part for the previous chunk's separators (chunk_parts with
 // the interior's last unknowns given).
-template <int P>
+template <int P, int M>
 __device__ __forceinline__ void ragged_parts(const double (&f)[M], const double (&fs)[P],
                                              double t1, double t2, const BandT<double>& bd,
                                              double (&pa)[P], double (&pb)[P]) {
@@ -115,7 +115,7 @@ __device__ __forceinline__ void ragged_parts(const double (&f)[M], const double 
 
 // x = y - Zl sp - Zr so in the interior.  A wave that holds last chunks runs both tables, each chunk's separators masked to
 // zero for the other's.
-template <int P>
+template <int P, int M>
 __device__ __forceinline__ void ragged_correct(double (&f)[M], bool last, TabD rec, TabD recl,
                                                const double (&sp)[P], const double (&so)[P]) {
   constexpr int MI = M - P;
@@ -162,6 +162,37 @@ __device__ __forceinline__ void store(double* p, double v) {
   else *p = v;
 }
 
+// Lane l of a 16-lane row receives the value of lane l - 1 (row_shr:1), lane
+// 0 of the row keeps `edge`; and the other way round.
+__device__ __forceinline__ double dpp_row_from_left(double v, double edge) {
+  const int lo = __builtin_amdgcn_update_dpp(__double2loint(edge), __double2loint(v), 0x111, 0xF,
+                                             0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(__double2hiint(edge), __double2hiint(v), 0x111, 0xF,
+                                             0xF, false);
+  return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double dpp_row_from_right(double v, double edge) {
+  const int lo = __builtin_amdgcn_update_dpp(__double2loint(edge), __double2loint(v), 0x101, 0xF,
+                                             0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(__double2hiint(edge), __double2hiint(v), 0x101, 0xF,
+                                             0xF, false);
+  return __hiloint2double(hi, lo);
+}
+
+// Brings a plan table of N lines of 64 bytes into the scalar cache: one load
+// per line, all in flight together, while the chunk's own loads are.  A
+// kernel starts with that cache empty, and the sweeps that read the table
+// hold few lines at a time, so without this each of them waits on memory.
+template <int N>
+__device__ __forceinline__ void warm(const double* p) {
+  using Line = const __attribute__((address_space(4))) unsigned*;
+  const Line u = (Line)p;
+  unsigned x = 0;
+#pragma unroll
+  for (int i = 0; i < N; ++i) x |= u[16 * i];
+  asm volatile("" ::"s"(x));
+}
+
 struct FusedArgs {
   double* x;
   long ld;
@@ -172,12 +203,102 @@ struct FusedArgs {
   double s, al;
 };
 
+// LDS the ragged blocks take (stage_blocks), in doubles.
+template <bool RAG>
+__host__ __device__ __forceinline__ int blocks_lds(int dcount) {
+  return RAG ? 12 * dcount : 0;
+}
+
+// The ragged blocks go to LDS (a barrier follows before they are read): their
+// family differs from lane to lane, so they cannot be scalar loads.
+template <bool RAG>
+__device__ __forceinline__ void stage_blocks(const FusedArgs& A, double* lds) {
+  if constexpr (RAG) {
+    for (int e = threadIdx.x; e < 12 * A.dcount; e += blockDim.x) lds[e] = A.blocks[e];
+  }
+}
+
+// The separators of chunk k from the reduced right-hand sides of its system,
+// value a of chunk j at rho[a plane + j step], summed in the order of the
+// separator kernels in solve.hip; four terms' loads are issued together.
+template <int P, bool RAG>
+__device__ __forceinline__ void separators(const FusedArgs& A, const double* blocks, int k,
+                                           const double* rho, int plane, int step,
+                                           double (&so)[P]) {
+#pragma unroll
+  for (int a = 0; a < P; ++a) so[a] = 0;
+  int j = k + A.dlo, jw = j + (j < 0 ? A.S : 0);  // unwrapped and wrapped
+  auto terms = [&](auto count, int t) {
+    constexpr int N = decltype(count)::value;
+    double w[N][P], B[N][P * P];
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+#pragma unroll
+      for (int a = 0; a < P; ++a) w[u][a] = rho[a * plane + jw * step];
+      if constexpr (RAG) {
+        const double* b = blocks + 4 * (A.dcount * rag_family(k, j, A.S) + t + u);
+#pragma unroll
+        for (int q = 0; q < P * P; ++q) B[u][q] = b[(q / P) * 2 + q % P];
+      } else {
+        const TabD b = (TabD)A.blocks + 4 * (t + u);
+#pragma unroll
+        for (int q = 0; q < P * P; ++q) B[u][q] = b[(q / P) * 2 + q % P];
+      }
+      ++j;
+      jw = jw + 1 == A.S ? 0 : jw + 1;
+    }
+#pragma unroll
+    for (int u = 0; u < N; ++u)
+#pragma unroll
+      for (int a = 0; a < P; ++a)
+#pragma unroll
+        for (int b = 0; b < P; ++b) so[a] = so[a] + B[u][a * P + b] * w[u][b];
+  };
+  int t = 0;
+#pragma unroll 1
+  for (; t + 4 <= A.dcount; t += 4) terms(std::integral_constant<int, 4>{}, t);
+#pragma unroll 1
+  for (; t < A.dcount; ++t) terms(std::integral_constant<int, 1>{}, t);
+}
+
+// Sum of two values over the workgroup in a fixed order, valid in thread 0;
+// red: two doubles per wave.
+__device__ __forceinline__ void group_sum2(double& m, double& e, double* red) {
+  m = wave_sum(m);
+  e = wave_sum(e);
+  if ((threadIdx.x & 63) == 0) {
+    red[2 * (threadIdx.x >> 6)] = m;
+    red[2 * (threadIdx.x >> 6) + 1] = e;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0)
+    for (int w = 1; w < (int)blockDim.x / 64; ++w) {
+      m += red[2 * w];
+      e += red[2 * w + 1];
+    }
+}
+
+// The state's (mass, energy) from the n partials column_whole's workgroups
+// left, by one workgroup.
+__device__ __forceinline__ void diag_tail(const DiagTail& d, double* sm) {
+  double m = 0.0, e = 0.0;
+  for (long b = threadIdx.x; b < d.n; b += blockDim.x) {
+    m += d.part[2 * b];
+    e += d.part[2 * b + 1];
+  }
+  group_sum2(m, e, sm);
+  if (threadIdx.x == 0) {
+    d.out[0] = m * d.scale;
+    d.out[1] = e * d.scale;
+  }
+}
+
 }  // namespace
 
 // KIND -1: one solve of the right-hand sides in x; KIND 0 .. 2: nsteps steps of
 // a 1D scheme from the state in x.  In place: a workgroup owns its systems and
 // loads all of them before it stores.
-template <int P, int L, bool RAG, int KIND, bool LINES>
+template <int P, int L, bool RAG, int KIND, bool LINES, int M = kChunk>
 __global__ __launch_bounds__(1024) void il_fused(const FusedArgs A) {
   constexpr int MI = M - P;
   extern __shared__ double sm[];
@@ -190,6 +311,7 @@ __global__ __launch_bounds__(1024) void il_fused(const FusedArgs A) {
   const long sl = sys < A.batch ? sys : (long)A.batch - 1;
   double* const part = sm;              // [P][S][L]: parts for the previous chunk, then separators
   double* const rho = sm + P * S * L;   // [P][S][L]: reduced right-hand sides, then first unknowns
+  double* const blk = sm + 2 * P * S * L;
   const int me = k * L + c;             // this thread's element of a plane
   const int nx = (k + 1 == S ? 0 : k + 1) * L + c, pv = (k == 0 ? S - 1 : k - 1) * L + c;
   const int plane = S * L;
@@ -216,6 +338,7 @@ __global__ __launch_bounds__(1024) void il_fused(const FusedArgs A) {
       for (int a = 0; a < P; ++a) fs[a] = f[MI + a];
     }
   }
+  stage_blocks<RAG>(A, blk);
   double sp[P];  // the previous chunk's separators
   if constexpr (KIND >= 0) {
     // the state's chunk ends: the previous chunk's separators (registers),
@@ -266,7 +389,7 @@ __global__ __launch_bounds__(1024) void il_fused(const FusedArgs A) {
     double t1 = 0, t2 = 0;  // the interior's last two unknowns
     const double eps = A.bd.c[0];
     if constexpr (RAG) {
-      ragged_sweep<P>(f, li, rec, eps, t1, t2);
+      ragged_sweep<P, M>(f, li, rec, eps, t1, t2);
     } else {
 #pragma unroll
       for (int a = 0; a < P; ++a) fs[a] = f[MI + a];
@@ -275,7 +398,7 @@ __global__ __launch_bounds__(1024) void il_fused(const FusedArgs A) {
       t2 = f[MI - 2];
     }
     double pa[P], pb[P];
-    ragged_parts<P>(f, fs, t1, t2, A.bd, pa, pb);
+    ragged_parts<P, M>(f, fs, t1, t2, A.bd, pa, pb);
     if (active) {
 #pragma unroll
       for (int a = 0; a < P; ++a) part[a * plane + me] = pb[a];
@@ -289,28 +412,7 @@ __global__ __launch_bounds__(1024) void il_fused(const FusedArgs A) {
     }
     __syncthreads();
     double so[P];
-#pragma unroll
-    for (int a = 0; a < P; ++a) so[a] = 0;
-    int j = k + A.dlo;
-    j += j < 0 ? S : 0;
-    if (j < 0) j += S;
-    if (j >= S) j -= S;
-    for (int t = 0; t < A.dcount; ++t) {
-      double w[P];
-#pragma unroll
-      for (int a = 0; a < P; ++a) w[a] = rho[a * plane + j * L + c];
-      auto add = [&](auto B) {
-#pragma unroll
-        for (int a = 0; a < P; ++a)
-#pragma unroll
-          for (int b = 0; b < P; ++b) so[a] = so[a] + B[a * 2 + b] * w[b];
-      };
-      if constexpr (RAG)
-        add(A.blocks + 4 * (A.dcount * rag_family(k, k + A.dlo + t, S) + t));
-      else
-        add((TabD)A.blocks + 4 * t);
-      j = j + 1 == S ? 0 : j + 1;
-    }
+    separators<P, RAG>(A, blk, k, rho + c, plane, L, so);
     if (active) {
 #pragma unroll
       for (int a = 0; a < P; ++a) part[a * plane + me] = so[a];
@@ -319,7 +421,7 @@ __global__ __launch_bounds__(1024) void il_fused(const FusedArgs A) {
 #pragma unroll
     for (int a = 0; a < P; ++a) sp[a] = part[a * plane + pv];
     if constexpr (RAG) {
-      ragged_correct<P>(f, last, table(A.rec), table(A.recl), sp, so);
+      ragged_correct<P, M>(f, last, table(A.rec), table(A.recl), sp, so);
       if constexpr (KIND >= 0) {  // the state's chunk again: unknowns 0 .. len - 1
         const int lj = fresh(li);
 #pragma unroll
@@ -363,55 +465,116 @@ __global__ __launch_bounds__(1024) void il_fused(const FusedArgs A) {
 // 32 of element e of the group, which spreads the threads' chunks over the
 // banks), so memory sees whole lines; two accesses per unknown.
 // Bound by HBM and, at two workgroups of LDS per CU, by how much of its
-// latency they cover: 20000 rows of 1000 points 73 us, 4.4 TB/s (79 us with a
+// latency they cover: 20000 rows of 1000 points 70 us, 4.6 TB/s (79 us with a
 // thread's 32 loads issued 8 at a time; one thread per row: 800 us, every lane
-// on a line of its own, 32 waves of them in all).
-template <int P>
-__global__ __launch_bounds__(256) void rows_ragged(double* x, long ld, int rows, int n, int R,
-                                                   const FusedArgs A) {
+// on a line of its own, 313 waves of them in all).
+// RAG as above, else rows of S M points (bitwise what the other
+// row kernels give).  From src to dst, which may be the same array.  stream:
+// the stores go past the caches, each as its value leaves LDS (large solves:
+// 20000 rows of 1000 70 us, 80 with all of a thread's values read first);
+// otherwise all at once and through the caches (1000 rows of 500 10.0 us
+// against 10.9; the step's column kernel reads the rows again: 1000 x 1000
+// 21.2 us per step, 22.1 streamed).  With
+// tail.out, the launch's last workgroup solves no rows: it finishes the
+// (mass, energy) of the state that the column kernel before it has read.
+template <int P, int M, bool RAG>
+__global__ __launch_bounds__(256) void rows_any(const double* src, long lds, double* dst, long ldd,
+                                                int rows, int n, unsigned magic, int R,
+                                                const FusedArgs A, const DiagTail tail,
+                                                const bool stream) {
   extern __shared__ double sm[];
+  if (tail.out != nullptr && blockIdx.x == gridDim.x - 1) {
+    diag_tail(tail, sm);
+    return;
+  }
   const int S = A.S, T = blockDim.x, t = threadIdx.x;
   const long row0 = (long)blockIdx.x * R;
   const int nr = rows - row0 < R ? (int)(rows - row0) : R;
   const int nel = nr * n;
   double* const part = sm;           // [P][T]
   double* const rho = sm + P * T;    // [P][T]
-  double* const tile = sm + 2 * P * T;
+  double* const blk = sm + 2 * P * T;
+  double* const tile = blk + blocks_lds<RAG>(A.dcount);
   const int rt = t / S;
   const bool active = rt < nr;
   const int r = active ? rt : nr - 1, k = active ? t - rt * S : S - 1;
   const bool last = k == S - 1;
-  const int len = last ? A.r : A.m, li = len - P;
-  const bool dense = ld == n;
-  double* const xg = x + row0 * ld;
-  auto at = [&](int e) -> long { return dense ? (long)e : (long)(e / n) * ld + e % n; };
-  constexpr int U = M;  // every load of a thread in flight
-  for (int e0 = t; e0 < nel; e0 += U * T) {
-    double v[U];
+  const int len = RAG ? (last ? A.r : A.m) : M, li = len - P;
+  const double* const xs = src + row0 * lds;
+  double* const xd = dst + row0 * ldd;
+  // element e of the group is row e / n (magic = ceil(2^32 / n): exact for the
+  // 13 bits of both)
+  auto at = [&](int e, long ld) -> long {
+    const unsigned q = __umulhi((unsigned)e, magic);
+    return (long)q * ld + (e - (int)q * n);
+  };
+  auto slot = [](int e) { return e + e / M; };
+  // a thread's at most M elements, every load in flight; pairs where the
+  // group is one aligned range
+  auto pairs = [&](const double* p, long ld) {
+    return ld == n && (reinterpret_cast<unsigned long>(p) & 15) == 0;
+  };
+  {
+    double v[M], odd = 0.0;
+    const bool two = pairs(xs, lds);
+    if (two) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int e = e0 + u * T;
-      v[u] = __builtin_nontemporal_load(xg + at(e < nel ? e : nel - 1));
+      for (int u = 0; u < M / 2; ++u) {
+        const int e = 2 * (t + u * T);
+        typedef double dv2 __attribute__((ext_vector_type(2)));
+        // (past the last pair: the first again, not used)
+        const dv2 w = __builtin_nontemporal_load(
+            reinterpret_cast<const dv2*>(xs + (e + 1 < nel ? e : 0)));
+        v[2 * u] = w.x;
+        v[2 * u + 1] = w.y;
+      }
+      if (nel & 1) odd = xs[nel - 1];
+    } else {
+#pragma unroll
+      for (int u = 0; u < M; ++u) {
+        const int e = t + u * T;
+        v[u] = __builtin_nontemporal_load(xs + at(e < nel ? e : nel - 1, lds));
+      }
     }
+    stage_blocks<RAG>(A, blk);
+    warm<M - P>(A.rec);
+    if (two) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int e = e0 + u * T;
-      if (e < nel) tile[e + (e >> 5)] = v[u];
+      for (int u = 0; u < M / 2; ++u) {
+        const int e = 2 * (t + u * T);
+        if (e + 1 < nel) {
+          tile[slot(e)] = v[2 * u];
+          tile[slot(e + 1)] = v[2 * u + 1];
+        }
+      }
+      if ((nel & 1) && t == 0) tile[slot(nel - 1)] = odd;
+    } else {
+#pragma unroll
+      for (int u = 0; u < M; ++u) {
+        const int e = t + u * T;
+        if (e < nel) tile[slot(e)] = v[u];
+      }
     }
   }
   __syncthreads();
   double f[M];
-  const int e0 = r * n + k * A.m;
+  const int e0 = r * n + k * (RAG ? A.m : M);
 #pragma unroll
-  for (int p = 0; p < M; ++p) {
-    const int e = e0 + (p < len ? p : len - 1);  // past the chunk: its last unknown
-    f[p] = tile[e + (e >> 5)];
-  }
+  for (int p = 0; p < M; ++p)  // past the chunk: its last unknown
+    f[p] = tile[slot(e0 + (!RAG || p < len ? p : len - 1))];
   double fs[P], t1 = 0, t2 = 0, pa[P], pb[P];
+  if constexpr (RAG) {
 #pragma unroll
-  for (int a = 0; a < P; ++a) fs[a] = tile[e0 + li + a + ((e0 + li + a) >> 5)];
-  ragged_sweep<P>(f, li, table(A.rec), A.bd.c[0], t1, t2);
-  ragged_parts<P>(f, fs, t1, t2, A.bd, pa, pb);
+    for (int a = 0; a < P; ++a) fs[a] = tile[slot(e0 + li + a)];
+    ragged_sweep<P, M>(f, li, table(A.rec), A.bd.c[0], t1, t2);
+  } else {
+#pragma unroll
+    for (int a = 0; a < P; ++a) fs[a] = f[M - P + a];
+    chunk_sweep<P, M, double, TabD>(f, table(A.rec), A.bd.c[0]);
+    t1 = f[M - P - 1];
+    t2 = f[M - P - 2];
+  }
+  ragged_parts<P, M>(f, fs, t1, t2, A.bd, pa, pb);
   const int rs = r * S, me = rs + k;
   const int nx = rs + (k + 1 == S ? 0 : k + 1), pv = rs + (k == 0 ? S - 1 : k - 1);
   if (active) {
@@ -427,21 +590,7 @@ __global__ __launch_bounds__(256) void rows_ragged(double* x, long ld, int rows,
   }
   __syncthreads();
   double so[P], sp[P];
-#pragma unroll
-  for (int a = 0; a < P; ++a) so[a] = 0;
-  int j = k + A.dlo;
-  j += j < 0 ? S : 0;
-  for (int q = 0; q < A.dcount; ++q) {
-    double w[P];
-#pragma unroll
-    for (int a = 0; a < P; ++a) w[a] = rho[a * T + rs + j];
-    const double* B = A.blocks + 4 * (A.dcount * rag_family(k, k + A.dlo + q, S) + q);
-#pragma unroll
-    for (int a = 0; a < P; ++a)
-#pragma unroll
-      for (int b = 0; b < P; ++b) so[a] = so[a] + B[a * 2 + b] * w[b];
-    j = j + 1 == S ? 0 : j + 1;
-  }
+  separators<P, RAG>(A, blk, k, rho + rs, T, 1, so);
   if (active) {
 #pragma unroll
     for (int a = 0; a < P; ++a) part[a * T + me] = so[a];
@@ -449,17 +598,242 @@ __global__ __launch_bounds__(256) void rows_ragged(double* x, long ld, int rows,
   __syncthreads();
 #pragma unroll
   for (int a = 0; a < P; ++a) sp[a] = part[a * T + pv];
-  ragged_correct<P>(f, last, table(A.rec), table(A.recl), sp, so);
+  if constexpr (RAG) ragged_correct<P, M>(f, last, table(A.rec), table(A.recl), sp, so);
+  else chunk_correct<P, M, double, TabD>(f, table(A.rec), sp, so);
   if (active) {
-    const int lj = fresh(li);
+    const int lj = RAG ? fresh(li) : li;
 #pragma unroll
     for (int p = 0; p < M - P; ++p)
-      if (p < lj) tile[e0 + p + ((e0 + p) >> 5)] = f[p];
+      if (!RAG || p < lj) tile[slot(e0 + p)] = f[p];
 #pragma unroll
-    for (int a = 0; a < P; ++a) tile[e0 + lj + a + ((e0 + lj + a) >> 5)] = so[a];
+    for (int a = 0; a < P; ++a) tile[slot(e0 + lj + a)] = so[a];
   }
   __syncthreads();
-  for (int e = t; e < nel; e += T) __builtin_nontemporal_store(tile[e + (e >> 5)], xg + at(e));
+  if (stream && ldd == n) {
+    for (int e = t; e < nel; e += T) __builtin_nontemporal_store(tile[slot(e)], xd + e);
+  } else if (pairs(xd, ldd)) {
+    double2 v[M / 2];
+#pragma unroll
+    for (int u = 0; u < M / 2; ++u) {
+      const int e = 2 * (t + u * T), g = e + 1 < nel ? e : 0;
+      v[u].x = tile[slot(g)];
+      v[u].y = tile[slot(g + 1)];
+    }
+#pragma unroll
+    for (int u = 0; u < M / 2; ++u) {
+      const int e = 2 * (t + u * T);
+      if (e + 1 < nel) *reinterpret_cast<double2*>(xd + e) = v[u];
+    }
+    if ((nel & 1) && t == 0) xd[nel - 1] = tile[slot(nel - 1)];
+  } else {
+    double v[M];
+#pragma unroll
+    for (int u = 0; u < M; ++u) {
+      const int e = t + u * T;
+      v[u] = tile[slot(e < nel ? e : nel - 1)];
+    }
+#pragma unroll
+    for (int u = 0; u < M; ++u) {
+      const int e = t + u * T;
+      if (e < nel) __builtin_nontemporal_store(v[u], xd + at(e, ldd));
+    }
+  }
+}
+
+// One step's right-hand side and column solves of a periodic 2D field, from
+// src to dst (not the same array): a workgroup takes L columns and every
+// chunk of them, so the columns leave it solved and corrected.  Small and
+// odd grids: the step is this launch and the rows.
+// Thread (c, k) forms r on its chunk of column c from the rows around it
+// (registers) and the columns beside it (DPP lane shifts inside the tile; the
+// edge lanes load the columns outside it), in the expressions of the column
+// pass in ch.hip, and solves as il_fused does.  What bounds it is the chain
+// load, right-hand side, sweep, separators, correction, store of one chunk,
+// so every load of a thread is issued before its first row.
+// DIAG: a (mass, energy) partial of src per workgroup.
+template <int M, int L, bool RAG, bool DIAG>
+__global__ __launch_bounds__(512) void column_whole(const double* __restrict__ src, long lds,
+                                                    double* __restrict__ dst, long ldd, int nx,
+                                                    int ny, const ChCoef K,
+                                                    double* __restrict__ dpart,
+                                                    const FusedArgs A) {
+  constexpr int P = 2, MI = M - P;
+  extern __shared__ double sm[];
+  const int S = A.S;
+  const int c = threadIdx.x % L, kt = threadIdx.x / L;
+  const bool active = kt < S;
+  const int k = active ? kt : S - 1;
+  // the last tile starts early enough to be whole; its first columns are its
+  // neighbour's
+  const int t0 = (int)tile_of<false>(blockIdx.x, gridDim.x) * L;
+  const int i0 = t0 + L <= nx ? t0 : nx - L, i = i0 + c;
+  const bool sv = active && i >= t0;
+  double* const part = sm;
+  double* const rho = sm + P * S * L;
+  double* const blk = sm + 2 * P * S * L;
+  double* const dred = blk + blocks_lds<RAG>(A.dcount);
+  const int plane = S * L;
+  const int me = k * L + c;
+  const int nxt = (k + 1 == S ? 0 : k + 1) * L + c, prv = (k == 0 ? S - 1 : k - 1) * L + c;
+  const bool last = k == S - 1;
+  const int len = RAG ? (last ? A.r : A.m) : M;
+  const int li = len - P;
+  const int row0 = k * (RAG ? A.m : M);
+
+  double X[M + 2], E[M + 2];  // rows row0 - 1 .. row0 + len of the column; of the one outside
+  {
+    // lane 0 also loads the column left of the tile, its last lane the one right of it
+    const int ie = c == 0 ? (i == 0 ? nx - 1 : i - 1)
+                          : (c == L - 1 ? (i == nx - 1 ? 0 : i + 1) : i);
+    const long de = (long)ie - i;
+    const double* const up = src + (long)(row0 == 0 ? ny - 1 : row0 - 1) * lds + i;
+    const double* const dn = src + (long)(row0 + len == ny ? 0 : row0 + len) * lds + i;
+    const double* own = src + (long)row0 * lds + i;
+    X[0] = up[0];
+    E[0] = up[de];
+#pragma unroll
+    for (int q = 1; q <= M + 1; ++q) {  // past the chunk: the row after it
+      const double* const a = q <= (RAG ? len : M) ? own : dn;
+      X[q] = a[0];
+      E[q] = a[de];
+      own += lds;
+    }
+  }
+  stage_blocks<RAG>(A, blk);
+  warm<MI>(A.rec);
+  double f[M], fs[P] = {0, 0};
+  double msum = 0.0, esum = 0.0;
+  const double eps = A.bd.c[0];
+  {
+    auto left = [&](int q) {
+      double v = dpp_row_from_left(X[q], E[q]);
+      return L < 16 && c == 0 ? E[q] : v;
+    };
+    auto right = [&](int q) {
+      double v = dpp_row_from_right(X[q], E[q]);
+      return L < 16 && c == L - 1 ? E[q] : v;
+    };
+    double xc_m = X[0], xl_m = left(0), xr_m = right(0);
+    double xc_c = X[1], xl_c = left(1), xr_c = right(1);
+#pragma unroll
+    for (int p = 0; p < M; ++p) {
+      const double xc_p = X[p + 2], xl_p = left(p + 2), xr_p = right(p + 2);
+      const double mu_c = xc_c * xc_c * xc_c - xc_c;
+      const double mu_l = xl_c * xl_c * xl_c - xl_c;
+      const double mu_r = xr_c * xr_c * xr_c - xr_c;
+      const double mu_s = xc_m * xc_m * xc_m - xc_m;
+      const double mu_n = xc_p * xc_p * xc_p - xc_p;
+      const double lap = K.cx * (mu_r + mu_l - 2.0 * mu_c) + K.cy * (mu_n + mu_s - 2.0 * mu_c);
+      const double dyy_w = xl_p + xl_m - 2.0 * xl_c;
+      const double dyy_c = xc_p + xc_m - 2.0 * xc_c;
+      const double dyy_e = xr_p + xr_m - 2.0 * xr_c;
+      double r = xc_c + lap - K.ccross * (dyy_e + dyy_w - 2.0 * dyy_c);
+      if (DIAG) {
+        const double w = xc_c * xc_c - 1.0;
+        const double gx = (xr_c - xc_c) * K.inv_dx, gy = (xc_p - xc_c) * K.inv_dy;
+        const bool in = !RAG || p < len;
+        msum += in ? xc_c : 0.0;
+        const double ee = 0.25 * w * w + K.half_gamma * (gx * gx + gy * gy);
+        esum += in ? ee : 0.0;
+      }
+      f[p] = r;
+      if constexpr (RAG) {
+#pragma unroll
+        for (int a = 0; a < P; ++a) {
+          fs[a] = p == li + a ? r : fs[a];
+          asm volatile("" : "+v"(fs[a]));
+        }
+      }
+      xl_m = xl_c; xc_m = xc_c; xr_m = xr_c;
+      xl_c = xl_p; xc_c = xc_p; xr_c = xr_p;
+    }
+  }
+  double t1 = 0, t2 = 0, pa[P], pb[P];
+  if constexpr (RAG) {
+    ragged_sweep<P, M>(f, li, table(A.rec), eps, t1, t2);
+  } else {
+#pragma unroll
+    for (int a = 0; a < P; ++a) fs[a] = f[MI + a];
+    chunk_sweep<P, M, double, TabD>(f, table(A.rec), eps);
+    t1 = f[MI - 1];
+    t2 = f[MI - 2];
+  }
+  ragged_parts<P, M>(f, fs, t1, t2, A.bd, pa, pb);
+  if (active) {
+#pragma unroll
+    for (int a = 0; a < P; ++a) part[a * plane + me] = pb[a];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int a = 0; a < P; ++a) pa[a] -= part[a * plane + nxt];
+  if (active) {
+#pragma unroll
+    for (int a = 0; a < P; ++a) rho[a * plane + me] = pa[a];
+  }
+  __syncthreads();
+  double so[P], sp[P];
+  separators<P, RAG>(A, blk, k, rho + c, plane, L, so);
+  if (active) {
+#pragma unroll
+    for (int a = 0; a < P; ++a) part[a * plane + me] = so[a];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int a = 0; a < P; ++a) sp[a] = part[a * plane + prv];
+  if constexpr (RAG) ragged_correct<P, M>(f, last, table(A.rec), table(A.recl), sp, so);
+  else chunk_correct<P, M, double, TabD>(f, table(A.rec), sp, so);
+  if (sv) {
+    double* p0 = dst + (long)row0 * ldd + i;
+    const int lj = RAG ? fresh(li) : li;
+#pragma unroll
+    for (int p = 0; p < MI; ++p)
+      if (!RAG || p < lj) __builtin_nontemporal_store(f[p], p0 + (long)p * ldd);
+#pragma unroll
+    for (int a = 0; a < P; ++a)
+      __builtin_nontemporal_store(so[a], p0 + (long)(lj + a) * ldd);
+  }
+  // the diagnostics' sums, while the stores drain
+  if (DIAG) {
+    msum = sv ? msum : 0.0;
+    esum = sv ? esum : 0.0;
+    group_sum2(msum, esum, dred);
+    if (threadIdx.x == 0) {
+      dpart[2 * blockIdx.x] = msum;
+      dpart[2 * blockIdx.x + 1] = esum;
+    }
+  }
+}
+
+// Mass and energy of a plain field by one workgroup: small grids, where a
+// second launch costs more than the sum.
+__global__ __launch_bounds__(1024) void diag_small(const double* __restrict__ c, long ld, int nx,
+                                                   int ny, const ChCoef K,
+                                                   double* __restrict__ out) {
+  __shared__ double red[2 * 16];
+  double m = 0.0, e = 0.0;
+  for (int j = threadIdx.x >> 6; j < ny; j += 16) {
+    const double* const row = c + (long)j * ld;
+    const double* const up = c + (long)(j + 1 == ny ? 0 : j + 1) * ld;
+    for (int i = threadIdx.x & 63; i < nx; i += 64) {
+      const double x = row[i];
+      const double gx = (row[i + 1 == nx ? 0 : i + 1] - x) * K.inv_dx;
+      const double gy = (up[i] - x) * K.inv_dy;
+      const double w = x * x - 1.0;
+      m += x;
+      e += 0.25 * w * w + K.half_gamma * (gx * gx + gy * gy);
+    }
+  }
+  group_sum2(m, e, red);
+  if (threadIdx.x == 0) {
+    out[0] = m * K.dxdy;
+    out[1] = e * K.dxdy;
+  }
+}
+
+hipError_t launch_diag_small(const double* c, long ld, int nx, int ny, const ChCoef& K,
+                             double* out, hipStream_t st) {
+  hipLaunchKernelGGL(diag_small, dim3(1), dim3(1024), 0, st, c, ld, nx, ny, K, out);
+  return hipGetLastError();
 }
 
 // Systems per workgroup (16, 32 or 64: whole lines of every row), or 0 where
@@ -478,7 +852,7 @@ int il_fused_systems(int S, int batch) {
 template <int P, int L, bool RAG, int KIND>
 static hipError_t fused_launch(const FusedArgs& a, hipStream_t st) {
   const dim3 grid((unsigned)((a.batch + L - 1) / L)), block(((L * a.S + 63) / 64) * 64);
-  const size_t lds = (size_t)2 * P * a.S * L * sizeof(double);
+  const size_t lds = ((size_t)2 * P * a.S * L + blocks_lds<RAG>(a.dcount)) * sizeof(double);
   if (a.ld % 16 == 0 && (reinterpret_cast<uintptr_t>(a.x) & 127) == 0)
     hipLaunchKernelGGL((il_fused<P, L, RAG, KIND, true>), grid, block, lds, st, a);
   else
@@ -504,50 +878,40 @@ static hipError_t fused_any(int kind, const FusedArgs& a, hipStream_t st) {
   }
 }
 
-// The kernel arguments of either plan (a chunk plan is the even split).
-template <class Plan>
-static FusedArgs fused_args(const Plan& c, int m, int r, const double* recl, double* x, long ld,
-                            int batch) {
+static FusedArgs fused_args(const DevRagged& c, double* x, long ld, int batch) {
   FusedArgs a{};
   a.x = x;
   a.ld = ld;
   a.batch = batch;
   a.nsteps = 1;
   a.S = c.S;
-  a.m = m;
-  a.r = r;
+  a.m = c.m;
+  a.r = c.r;
   a.dlo = c.dlo;
   a.dcount = c.dcount;
   a.rec = c.rec;
-  a.recl = recl;
+  a.recl = c.recl;
   a.blocks = c.blocks;
   for (int i = 0; i < 5; ++i) a.bd.c[i] = c.coef[i];
   return a;
 }
 
-hipError_t launch_il_fused(const DevChunk& c, int kind, double* x, long ld, int batch, int nsteps,
-                           double s, double al, hipStream_t st) {
-  FusedArgs a = fused_args(c, M, M, c.rec, x, ld, batch);
-  a.nsteps = nsteps;
-  a.s = s;
-  a.al = al;
-  return c.P == 2 ? fused_any<2, false>(kind, a, st) : fused_any<1, false>(kind, a, st);
-}
-
 hipError_t launch_il_fused(const DevRagged& c, int kind, double* x, long ld, int batch, int nsteps,
                            double s, double al, hipStream_t st) {
-  FusedArgs a = fused_args(c, c.m, c.r, c.recl, x, ld, batch);
+  if (c.M != kChunk) return hipErrorInvalidValue;
+  FusedArgs a = fused_args(c, x, ld, batch);
   a.nsteps = nsteps;
   a.s = s;
   a.al = al;
+  if (c.even) return c.P == 2 ? fused_any<2, false>(kind, a, st) : fused_any<1, false>(kind, a, st);
   return c.P == 2 ? fused_any<2, true>(kind, a, st) : fused_any<1, true>(kind, a, st);
 }
 
-bool rows_ragged_fits(const DevRagged& c) { return c.S >= 1 && c.S <= 256; }
+bool rows_any_fits(const DevRagged& c) { return c.S >= 1 && c.S <= 256; }
 
-template <int P>
-static hipError_t rows_ragged_launch(const DevRagged& c, double* x, long ld, int rows,
-                                     hipStream_t st) {
+hipError_t launch_rows_any(const DevRagged& c, const double* src, long lds, double* dst, long ldd,
+                           int rows, const DiagTail* tail, bool stream, hipStream_t st) {
+  if (!rows_any_fits(c)) return hipErrorInvalidValue;
   // rows per workgroup: at least a wave of chunks, at most 256 (128 of short
   // rows: 200000 rows of 100 74 us, 93 with 256), and in between as many as
   // leave the chip two workgroups per CU
@@ -558,16 +922,78 @@ static hipError_t rows_ragged_launch(const DevRagged& c, double* x, long ld, int
   R = R > rows ? rows : R;
   const int T = ((R * c.S + 63) / 64) * 64;
   const int nel = R * c.n;
-  const size_t lds = ((size_t)2 * P * T + nel + nel / 32 + 1) * sizeof(double);
-  hipLaunchKernelGGL((rows_ragged<P>), dim3((unsigned)((rows + R - 1) / R)), dim3(T), lds, st, x,
-                     ld, rows, c.n, R, fused_args(c, c.m, c.r, c.recl, x, ld, rows));
+  const size_t lds_bytes =
+      ((size_t)2 * c.P * T + (c.even ? 0 : 12 * c.dcount) + nel + nel / c.M + 1) * sizeof(double);
+  const unsigned magic = (unsigned)(((1ull << 32) + c.n - 1) / c.n);
+  const dim3 grid((unsigned)((rows + R - 1) / R + (tail ? 1 : 0)));
+  const FusedArgs a = fused_args(c, nullptr, 0, rows);
+  const DiagTail d = tail ? *tail : DiagTail{};
+#define CHX_ROWS(P_, M_, RAG_)                                                                  \
+  hipLaunchKernelGGL((rows_any<P_, M_, RAG_>), grid, dim3(T), lds_bytes, st, src, lds, dst, ldd, \
+                     rows, c.n, magic, R, a, d, stream)
+  if (c.P == 1) {
+    if (c.even || c.M != kChunk) return hipErrorInvalidValue;
+    CHX_ROWS(1, kChunk, true);
+  } else if (c.M == 8) {
+    if (c.even) CHX_ROWS(2, 8, false);
+    else CHX_ROWS(2, 8, true);
+  } else if (c.M == 16) {
+    if (c.even) CHX_ROWS(2, 16, false);
+    else CHX_ROWS(2, 16, true);
+  } else {
+    if (c.even) CHX_ROWS(2, kChunk, false);
+    else CHX_ROWS(2, kChunk, true);
+  }
+#undef CHX_ROWS
   return hipGetLastError();
 }
 
-hipError_t launch_rows_ragged(const DevRagged& c, double* x, long ld, int rows, hipStream_t st) {
-  if (!rows_ragged_fits(c)) return hipErrorInvalidValue;
-  return c.P == 2 ? rows_ragged_launch<2>(c, x, ld, rows, st)
-                  : rows_ragged_launch<1>(c, x, ld, rows, st);
+// Columns per workgroup, or 0 where 4 columns need more than 512 threads.
+int column_whole_columns(int nx, int S) {
+  if (S * 4 > 512) return 0;
+  if (nx >= 16 * 256 && S * 16 <= 512) return 16;
+  if (nx >= 8 * 256 && S * 8 <= 512) return 8;
+  return nx >= 4 ? 4 : 0;
+}
+
+long column_whole_blocks(int nx, int S) {
+  const int L = column_whole_columns(nx, S);
+  return L > 0 ? (nx + L - 1) / L : 0;
+}
+
+hipError_t launch_column_whole(const DevRagged& c, const double* src, long lds, double* dst,
+                               long ldd, int nx, int ny, const ChCoef& K, double* dpart,
+                               hipStream_t st) {
+  const int L = column_whole_columns(nx, c.S);
+  if (c.P != 2 || L == 0 || c.n != ny || src == dst) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)((nx + L - 1) / L)), block(((L * c.S + 63) / 64) * 64);
+  const size_t lds_bytes =
+      ((size_t)4 * c.S * L + (c.even ? 0 : 12 * c.dcount) + 16) * sizeof(double);
+  const FusedArgs a = fused_args(c, nullptr, 0, nx);
+  const bool diag = dpart != nullptr;
+#define CHX_COLW(M_, L_, RAG_, D_)                                                               \
+  hipLaunchKernelGGL((column_whole<M_, L_, RAG_, D_>), grid, block, lds_bytes, st, src, lds, dst, \
+                     ldd, nx, ny, K, dpart, a)
+#define CHX_COLW_L(M_, RAG_, D_)             \
+  do {                                       \
+    if (L == 16) CHX_COLW(M_, 16, RAG_, D_); \
+    else if (L == 8) CHX_COLW(M_, 8, RAG_, D_); \
+    else CHX_COLW(M_, 4, RAG_, D_);          \
+  } while (0)
+#define CHX_COLW_M(RAG_, D_)                      \
+  do {                                            \
+    if (c.M == 8) CHX_COLW_L(8, RAG_, D_);        \
+    else if (c.M == 16) CHX_COLW_L(16, RAG_, D_); \
+    else CHX_COLW_L(kChunk, RAG_, D_);            \
+  } while (0)
+  if (c.even && diag) CHX_COLW_M(false, true);
+  else if (c.even) CHX_COLW_M(false, false);
+  else if (diag) CHX_COLW_M(true, true);
+  else CHX_COLW_M(true, false);
+#undef CHX_COLW_M
+#undef CHX_COLW_L
+#undef CHX_COLW
+  return hipGetLastError();
 }
 
 }  // namespace chx

@@ -28,27 +28,51 @@ struct DevChunk {
   int red_shape = 0;                // separator-kernel tile shape (index into the candidates)
 };
 
-// Device copy of RaggedTables (chunks of m, a last one of r).
+// Device copy of RaggedTables (chunks of m <= M, a last one of r); even: S
+// chunks of M, one family of blocks (the chunk tables of DevChunk).
 struct DevRagged {
   int n = 0, P = 2, M = kChunk, m = 0, r = 0, S = 0, dlo = 0, dcount = 0;
+  bool even = false;
   double coef[5] = {};
   const double* rec = nullptr;     // device, (M - P) * 8
   const double* recl = nullptr;    // device, (M - P) * 8: the last chunk's
-  const double* blocks = nullptr;  // device, 3 * dcount * 4
+  const double* blocks = nullptr;  // device, 3 * dcount * 4 (even: dcount * 4)
 };
+inline DevRagged as_ragged(const DevChunk& c) {
+  DevRagged d;
+  d.n = c.n;
+  d.P = c.P;
+  d.M = d.m = d.r = c.M;
+  d.S = c.S;
+  d.dlo = c.dlo;
+  d.dcount = c.dcount;
+  d.even = true;
+  for (int k = 0; k < 5; ++k) d.coef[k] = c.coef[k];
+  d.rec = d.recl = c.rec;
+  d.blocks = c.blocks;
+  return d;
+}
 
 // One-launch interleaved solve (kind -1) or nsteps steps of a batched 1D
 // scheme (kind 0 .. 2) in place on x (fused.hip): a workgroup holds every
 // chunk of il_fused_systems(S, batch) systems; 0 where S is too large.
 int il_fused_systems(int S, int batch);
-hipError_t launch_il_fused(const DevChunk& c, int kind, double* x, long ld, int batch, int nsteps,
-                           double s, double al, hipStream_t st);
 hipError_t launch_il_fused(const DevRagged& c, int kind, double* x, long ld, int batch, int nsteps,
                            double s, double al, hipStream_t st);
 
-// Contiguous rows of any length in place (fused.hip), at most 256 chunks.
-bool rows_ragged_fits(const DevRagged& c);
-hipError_t launch_rows_ragged(const DevRagged& c, double* x, long ld, int rows, hipStream_t st);
+// (mass, energy) partials of a state for a following launch to finish: n
+// pairs, one per workgroup of column_whole.
+struct DiagTail {
+  const double* part = nullptr;
+  long n = 0;
+  double scale = 0.0;
+  double* out = nullptr;
+};
+// Contiguous rows of any length (fused.hip), at most 256 chunks, from src to
+// dst (may be the same array); stream: streamed stores.
+bool rows_any_fits(const DevRagged& c);
+hipError_t launch_rows_any(const DevRagged& c, const double* src, long lds, double* dst, long ldd,
+                           int rows, const DiagTail* tail, bool stream, hipStream_t st);
 
 // Number of candidate tile shapes of the separator kernel, and the LDS one
 // launch of shape `shape` needs (elem = sizeof the sweep type; diag = the

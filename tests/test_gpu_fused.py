@@ -85,3 +85,61 @@ def test_steps_in_one_call(chx, orc, kind, n, batch, L, dt, a, D):  # noqa: F811
     assert rel(outs[0], orc.batch1d_step(kind, x0, L, dt, a, D, nsteps=5)) < tol
     if n <= 2048:
         assert np.array_equal(outs[0], outs[1])
+
+
+# (ny, nx): one chunk and one tile of columns, last tiles that overlap, a short
+# last chunk of either direction and none, 8-, 16- and 32-point chunks, tiles of
+# 4, 8 and 16 columns, the longest columns a workgroup holds and the first it
+# does not, the largest grid that prefers the two launches
+GRIDS = [(5, 5), (6, 6), (7, 130), (8, 5), (38, 41), (64, 64), (104, 6), (256, 96), (257, 259),
+         (250, 2049), (120, 4100), (700, 90), (1024, 1024), (2003, 70), (4095, 70), (4097, 70)]
+
+
+@pytest.mark.parametrize("ny,nx", GRIDS)
+def test_steps_of_any_grid(chx, orc, ny, nx):  # noqa: F811
+    """Three steps in one call in a padded array, every state's mass and
+    energy, against the oracle (per step 1e-12, or 20 eps (1 + 16 s) where the
+    operator is stiffer than that allows)."""
+    L, g, dt, n = 2 * math.pi, 0.01, 1e-6, 3
+    c0 = inputs.noise_field(ny, nx, 91)
+    h = chx.ch_create(nx, ny, L, L, 1.0, g, dt)
+    buf = torch.full((ny, nx + 3), 7.25, dtype=torch.float64, device="cuda")
+    buf[:, :nx] = torch.from_numpy(c0)
+    d = torch.zeros(2 * (n + 1), dtype=torch.float64, device="cuda")
+    print(f"[case] three steps {ny}x{nx}", flush=True)
+    chx.ch_adi_step(h, buf, nsteps=n, diag_out=d)
+    torch.cuda.synchronize()
+    out, diag = buf.cpu().numpy(), d.cpu().numpy()
+    assert np.all(out[:, nx:] == 7.25)
+    tol = max(1e-12, 20 * np.finfo(float).eps * (1 + 16 * g * dt / (L / max(nx, ny)) ** 4))
+    c, l1 = c0, np.sum(np.abs(c0)) * (L / nx) * (L / ny)
+    for k in range(n + 1):
+        assert abs(diag[2 * k] - orc.ch_mass(c, L, L)) <= n * tol * l1
+        e = orc.ch_energy(c, L, L, g)
+        assert abs(diag[2 * k + 1] - e) <= n * tol * abs(e)
+        if k < n:
+            c = orc.ch_step(c, L, L, 1.0, g, dt)
+    assert rel(out[:, :nx], c) < n * tol
+
+
+def test_two_launch_step_is_bitwise_repeatable_and_replayable(chx):  # noqa: F811
+    """The same call twice, eager and from a captured graph replayed with
+    eager work between: bitwise equal, diagnostics included."""
+    L = 2 * math.pi
+    for ny, nx in ((128, 128), (90, 203)):
+        c0 = inputs.noise_field(ny, nx, 92)
+        h = chx.ch_create(nx, ny, L, L, 1.0, 0.01, 1e-5)
+        c = torch.empty((ny, nx), dtype=torch.float64, device="cuda")
+        d = torch.zeros(8, dtype=torch.float64, device="cuda")
+        ws = torch.empty(chx.ch_ws_bytes(h) + 256, dtype=torch.uint8, device="cuda")
+        outs = []
+        for call in range(5):
+            if call == 2:
+                chx.ch_set_tuning(h, 1, what=chx.CHX_TUNE_GRAPH)
+            print(f"[case] repeat {ny}x{nx} call {call}", flush=True)
+            c.copy_(torch.from_numpy(c0))
+            chx.ch_adi_step(h, c, nsteps=3, diag_out=d, ws=ws)
+            torch.cuda.synchronize()
+            outs.append((c.cpu().numpy(), d.cpu().numpy()))
+        for o in outs[1:]:
+            assert np.array_equal(o[0], outs[0][0]) and np.array_equal(o[1], outs[0][1])
