@@ -778,10 +778,10 @@ int batch1d_step(chx_batch1d b, int batch, double* x, long ld, int nsteps, void*
   double* rho = reinterpret_cast<double*>(base + 2 * field);
   // systems that a workgroup holds take all steps of the call in one launch
   const BandPlan* p = b->plan;
-  if (p->has_chunk && il_fused_systems(p->dchunk.S, batch) > 0)
+  if (p->has_chunk && il_fused_systems(p->dchunk.S, batch, true) > 0)
     return launch_il_fused(as_ragged(p->dchunk), b->kind, x, ld, batch, nsteps, b->s, b->al,
                            static_cast<hipStream_t>(s)) == hipSuccess ? CHX_OK : CHX_EHIP;
-  if (p->has_ragged && il_fused_systems(p->dragged.S, batch) > 0)
+  if (p->has_ragged && il_fused_systems(p->dragged.S, batch, true) > 0)
     return launch_il_fused(p->dragged, b->kind, x, ld, batch, nsteps, b->s, b->al,
                            static_cast<hipStream_t>(s)) == hipSuccess ? CHX_OK : CHX_EHIP;
   const hipError_t e =
@@ -1402,6 +1402,10 @@ static_assert(kNumSplitShapes == CHX_NUM_SPLIT_SHAPES, "shape count mismatch");
 // 176: long columns leave few workgroups).
 constexpr long kPairPoints = 1L << 20;
 constexpr int kPairColumn = 1024;
+// The thesis scheme's two launches against its three and the diagnostics' two
+// (four steps a call: 512 x 512 61 us against 121, 1024 x 1024 117 against 158,
+// 2048 x 1536 282 against 300, 2048 x 2048 363 against 351).
+constexpr long kPairPoints2 = 3L << 20;
 // ... and of this many take their final mass and energy in one launch.
 constexpr long kDiagSmall = 1L << 15;
 
@@ -1452,6 +1456,13 @@ int ch_create(const chx_ch_params* prm, chx_ch* out) {
   // columns, and the smaller of the others)
   const bool chunked = q.nx % 64 == 0 && q.ny % kChunk == 0 && q.nx / kChunk <= 256;
   int pair_y = 0, pair_x = 0;
+  if (q.scheme == CHX_SCHEME_P2 &&
+      (!chunked || (long)q.nx * q.ny <= kPairPoints2)) {
+    pair_y = pair_chunk(q.ny, true, 4);  // tiles of four columns
+    pair_x = pair_chunk(q.nx, false, 4);
+    h->pair = pair_y > 0 && pair_y < kChunk && pair_x > 0;
+    if (!h->pair) pair_y = pair_x = 0;
+  }
   if (c16 && (!chunked || ((long)q.nx * q.ny <= kPairPoints && q.ny <= kPairColumn))) {
     pair_y = pair_chunk(q.ny, true, q.nx);
     pair_x = pair_chunk(q.nx, false, q.nx);
@@ -1534,8 +1545,12 @@ int ch_create(const chx_ch_params* prm, chx_ch* out) {
     }
     h->part_count = diag_parts;
   }
+  if (q.scheme == CHX_SCHEME_P2 && h->py->has_chunk)
+    h->part_count = std::max(h->part_count, ch2_column_parts(q.nx, &h->py->dchunk));
   if (h->pair)
-    h->part_count = std::max(h->part_count, column_whole_blocks(q.nx, h->py->dragged.S));
+    h->part_count = std::max(h->part_count, q.scheme == CHX_SCHEME_P2
+                                                ? (long)(q.nx + 3) / 4
+                                                : column_whole_blocks(q.nx, h->py->dragged.S));
   h->off_part = off;
   off += align256((size_t)h->part_count * 2 * sizeof(double));
   h->ws_total = off;
@@ -1991,15 +2006,50 @@ int ch_adi_step_p2(chx_ch h, double* c, double* cprev, long ld, int nsteps, doub
   double* part = reinterpret_cast<double*>(base + h->off_part);
   const bool col_chunk = h->py->has_chunk;
   hipError_t e = hipSuccess;
+  if (h->pair) {
+    // whole columns of r into the workspace; the rows' launch solves them into
+    // v, advances the states and finishes the diagnostics of the one before
+    double* r = rbuf[0];
+    DiagTail tail;
+    tail.part = part;
+    tail.n = (nx + 3) / 4;
+    tail.scale = h->K.dxdy;
+    StateUpdate up;
+    up.c = c;
+    up.cp = cprev;
+    up.ldc = up.ldp = up.ldn = ld;
+    for (int n = 0; n < nsteps && e == hipSuccess; ++n) {
+      e = launch_column_whole2(h->py->dragged, up.c, ld, up.cp, ld, r, nx, nx, ny, h->K2, h->K,
+                               diag_out ? part : nullptr, st);
+      // the new state takes the older one's array; the last one goes to c, and
+      // the state before it to cprev
+      const bool last = n + 1 == nsteps;
+      double* const older = const_cast<double*>(up.cp);
+      up.next = last ? c : older;
+      up.next_prev = last && older != c ? cprev : nullptr;
+      tail.out = diag_out ? diag_out + 2 * n : nullptr;
+      if (e == hipSuccess)
+        e = launch_rows_update(h->px->dragged, r, nx, ny, up, diag_out ? &tail : nullptr, st);
+      up.cp = up.c;
+      up.c = older;
+    }
+    if (e == hipSuccess && diag_out)
+      e = (long)nx * ny <= kDiagSmall
+              ? launch_diag_small(c, ld, nx, ny, h->K, diag_out + 2 * nsteps, st)
+              : launch_ch_diag(c, ld, nx, ny, h->K, part, diag_out + 2 * nsteps, st);
+    return e == hipSuccess ? CHX_OK : CHX_EHIP;
+  }
   // v = L_y^{-1} L_x^{-1} r in place: columns (interleaved), then rows
   // (chunked columns: the chunk correction is left to whoever reads r next)
   const DevChunk* recon = col_chunk ? &h->py->dchunk : nullptr;
   // with chunked columns the right-hand-side kernel has already run the
   // column chunk sweep (y in r, separator parts in rho)
   const DevChunk* sweep = col_chunk ? &h->py->dchunk : nullptr;
-  auto solve_in_place = [&](double* r) {
+  auto solve_in_place = [&](double* r, long dparts, double* dout) {
     hipError_t e2 = col_chunk ? launch_reduced_il<2>(h->py->dchunk, rho, nx, r, nx, kChunk,
-                                                     kChunk - 2, st)
+                                                     kChunk - 2, st, dparts > 0 ? part : nullptr,
+                                                     dparts, h->K.dxdy,
+                                                     dparts > 0 ? dout : nullptr)
                               : solve_il(h->py, r, nx, nx, nullptr, st);
     if (e2 == hipSuccess) e2 = solve_rows(h->px, r, nx, ny, false, st);
     return e2;
@@ -2012,23 +2062,30 @@ int ch_adi_step_p2(chx_ch h, double* c, double* cprev, long ld, int nsteps, doub
     long ld;
   };
   Buf cur{c, ld}, prev{cprev, ld}, spare{w, nx};
-  if (diag_out) e = launch_ch_diag(c, ld, nx, ny, h->K, part, diag_out, st);
+  // the column-streaming kernel also sums the diagnostics of the state it
+  // forms, and the separator kernel finishes them; the others leave both to
+  // launches of their own (as where the separators' decay window is too long
+  // for the separator kernels that can)
+  const bool tail = sweep && reduced_lds_bytes(0, 2, sizeof(double), sweep->S, sweep->dcount,
+                                               true) <= kMaxLdsBytes;
+  const long dparts = diag_out && tail ? ch2_column_parts(nx, sweep) : 0;
+  if (diag_out && dparts == 0) e = launch_ch_diag(c, ld, nx, ny, h->K, part, diag_out, st);
   if (e == hipSuccess)
     e = launch_ch2_rhs(c, ld, cprev, ld, nullptr, 0, nullptr, 0, rbuf[0], nx, nx, ny, h->K2,
-                       nullptr, sweep, rho, st);
-  if (e == hipSuccess) e = solve_in_place(rbuf[0]);
+                       nullptr, sweep, rho, st, &h->K, dparts > 0 ? part : nullptr);
+  if (e == hipSuccess) e = solve_in_place(rbuf[0], dparts, diag_out);
   for (int n = 1; n < nsteps && e == hipSuccess; ++n) {
     double* rv = rbuf[(n - 1) & 1];
     double* rn = rbuf[n & 1];
     e = launch_ch2_rhs(cur.p, cur.ld, prev.p, prev.ld, rv, nx, spare.p, spare.ld, rn, nx, nx, ny,
-                       h->K2, recon, sweep, rho, st);
-    if (e == hipSuccess && diag_out)
+                       h->K2, recon, sweep, rho, st, &h->K, dparts > 0 ? part : nullptr);
+    if (e == hipSuccess && diag_out && dparts == 0)
       e = launch_ch_diag(spare.p, spare.ld, nx, ny, h->K, part, diag_out + 2 * n, st);
     const Buf old_prev = prev;
     prev = cur;
     cur = spare;
     spare = old_prev;
-    if (e == hipSuccess) e = solve_in_place(rn);
+    if (e == hipSuccess) e = solve_in_place(rn, dparts, diag_out + 2 * n);
   }
   if (e == hipSuccess)
     e = launch_ch2_update(cur.p, cur.ld, prev.p, prev.ld, rbuf[(nsteps - 1) & 1], nx, c, cprev,

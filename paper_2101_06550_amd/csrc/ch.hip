@@ -929,13 +929,16 @@ __global__ __launch_bounds__(256) void ch2_update(const double* c, long ldc, con
 constexpr int kSeg2 = 60;  // output columns per wave
 constexpr int kPf2 = 8;    // rows of loads in flight ahead of the row being worked
 
-template <bool UPD, bool RECON>
+// DIAG: each wave also leaves the (mass, energy) sum of its output columns of
+// the state (C, or C_new), pair number chunk * segments + segment.
+template <bool UPD, bool RECON, bool DIAG>
 __global__ __launch_bounds__(256) void ch2_column_pass(
     const double* __restrict__ c, long ld, const double* __restrict__ cp, long ldp,
     const double* __restrict__ v, long ldv, double* __restrict__ cnew, long ldn,
     double* __restrict__ r, long ldr, int nx, int ny, Ch2Coef K, int Sc,
     const double* __restrict__ rec, const double* __restrict__ srec, BandT<double> sbd,
-    double* __restrict__ rhop) {
+    double* __restrict__ rhop, ChCoef D, double* __restrict__ dpart) {
+  double msum = 0.0, esum = 0.0;
   constexpr int Q = M + 4;  // rows kc M - 2 .. kc M + M + 1
   const int lane = threadIdx.x & 63;
   const int seg = blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -1021,6 +1024,14 @@ __global__ __launch_bounds__(256) void ch2_column_pass(
       const double lap = (mu_r + mu_l - 2.0 * U[w]) * K.inv_dx2 +
                          (U[w + 1] + U[w - 1] - 2.0 * U[w]) * K.inv_dy2;
       f[w - 2] = -(2.0 / 3.0) * (C[w] - Pv[w]) - K.a * bih + K.b * lap;
+      if (DIAG) {
+        const double ww = C[w] * C[w] - 1.0;
+        const double gx = (dpp_from_right(C[w], C[w]) - C[w]) * D.inv_dx;
+        const double gy = (C[w + 1] - C[w]) * D.inv_dy;
+        msum += C[w];
+        esum += 0.25 * ww * ww + D.half_gamma * (gx * gx + gy * gy);
+        asm volatile("" : "+v"(msum), "+v"(esum));
+      }
     }
     // this row's values are complete here and the next row's loads are issued
     // after this point (empty volatile asms keep their order)
@@ -1031,6 +1042,15 @@ __global__ __launch_bounds__(256) void ch2_column_pass(
   chunk_sweep<P, M, double>(f, srec, sbd.c[0]);
   double pa[P], pb[P];
   chunk_parts<P, M, double>(f, sbd, pa, pb);
+  if (DIAG) {
+    msum = wave_sum(own ? msum : 0.0);
+    esum = wave_sum(own ? esum : 0.0);
+    if (lane == 0) {
+      const long b = (long)kc * ((nx + kSeg2 - 1) / kSeg2) + seg;
+      dpart[2 * b] = msum;
+      dpart[2 * b + 1] = esum;
+    }
+  }
   if (!own) return;
 #pragma unroll
   for (int p = 0; p < MI; ++p) __builtin_nontemporal_store(f[p], &r[((long)kc * M + p) * ldr + io]);
@@ -1041,10 +1061,19 @@ __global__ __launch_bounds__(256) void ch2_column_pass(
   }
 }
 
+// The column-streaming kernel runs one wave per (60-column segment, chunk):
+// it takes over once that fills every SIMD twice; smaller grids keep the
+// tile kernel, whose eight waves per 64 x 32 tile fill the chip sooner
+// (1024 x 1024: 0.039 ms per step with it, 0.043 with the column kernel).
+long ch2_column_parts(int nx, const DevChunk* sweep) {
+  const long waves = sweep ? (long)((nx + kSeg2 - 1) / kSeg2) * sweep->S : 0;
+  return waves >= 2048 ? waves : 0;
+}
+
 hipError_t launch_ch2_rhs(const double* c, long ld, const double* cp, long ldp, const double* v,
                           long ldv, double* cnew, long ldn, double* r, long ldr, int nx, int ny,
                           const Ch2Coef& K, const DevChunk* recon, const DevChunk* sweep,
-                          double* rho, hipStream_t st) {
+                          double* rho, hipStream_t st, const ChCoef* D, double* dpart) {
   dim3 grid((nx + kT2X - 1) / kT2X, (ny + kT2Y - 1) / kT2Y);
   const int Sc = recon ? recon->S : 0;
   const double* rec = recon ? recon->rec : nullptr;
@@ -1057,23 +1086,22 @@ hipError_t launch_ch2_rhs(const double* c, long ld, const double* cp, long ldp, 
 #define CHX_CH2(U, R, W)                                                                        \
   hipLaunchKernelGGL((ch2_rhs<U, R, W>), grid, dim3(kT2T), 0, st, c, ld, cp, ldp, v, ldv, cnew, \
                      ldn, r, ldr, nx, ny, K, Sc, rec, srec, sbd, rho)
-  // the column-streaming kernel runs one wave per (60-column segment, chunk):
-  // it takes over once that fills every SIMD twice; smaller grids keep the
-  // tile kernel, whose eight waves per 64 x 32 tile fill the chip sooner
-  // (1024 x 1024: 0.039 ms per step with it, 0.043 with the column kernel)
-  const bool columns = sweep && (long)((nx + kSeg2 - 1) / kSeg2) * sweep->S >= 2048;
-  if (columns) {
+  if (ch2_column_parts(nx, sweep) > 0) {
     const int Scol = sweep->S;
     if ((long)Scol * M != ny || (recon && recon->S != Scol)) return hipErrorInvalidValue;
     // blocks in chunk-row order (measured: banding whole chunk rows onto one
     // XCD, so shared halo rows meet in one L2, was 3-4 % slower)
     const dim3 g2((unsigned)(((nx + kSeg2 - 1) / kSeg2 + 3) / 4), (unsigned)Scol);
-#define CHX_CH2C(U, R)                                                                       \
-  hipLaunchKernelGGL((ch2_column_pass<U, R>), g2, dim3(256), 0, st, c, ld, cp, ldp, v, ldv, cnew, \
-                     ldn, r, ldr, nx, ny, K, Scol, rec, srec, sbd, rho)
-    if (v && recon) CHX_CH2C(true, true);
-    else if (v) CHX_CH2C(true, false);
-    else CHX_CH2C(false, false);
+    const bool diag = D && dpart;
+    const ChCoef dk = D ? *D : ChCoef{};
+#define CHX_CH2C(U, R, G)                                                                       \
+  hipLaunchKernelGGL((ch2_column_pass<U, R, G>), g2, dim3(256), 0, st, c, ld, cp, ldp, v, ldv,  \
+                     cnew, ldn, r, ldr, nx, ny, K, Scol, rec, srec, sbd, rho, dk, dpart)
+    if (v && !recon) return hipErrorInvalidValue;  // a chunked plan always defers its correction
+    if (v && diag) CHX_CH2C(true, true, true);
+    else if (v) CHX_CH2C(true, true, false);
+    else if (diag) CHX_CH2C(false, false, true);
+    else CHX_CH2C(false, false, false);
 #undef CHX_CH2C
   } else if (sweep) {
     if (v && recon) CHX_CH2(true, true, true);

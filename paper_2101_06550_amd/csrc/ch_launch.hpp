@@ -31,7 +31,11 @@ struct Ch2Coef {
 hipError_t launch_ch2_rhs(const double* c, long ld, const double* cp, long ldp, const double* v,
                           long ldv, double* cnew, long ldn, double* r, long ldr, int nx, int ny,
                           const Ch2Coef& K, const DevChunk* recon, const DevChunk* sweep,
-                          double* rho, hipStream_t st);
+                          double* rho, hipStream_t st, const ChCoef* D = nullptr,
+                          double* dpart = nullptr);
+// (mass, energy) partials of the state that launch_ch2_rhs leaves in dpart
+// (with D) where it streams columns on a grid of nx columns; 0 elsewhere.
+long ch2_column_parts(int nx, const DevChunk* sweep);
 // out = 2C - Cp + v, out_prev = C, elementwise (outputs may alias inputs);
 // recon as above.
 hipError_t launch_ch2_update(const double* c, long ldc, const double* cp, long ldp,
@@ -47,6 +51,12 @@ long column_whole_blocks(int nx, int S);
 hipError_t launch_column_whole(const DevRagged& c, const double* src, long lds, double* dst,
                                long ldd, int nx, int ny, const ChCoef& K, double* dpart,
                                hipStream_t st);
+// The same for the thesis's delta-form scheme, from the states C and Cp into
+// dst (neither of them): 8- or 16-point chunks, at most 128 per column.
+hipError_t launch_column_whole2(const DevRagged& c, const double* C, long ldc, const double* Cp,
+                                long ldp, double* dst, long ldd, int nx, int ny,
+                                const Ch2Coef& K, const ChCoef& D, double* dpart,
+                                hipStream_t st);
 // Mass and energy of a small field in one launch of one workgroup.
 hipError_t launch_diag_small(const double* c, long ld, int nx, int ny, const ChCoef& K,
                              double* out, hipStream_t st);

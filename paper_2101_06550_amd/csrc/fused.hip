@@ -193,6 +193,14 @@ __device__ __forceinline__ void warm(const double* p) {
   asm volatile("" ::"s"(x));
 }
 
+// Lane l of a quad receives the value of its lane (SEL >> 2 l) & 3.
+template <int SEL>
+__device__ __forceinline__ double dpp_quad(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), SEL, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), SEL, 0xF, 0xF, true);
+  return __hiloint2double(hi, lo);
+}
+
 struct FusedArgs {
   double* x;
   long ld;
@@ -477,11 +485,14 @@ __global__ __launch_bounds__(1024) void il_fused(const FusedArgs A) {
 // 21.2 us per step, 22.1 streamed).  With
 // tail.out, the launch's last workgroup solves no rows: it finishes the
 // (mass, energy) of the state that the column kernel before it has read.
-template <int P, int M, bool RAG>
+// UPD: the solved rows v are not stored: they advance the thesis scheme's two
+// states, next = (2 C - Cp) + v and, where given, next_prev = C (each element
+// read before it is written: next may be Cp, or next C and next_prev Cp).
+template <int P, int M, bool RAG, bool UPD = false>
 __global__ __launch_bounds__(256) void rows_any(const double* src, long lds, double* dst, long ldd,
                                                 int rows, int n, unsigned magic, int R,
                                                 const FusedArgs A, const DiagTail tail,
-                                                const bool stream) {
+                                                const bool stream, const StateUpdate up) {
   extern __shared__ double sm[];
   if (tail.out != nullptr && blockIdx.x == gridDim.x - 1) {
     diag_tail(tail, sm);
@@ -556,6 +567,16 @@ __global__ __launch_bounds__(256) void rows_any(const double* src, long lds, dou
       }
     }
   }
+  // the states' elements, in flight until the rows are solved
+  double uc[UPD ? M : 1], upv[UPD ? M : 1];
+  if constexpr (UPD) {
+#pragma unroll
+    for (int u = 0; u < M; ++u) {
+      const int e = t + u * T < nel ? t + u * T : nel - 1;
+      uc[u] = up.c[row0 * up.ldc + at(e, up.ldc)];
+      upv[u] = up.cp[row0 * up.ldp + at(e, up.ldp)];
+    }
+  }
   __syncthreads();
   double f[M];
   const int e0 = r * n + k * (RAG ? A.m : M);
@@ -609,7 +630,21 @@ __global__ __launch_bounds__(256) void rows_any(const double* src, long lds, dou
     for (int a = 0; a < P; ++a) tile[slot(e0 + lj + a)] = so[a];
   }
   __syncthreads();
-  if (stream && ldd == n) {
+  if constexpr (UPD) {
+    double v[M];
+#pragma unroll
+    for (int u = 0; u < M; ++u) {
+      const int e = t + u * T;
+      v[u] = (2.0 * uc[u] - upv[u]) + tile[slot(e < nel ? e : nel - 1)];
+    }
+#pragma unroll
+    for (int u = 0; u < M; ++u) {
+      const int e = t + u * T;
+      if (e >= nel) continue;
+      up.next[row0 * up.ldn + at(e, up.ldn)] = v[u];
+      if (up.next_prev != nullptr) up.next_prev[row0 * up.ldn + at(e, up.ldn)] = uc[u];
+    }
+  } else if (stream && ldd == n) {
     for (int e = t; e < nel; e += T) __builtin_nontemporal_store(tile[slot(e)], xd + e);
   } else if (pairs(xd, ldd)) {
     double2 v[M / 2];
@@ -638,6 +673,65 @@ __global__ __launch_bounds__(256) void rows_any(const double* src, long lds, dou
       if (e < nel) __builtin_nontemporal_store(v[u], xd + at(e, ldd));
     }
   }
+}
+
+// The solve of one chunk per thread, a workgroup holding whole columns: f the
+// right-hand sides in, the interior's solutions out; fs the separators'
+// (RAG: given; otherwise f's last two).
+template <int P, int M, int L, bool RAG>
+__device__ __forceinline__ void column_solve(const FusedArgs& A, double (&f)[M], double (&fs)[P],
+                                             double* part, double* rho, const double* blk, int k,
+                                             int c, int me, int nxt, int prv, bool active,
+                                             bool last, int li) {
+  constexpr int MI = M - P;
+  const int plane = A.S * L;
+  const double eps = A.bd.c[0];
+  double t1 = 0, t2 = 0, pa[P], pb[P];
+  if constexpr (RAG) {
+    ragged_sweep<P, M>(f, li, table(A.rec), eps, t1, t2);
+  } else {
+#pragma unroll
+    for (int a = 0; a < P; ++a) fs[a] = f[MI + a];
+    chunk_sweep<P, M, double, TabD>(f, table(A.rec), eps);
+    t1 = f[MI - 1];
+    t2 = f[MI - 2];
+  }
+  ragged_parts<P, M>(f, fs, t1, t2, A.bd, pa, pb);
+  if (active) {
+#pragma unroll
+    for (int a = 0; a < P; ++a) part[a * plane + me] = pb[a];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int a = 0; a < P; ++a) pa[a] -= part[a * plane + nxt];
+  if (active) {
+#pragma unroll
+    for (int a = 0; a < P; ++a) rho[a * plane + me] = pa[a];
+  }
+  __syncthreads();
+  double sp[P];
+  separators<P, RAG>(A, blk, k, rho + c, plane, L, fs);
+  if (active) {
+#pragma unroll
+    for (int a = 0; a < P; ++a) part[a * plane + me] = fs[a];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int a = 0; a < P; ++a) sp[a] = part[a * plane + prv];
+  if constexpr (RAG) ragged_correct<P, M>(f, last, table(A.rec), table(A.recl), sp, fs);
+  else chunk_correct<P, M, double, TabD>(f, table(A.rec), sp, fs);
+}
+
+// A solved chunk into its column: the interior, then the separators.
+template <int P, int M, bool RAG>
+__device__ __forceinline__ void column_store(const double (&f)[M], const double (&fs)[P],
+                                             double* p0, long ldd, int li) {
+  const int lj = RAG ? fresh(li) : M - P;
+#pragma unroll
+  for (int p = 0; p < M - P; ++p)
+    if (!RAG || p < lj) __builtin_nontemporal_store(f[p], p0 + (long)p * ldd);
+#pragma unroll
+  for (int a = 0; a < P; ++a) __builtin_nontemporal_store(fs[a], p0 + (long)(lj + a) * ldd);
 }
 
 // One step's right-hand side and column solves of a periodic 2D field, from
@@ -672,7 +766,6 @@ __global__ __launch_bounds__(512) void column_whole(const double* __restrict__ s
   double* const rho = sm + P * S * L;
   double* const blk = sm + 2 * P * S * L;
   double* const dred = blk + blocks_lds<RAG>(A.dcount);
-  const int plane = S * L;
   const int me = k * L + c;
   const int nxt = (k + 1 == S ? 0 : k + 1) * L + c, prv = (k == 0 ? S - 1 : k - 1) * L + c;
   const bool last = k == S - 1;
@@ -703,7 +796,6 @@ __global__ __launch_bounds__(512) void column_whole(const double* __restrict__ s
   warm<MI>(A.rec);
   double f[M], fs[P] = {0, 0};
   double msum = 0.0, esum = 0.0;
-  const double eps = A.bd.c[0];
   {
     auto left = [&](int q) {
       double v = dpp_row_from_left(X[q], E[q]);
@@ -748,51 +840,139 @@ __global__ __launch_bounds__(512) void column_whole(const double* __restrict__ s
       xl_c = xl_p; xc_c = xc_p; xr_c = xr_p;
     }
   }
-  double t1 = 0, t2 = 0, pa[P], pb[P];
-  if constexpr (RAG) {
-    ragged_sweep<P, M>(f, li, table(A.rec), eps, t1, t2);
-  } else {
-#pragma unroll
-    for (int a = 0; a < P; ++a) fs[a] = f[MI + a];
-    chunk_sweep<P, M, double, TabD>(f, table(A.rec), eps);
-    t1 = f[MI - 1];
-    t2 = f[MI - 2];
-  }
-  ragged_parts<P, M>(f, fs, t1, t2, A.bd, pa, pb);
-  if (active) {
-#pragma unroll
-    for (int a = 0; a < P; ++a) part[a * plane + me] = pb[a];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int a = 0; a < P; ++a) pa[a] -= part[a * plane + nxt];
-  if (active) {
-#pragma unroll
-    for (int a = 0; a < P; ++a) rho[a * plane + me] = pa[a];
-  }
-  __syncthreads();
-  double so[P], sp[P];
-  separators<P, RAG>(A, blk, k, rho + c, plane, L, so);
-  if (active) {
-#pragma unroll
-    for (int a = 0; a < P; ++a) part[a * plane + me] = so[a];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int a = 0; a < P; ++a) sp[a] = part[a * plane + prv];
-  if constexpr (RAG) ragged_correct<P, M>(f, last, table(A.rec), table(A.recl), sp, so);
-  else chunk_correct<P, M, double, TabD>(f, table(A.rec), sp, so);
-  if (sv) {
-    double* p0 = dst + (long)row0 * ldd + i;
-    const int lj = RAG ? fresh(li) : li;
-#pragma unroll
-    for (int p = 0; p < MI; ++p)
-      if (!RAG || p < lj) __builtin_nontemporal_store(f[p], p0 + (long)p * ldd);
-#pragma unroll
-    for (int a = 0; a < P; ++a)
-      __builtin_nontemporal_store(so[a], p0 + (long)(lj + a) * ldd);
-  }
+  column_solve<P, M, L, RAG>(A, f, fs, part, rho, blk, k, c, me, nxt, prv, active, last, li);
+  if (sv) column_store<P, M, RAG>(f, fs, dst + (long)row0 * ldd + i, ldd, li);
   // the diagnostics' sums, while the stores drain
+  if (DIAG) {
+    msum = sv ? msum : 0.0;
+    esum = sv ? esum : 0.0;
+    group_sum2(msum, esum, dred);
+    if (threadIdx.x == 0) {
+      dpart[2 * blockIdx.x] = msum;
+      dpart[2 * blockIdx.x + 1] = esum;
+    }
+  }
+}
+
+// The thesis scheme's step in the same form: r from the two states C and Cp
+// (the expressions of ch2_rhs in ch.hip) and the column solves.  Tiles of four
+// columns: each lane holds its own column and one of the four outside the
+// tile (two on either side), and the neighbours at distance one and two come
+// from the quad's lanes.
+template <int M, bool RAG, bool DIAG>
+__global__ __launch_bounds__(512) void column_whole2(const double* __restrict__ C, long ldc,
+                                                     const double* __restrict__ Cp, long ldp,
+                                                     double* __restrict__ dst, long ldd, int nx,
+                                                     int ny, const Ch2Coef K, const ChCoef D,
+                                                     double* __restrict__ dpart,
+                                                     const FusedArgs A) {
+  constexpr int P = 2, MI = M - P, L = 4, Q = M + 4;
+  extern __shared__ double sm[];
+  const int S = A.S;
+  const int c = threadIdx.x % L, kt = threadIdx.x / L;
+  const bool active = kt < S;
+  const int k = active ? kt : S - 1;
+  const int t0 = (int)tile_of<false>(blockIdx.x, gridDim.x) * L;
+  const int i0 = t0 + L <= nx ? t0 : nx - L, i = i0 + c;
+  const bool sv = active && i >= t0;
+  double* const part = sm;
+  double* const rho = sm + P * S * L;
+  double* const blk = sm + 2 * P * S * L;
+  double* const dred = blk + blocks_lds<RAG>(A.dcount);
+  const int me = k * L + c;
+  const int nxt = (k + 1 == S ? 0 : k + 1) * L + c, prv = (k == 0 ? S - 1 : k - 1) * L + c;
+  const bool last = k == S - 1;
+  const int len = RAG ? (last ? A.r : A.m) : M;
+  const int li = len - P;
+  const int row0 = k * (RAG ? A.m : M);
+
+  // own column and the one outside, rows row0 - 2 .. row0 + len + 1
+  double xc[Q], xp[Q], hc[Q], hp[Q];
+  {
+    int ih = c < 2 ? i0 - 2 + c : i0 + 2 + c;
+    ih += ih < 0 ? nx : 0;
+    ih -= ih >= nx ? nx : 0;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      int j = row0 - 2 + (q < (RAG ? len : M) + 4 ? q : 0);
+      j += j < 0 ? ny : 0;
+      j -= j >= ny ? ny : 0;
+      const double* const a = C + (long)j * ldc;
+      const double* const b = Cp + (long)j * ldp;
+      xc[q] = a[i];
+      hc[q] = a[ih];
+      xp[q] = b[i];
+      hp[q] = b[ih];
+    }
+  }
+  stage_blocks<RAG>(A, blk);
+  warm<MI>(A.rec);
+  double f[M], fs[P] = {0, 0};
+  double msum = 0.0, esum = 0.0;
+  {
+    // lane l of a quad takes lane ((sel >> 2 l) & 3)'s value
+    auto left1 = [&](double own, double out) {  // columns c - 1
+      const double a = dpp_quad<0x90>(own), b = dpp_quad<0x01>(out);
+      return c == 0 ? b : a;
+    };
+    auto right1 = [&](double own, double out) {  // c + 1
+      const double a = dpp_quad<0xF9>(own), b = dpp_quad<0x80>(out);
+      return c == 3 ? b : a;
+    };
+    auto left2 = [&](double own, double out) {  // c - 2: the lanes outside hold them in order
+      const double a = dpp_quad<0x40>(own);
+      return c < 2 ? out : a;
+    };
+    auto right2 = [&](double own, double out) {  // c + 2
+      const double a = dpp_quad<0x0E>(own);
+      return c >= 2 ? out : a;
+    };
+    double B[Q], U[Q], BL[Q], BR[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      B[q] = 2.0 * xc[q] - xp[q];
+      U[q] = xc[q] * xc[q] * xc[q] - xc[q];
+      const double H = 2.0 * hc[q] - hp[q];
+      BL[q] = left1(B[q], H);
+      BR[q] = right1(B[q], H);
+      if (q < 4) continue;
+      const int w = q - 2, p = q - 4;  // right-hand side of the chunk's row p
+      const double Hw = 2.0 * hc[w] - hp[w];
+      const double hu = hc[w] * hc[w] * hc[w] - hc[w];
+      const double mu_l = left1(U[w], hu), mu_r = right1(U[w], hu);
+      const double d4x = (left2(B[w], Hw) - 4.0 * BL[w] + 6.0 * B[w] - 4.0 * BR[w] +
+                          right2(B[w], Hw)) * K.inv_dx4;
+      const double d4y =
+          (B[w - 2] - 4.0 * B[w - 1] + 6.0 * B[w] - 4.0 * B[w + 1] + B[w + 2]) * K.inv_dy4;
+      const double dyy_w = BL[w + 1] + BL[w - 1] - 2.0 * BL[w];
+      const double dyy_c = B[w + 1] + B[w - 1] - 2.0 * B[w];
+      const double dyy_e = BR[w + 1] + BR[w - 1] - 2.0 * BR[w];
+      const double dxxyy = (dyy_e + dyy_w - 2.0 * dyy_c) * K.inv_dx2dy2;
+      const double bih = d4x + 2.0 * dxxyy + d4y;
+      const double lap = (mu_r + mu_l - 2.0 * U[w]) * K.inv_dx2 +
+                         (U[w + 1] + U[w - 1] - 2.0 * U[w]) * K.inv_dy2;
+      const double r = -(2.0 / 3.0) * (xc[w] - xp[w]) - K.a * bih + K.b * lap;
+      if (DIAG) {
+        const double ww = xc[w] * xc[w] - 1.0;
+        const double gx = (right1(xc[w], hc[w]) - xc[w]) * D.inv_dx;
+        const double gy = (xc[w + 1] - xc[w]) * D.inv_dy;
+        const bool in = !RAG || p < len;
+        msum += in ? xc[w] : 0.0;
+        const double ee = 0.25 * ww * ww + D.half_gamma * (gx * gx + gy * gy);
+        esum += in ? ee : 0.0;
+      }
+      f[p] = r;
+      if constexpr (RAG) {
+#pragma unroll
+        for (int a = 0; a < P; ++a) {
+          fs[a] = p == li + a ? r : fs[a];
+          asm volatile("" : "+v"(fs[a]));
+        }
+      }
+    }
+  }
+  column_solve<P, M, L, RAG>(A, f, fs, part, rho, blk, k, c, me, nxt, prv, active, last, li);
+  if (sv) column_store<P, M, RAG>(f, fs, dst + (long)row0 * ldd + i, ldd, li);
   if (DIAG) {
     msum = sv ? msum : 0.0;
     esum = sv ? esum : 0.0;
@@ -843,8 +1023,13 @@ hipError_t launch_diag_small(const double* c, long ld, int nx, int ny, const ChC
 // up to 1024 threads (131072 systems of 1024: 444 us, 457 with 16; 512 points:
 // 395 us, 409 with 64), as long as there are two workgroups for every CU
 // (1024 systems of 1024: 9.4 us with 16, 12.3 with 32).
-int il_fused_systems(int S, int batch) {
+// The 1D schemes' steps wait on each other at barriers and want several small
+// workgroups per CU: 32 up to 512 threads, else 16 (four steps of 262144
+// systems of 256: 268 us with 32, 298 with 64; 65536 of 1024: 343 us with 16,
+// 484 with 32).
+int il_fused_systems(int S, int batch, bool steps) {
   if (S * 16 > 1024) return 0;
+  if (steps) return S * 32 <= 512 && batch >= 32 * 512 ? 32 : 16;
   if (S * 64 <= 512 && batch >= 64 * 512) return 64;
   return S * 32 <= 1024 && batch >= 32 * 512 ? 32 : 16;
 }
@@ -870,8 +1055,8 @@ static hipError_t fused_kind(int kind, const FusedArgs& a, hipStream_t st) {
 
 template <int P, bool RAG>
 static hipError_t fused_any(int kind, const FusedArgs& a, hipStream_t st) {
-  switch (il_fused_systems(a.S, a.batch)) {
-    case 64: return fused_kind<P, 64, RAG>(kind, a, st);
+  switch (il_fused_systems(a.S, a.batch, kind >= 0)) {
+    case 64: return fused_launch<P, 64, RAG, -1>(a, st);
     case 32: return fused_kind<P, 32, RAG>(kind, a, st);
     case 16: return fused_kind<P, 16, RAG>(kind, a, st);
     default: return hipErrorInvalidValue;
@@ -909,8 +1094,9 @@ hipError_t launch_il_fused(const DevRagged& c, int kind, double* x, long ld, int
 
 bool rows_any_fits(const DevRagged& c) { return c.S >= 1 && c.S <= 256; }
 
-hipError_t launch_rows_any(const DevRagged& c, const double* src, long lds, double* dst, long ldd,
-                           int rows, const DiagTail* tail, bool stream, hipStream_t st) {
+static hipError_t rows_any_launch(const DevRagged& c, const double* src, long lds, double* dst,
+                                  long ldd, int rows, const DiagTail* tail, bool stream,
+                                  const StateUpdate* update, hipStream_t st) {
   if (!rows_any_fits(c)) return hipErrorInvalidValue;
   // rows per workgroup: at least a wave of chunks, at most 256 (128 of short
   // rows: 200000 rows of 100 74 us, 93 with 256), and in between as many as
@@ -928,24 +1114,39 @@ hipError_t launch_rows_any(const DevRagged& c, const double* src, long lds, doub
   const dim3 grid((unsigned)((rows + R - 1) / R + (tail ? 1 : 0)));
   const FusedArgs a = fused_args(c, nullptr, 0, rows);
   const DiagTail d = tail ? *tail : DiagTail{};
-#define CHX_ROWS(P_, M_, RAG_)                                                                  \
-  hipLaunchKernelGGL((rows_any<P_, M_, RAG_>), grid, dim3(T), lds_bytes, st, src, lds, dst, ldd, \
-                     rows, c.n, magic, R, a, d, stream)
+  const StateUpdate up = update ? *update : StateUpdate{};
+#define CHX_ROWS(P_, M_, RAG_, U_)                                                               \
+  hipLaunchKernelGGL((rows_any<P_, M_, RAG_, U_>), grid, dim3(T), lds_bytes, st, src, lds, dst,  \
+                     ldd, rows, c.n, magic, R, a, d, stream, up)
+#define CHX_ROWS_M(RAG_, U_)                            \
+  do {                                                  \
+    if (c.M == 8) CHX_ROWS(2, 8, RAG_, U_);             \
+    else if (c.M == 16) CHX_ROWS(2, 16, RAG_, U_);      \
+    else CHX_ROWS(2, kChunk, RAG_, U_);                 \
+  } while (0)
   if (c.P == 1) {
-    if (c.even || c.M != kChunk) return hipErrorInvalidValue;
-    CHX_ROWS(1, kChunk, true);
-  } else if (c.M == 8) {
-    if (c.even) CHX_ROWS(2, 8, false);
-    else CHX_ROWS(2, 8, true);
-  } else if (c.M == 16) {
-    if (c.even) CHX_ROWS(2, 16, false);
-    else CHX_ROWS(2, 16, true);
+    if (c.even || c.M != kChunk || update) return hipErrorInvalidValue;
+    CHX_ROWS(1, kChunk, true, false);
+  } else if (update) {
+    if (c.even) CHX_ROWS_M(false, true);
+    else CHX_ROWS_M(true, true);
   } else {
-    if (c.even) CHX_ROWS(2, kChunk, false);
-    else CHX_ROWS(2, kChunk, true);
+    if (c.even) CHX_ROWS_M(false, false);
+    else CHX_ROWS_M(true, false);
   }
+#undef CHX_ROWS_M
 #undef CHX_ROWS
   return hipGetLastError();
+}
+
+hipError_t launch_rows_any(const DevRagged& c, const double* src, long lds, double* dst, long ldd,
+                           int rows, const DiagTail* tail, bool stream, hipStream_t st) {
+  return rows_any_launch(c, src, lds, dst, ldd, rows, tail, stream, nullptr, st);
+}
+
+hipError_t launch_rows_update(const DevRagged& c, const double* src, long lds, int rows,
+                              const StateUpdate& update, const DiagTail* tail, hipStream_t st) {
+  return rows_any_launch(c, src, lds, nullptr, 0, rows, tail, false, &update, st);
 }
 
 // Columns per workgroup, or 0 where 4 columns need more than 512 threads.
@@ -993,6 +1194,36 @@ hipError_t launch_column_whole(const DevRagged& c, const double* src, long lds, 
 #undef CHX_COLW_M
 #undef CHX_COLW_L
 #undef CHX_COLW
+  return hipGetLastError();
+}
+
+hipError_t launch_column_whole2(const DevRagged& c, const double* C, long ldc, const double* Cp,
+                                long ldp, double* dst, long ldd, int nx, int ny,
+                                const Ch2Coef& K, const ChCoef& D, double* dpart,
+                                hipStream_t st) {
+  if (c.P != 2 || c.M > 16 || c.S * 4 > 512 || nx < 5 || c.n != ny || dst == C || dst == Cp)
+    return hipErrorInvalidValue;
+  const dim3 grid((unsigned)((nx + 3) / 4)), block(((4 * c.S + 63) / 64) * 64);
+  const size_t lds_bytes =
+      ((size_t)16 * c.S + (c.even ? 0 : 12 * c.dcount) + 16) * sizeof(double);
+  const FusedArgs a = fused_args(c, nullptr, 0, nx);
+#define CHX_COL2(M_, RAG_, D_)                                                                    \
+  hipLaunchKernelGGL((column_whole2<M_, RAG_, D_>), grid, block, lds_bytes, st, C, ldc, Cp, ldp, \
+                     dst, ldd, nx, ny, K, D, dpart, a)
+#define CHX_COL2_M(RAG_, D_)             \
+  do {                                   \
+    if (c.M == 8) CHX_COL2(8, RAG_, D_); \
+    else CHX_COL2(16, RAG_, D_);         \
+  } while (0)
+  if (dpart) {
+    if (c.even) CHX_COL2_M(false, true);
+    else CHX_COL2_M(true, true);
+  } else {
+    if (c.even) CHX_COL2_M(false, false);
+    else CHX_COL2_M(true, false);
+  }
+#undef CHX_COL2_M
+#undef CHX_COL2
   return hipGetLastError();
 }
 

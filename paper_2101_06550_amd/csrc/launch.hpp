@@ -55,8 +55,8 @@ inline DevRagged as_ragged(const DevChunk& c) {
 
 // One-launch interleaved solve (kind -1) or nsteps steps of a batched 1D
 // scheme (kind 0 .. 2) in place on x (fused.hip): a workgroup holds every
-// chunk of il_fused_systems(S, batch) systems; 0 where S is too large.
-int il_fused_systems(int S, int batch);
+// chunk of il_fused_systems(S, batch, kind >= 0) systems; 0 where S is too large.
+int il_fused_systems(int S, int batch, bool steps = false);
 hipError_t launch_il_fused(const DevRagged& c, int kind, double* x, long ld, int batch, int nsteps,
                            double s, double al, hipStream_t st);
 
@@ -73,6 +73,19 @@ struct DiagTail {
 bool rows_any_fits(const DevRagged& c);
 hipError_t launch_rows_any(const DevRagged& c, const double* src, long lds, double* dst, long ldd,
                            int rows, const DiagTail* tail, bool stream, hipStream_t st);
+
+// The same rows solved into v, which advances two states element by element:
+// next = (2 C - Cp) + v, and next_prev = C unless it is NULL (both with ldn;
+// next may be Cp's array, or next C's and next_prev Cp's).
+struct StateUpdate {
+  const double* c = nullptr;
+  const double* cp = nullptr;
+  double* next = nullptr;
+  double* next_prev = nullptr;
+  long ldc = 0, ldp = 0, ldn = 0;
+};
+hipError_t launch_rows_update(const DevRagged& c, const double* src, long lds, int rows,
+                              const StateUpdate& update, const DiagTail* tail, hipStream_t st);
 
 // Number of candidate tile shapes of the separator kernel, and the LDS one
 // launch of shape `shape` needs (elem = sizeof the sweep type; diag = the

@@ -143,3 +143,50 @@ def test_two_launch_step_is_bitwise_repeatable_and_replayable(chx):  # noqa: F81
             outs.append((c.cpu().numpy(), d.cpu().numpy()))
         for o in outs[1:]:
             assert np.array_equal(o[0], outs[0][0]) and np.array_equal(o[1], outs[0][1])
+
+
+# (ny, nx): as GRIDS for the thesis scheme's two launches (tiles of four columns
+# with two on either side), and two grids of the column-streaming kernel, whose
+# waves also sum the diagnostics
+GRIDS2 = [(6, 5), (6, 6), (7, 130), (41, 38), (64, 64), (257, 259), (700, 90), (96, 2051),
+          (128, 4100), (2048, 64), (2050, 70), (2048, 2048), (3200, 1280)]
+
+
+@pytest.mark.parametrize("ny,nx", GRIDS2)
+@pytest.mark.parametrize("n", [1, 2, 3])
+def test_thesis_steps_of_any_grid(chx, orc, ny, nx, n):  # noqa: F811
+    """One to three steps in one call from two independent states in padded
+    arrays: both states (the previous one bitwise after one step) and every
+    state's mass and energy, against the oracle (20 eps (1 + 16 s') per step,
+    s' = 2/3 g dt / h^4, or 1e-12)."""
+    L, g, dt = 2 * math.pi, 0.01, 1e-6
+    if nx * ny > 1 << 20 and n == 2:
+        pytest.skip("the large grids run one and three steps")
+    c0, p0 = inputs.noise_field(ny, nx, 93), inputs.noise_field(ny, nx, 94)
+    h = chx.ch_create(nx, ny, L, L, 1.0, g, dt, scheme=chx.CHX_SCHEME_P2)
+    bufs = []
+    for f in (c0, p0):
+        b = torch.full((ny, nx + 3), 7.25, dtype=torch.float64, device="cuda")
+        b[:, :nx] = torch.from_numpy(f)
+        bufs.append(b)
+    d = torch.zeros(2 * (n + 1), dtype=torch.float64, device="cuda")
+    print(f"[case] thesis scheme, {n} steps {ny}x{nx}", flush=True)
+    chx.ch_adi_step_p2(h, bufs[0], bufs[1], nsteps=n, diag_out=d)
+    torch.cuda.synchronize()
+    out, diag = [b.cpu().numpy() for b in bufs], d.cpu().numpy()
+    assert np.all(out[0][:, nx:] == 7.25) and np.all(out[1][:, nx:] == 7.25)
+    s = 2.0 / 3.0 * g * dt / (L / max(nx, ny)) ** 4
+    tol = max(1e-12, 20 * np.finfo(float).eps * (1 + 16 * s))
+    c, p = c0, p0
+    for k in range(n + 1):
+        l1 = np.sum(np.abs(c)) * (L / nx) * (L / ny)
+        e = orc.ch_energy(c, L, L, g)
+        assert abs(diag[2 * k] - orc.ch_mass(c, L, L)) <= 4 * n * tol * l1
+        assert abs(diag[2 * k + 1] - e) <= 4 * n * tol * abs(e)
+        if k < n:
+            c, p = orc.ch2_step(c, p, L, L, 1.0, g, dt)
+    # each step doubles the newer state's error and adds the older one's
+    assert rel(out[0][:, :nx], c) < 4 ** n * tol
+    assert rel(out[1][:, :nx], p) < 4 ** n * tol
+    if n == 1:
+        assert np.array_equal(out[1][:, :nx], c0)
