@@ -53,6 +53,25 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;
 }
 
+// Brings a plan table of N lines of 64 bytes into the scalar cache: one load
+// per line, all in flight together, while the chunk's own loads are.  A
+// kernel starts with that cache empty, and the sweeps that read the table
+// hold few lines at a time, so without this the first of them wait on memory
+// again and again (FP32-refined 1024 x 1024, five steps: 406 us against 382;
+// rows of the 8192 x 8192 step: three steps 1.451 ms against 1.437).  Not in
+// kernels that read the pointer out of memory: it costs the ensemble's row
+// kernel its scalar table (0.94 ms against 1.13), and the FP64 column passes
+// gain nothing, their tables' first use lying behind the field's loads.
+template <int N>
+__device__ __forceinline__ void warm(const void* p) {
+  using Line = const __attribute__((address_space(4))) unsigned*;
+  const Line u = (Line)p;
+  unsigned x = 0;
+#pragma unroll
+  for (int i = 0; i < N; ++i) x |= u[16 * i];
+  asm volatile("" ::"s"(x));
+}
+
 // Streaming 16-byte global accesses (non-temporal: the data is touched once
 // per pass).  On gfx950 a plain copy moves 6.5 TB/s with non-temporal loads
 // and stores against 5.6 TB/s with ordinary ones; in the step's passes the

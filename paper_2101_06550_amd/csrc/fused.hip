@@ -179,20 +179,6 @@ __device__ __forceinline__ double dpp_row_from_right(double v, double edge) {
   return __hiloint2double(hi, lo);
 }
 
-// Brings a plan table of N lines of 64 bytes into the scalar cache: one load
-// per line, all in flight together, while the chunk's own loads are.  A
-// kernel starts with that cache empty, and the sweeps that read the table
-// hold few lines at a time, so without this each of them waits on memory.
-template <int N>
-__device__ __forceinline__ void warm(const double* p) {
-  using Line = const __attribute__((address_space(4))) unsigned*;
-  const Line u = (Line)p;
-  unsigned x = 0;
-#pragma unroll
-  for (int i = 0; i < N; ++i) x |= u[16 * i];
-  asm volatile("" ::"s"(x));
-}
-
 // Lane l of a quad receives the value of its lane (SEL >> 2 l) & 3.
 template <int SEL>
 __device__ __forceinline__ double dpp_quad(double v) {

@@ -398,8 +398,9 @@ __device__ __forceinline__ void rstep_final_body(const BV& B, CP __restrict__ c,
   }
 }
 
-// Single-field kernels: block = 4 waves = 4 consecutive (64-column segment,
-// chunk) pairs, segments fastest (full blocks whatever the segment count).
+// Single-field kernels: a block of w waves takes w consecutive (64-column
+// segment, chunk) pairs, segments fastest (full blocks whatever the segment
+// count).
 template <bool DIAG, int NB>
 __global__ __launch_bounds__(256) void rstep_first(const double* __restrict__ c, long ld,
                                                    double* __restrict__ rbuf,
@@ -409,9 +410,11 @@ __global__ __launch_bounds__(256) void rstep_first(const double* __restrict__ c,
                                                    BandT<float> bd, ChCoef K,
                                                    double* __restrict__ part, RBufs Bv, int Sc,
                                                    const double* __restrict__ rec) {
-  const int li = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int li = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
   const int seg = li % nseg, kc = li / nseg;
   if (kc >= Sc) return;  // no barrier in this kernel
+  warm<MI / 2>(rec32);
+  if (NB > 0) warm<MI>(rec);
   rstep_first_body<DIAG, NB>(c, ld, rbuf, y32, rho, nx, ny, nseg, rec32, bd, K, part, seg, kc,
                              Bv, Sc, rec);
 }
@@ -425,9 +428,11 @@ __global__ __launch_bounds__(256) void rstep_resid(const double* __restrict__ rb
                                                    const float* __restrict__ rec32,
                                                    BandT<float> bd, BandT<double> ax,
                                                    BandT<double> ay) {
-  const int li = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int li = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
   const int seg = li % nseg, kc = li / nseg;
   if (kc >= Sc) return;  // no barrier in this kernel
+  warm<MI / 2>(rec32);
+  warm<MI>(rec);
   rstep_resid_body<NB>(rbuf, B, y32, rho, nx, ny, Sc, rec, rec32, bd, ax, ay, seg, kc);
 }
 
@@ -436,9 +441,10 @@ __global__ __launch_bounds__(256) void rstep_final(RBufs B, double* __restrict__
                                                    int nx, int ny, int nseg, int Sc,
                                                    const double* __restrict__ rec, ChCoef K,
                                                    double* __restrict__ part) {
-  const int li = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int li = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
   const int seg = li % nseg, kc = li / nseg;
   if (kc >= Sc) return;  // no barrier in this kernel
+  warm<MI>(rec);
   rstep_final_body<NB, DIAG>(B, c, ld, nx, ny, nseg, Sc, rec, K, part, seg, kc);
 }
 
@@ -556,9 +562,14 @@ hipError_t launch_ens_rstep_final(const EnsRun* runs, const EnsClasses& cls, con
 int rstep_segments(int nx) { return (nx + kSegR - 1) / kSegR; }
 long rstep_parts(int nx, int ny) { return (long)rstep_segments(nx) * (ny / M); }
 
+// (segment, chunk) pairs per block: four, or one on grids whose pairs do not
+// fill the SIMDs twice, so that every CU gets some (with the rows' smaller
+// groups, 1024 x 1024 five steps 426 -> 410 us).
+static int rstep_waves(int nx, int ny) { return rstep_parts(nx, ny) < 2048 ? 1 : 4; }
+static dim3 rstep_block(int nx, int ny) { return dim3(64 * rstep_waves(nx, ny)); }
 static dim3 rstep_grid(int nx, int ny) {
-  const long pairs = (long)((nx + kSegR - 1) / kSegR) * (ny / M);
-  return dim3((unsigned)((pairs + 3) / 4));
+  const int w = rstep_waves(nx, ny);
+  return dim3((unsigned)((rstep_parts(nx, ny) + w - 1) / w));
 }
 
 hipError_t launch_rstep_first(const double* c, long ld, double* rbuf, float* y32, float* rho,
@@ -571,7 +582,7 @@ hipError_t launch_rstep_first(const double* c, long ld, double* rbuf, float* y32
   RBufs B{};
   for (int b = 0; b < nbprev; ++b) B.v[b] = vprev[b];
 #define CHX_RFIRST(D_, NB_)                                                                     \
-  hipLaunchKernelGGL((rstep_first<D_, NB_>), rstep_grid(nx, ny), dim3(256), 0, st, c, ld, rbuf, \
+  hipLaunchKernelGGL((rstep_first<D_, NB_>), rstep_grid(nx, ny), rstep_block(nx, ny), 0, st, c, ld, rbuf, \
                      y32, rho, nx, ny, nseg, cy.rec32, bd, K, part, B, cy.S, cy.rec)
   const bool d = part != nullptr;
   switch (nbprev) {
@@ -600,7 +611,7 @@ hipError_t launch_rstep_resid(const double* rbuf, const float* const* v, int nb,
   for (int b = 0; b < nb; ++b) B.v[b] = v[b];
   const int nseg = (nx + kSegR - 1) / kSegR;
 #define CHX_RRES(NB_)                                                                           \
-  hipLaunchKernelGGL((rstep_resid<NB_>), rstep_grid(nx, ny), dim3(256), 0, st, rbuf, B, y32, rho, \
+  hipLaunchKernelGGL((rstep_resid<NB_>), rstep_grid(nx, ny), rstep_block(nx, ny), 0, st, rbuf, B, y32, rho, \
                      nx, ny, nseg, cy.S, cy.rec, cy.rec32, bd, ax, ay)
   if (nb == 1) CHX_RRES(1);
   else if (nb == 2) CHX_RRES(2);
@@ -617,7 +628,7 @@ hipError_t launch_rstep_final(const float* const* v, int nb, double* c, long ld,
   for (int b = 0; b < nb; ++b) B.v[b] = v[b];
   const int nseg = (nx + kSegR - 1) / kSegR;
 #define CHX_RFIN(NB_, D_)                                                                         \
-  hipLaunchKernelGGL((rstep_final<NB_, D_>), rstep_grid(nx, ny), dim3(256), 0, st, B, c, ld, nx, \
+  hipLaunchKernelGGL((rstep_final<NB_, D_>), rstep_grid(nx, ny), rstep_block(nx, ny), 0, st, B, c, ld, nx, \
                      ny, nseg, cy.S, cy.rec, K, part)
   if (diag_out) {
     if (nb == 1) CHX_RFIN(1, true);

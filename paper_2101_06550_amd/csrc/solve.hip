@@ -532,6 +532,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void r
     const double* src, long lds, double* dst, long ldd, int rows, int n, int S, int R,
     const T* __restrict__ rec, BandT<T> bd, const T* __restrict__ blocks, int dlo, int dcount) {
   __shared__ RowLds<P, M, T> sh;
+  warm<(M - P) * sizeof(T) / 8>(rec);
   row_solve_body<P, M, T, ACC>(src, lds, dst, ldd, rows, n, S, R, rec, bd, blocks, dlo, dcount,
                                (long)blockIdx.x * R, sh);
 }
@@ -679,6 +680,7 @@ template <int P, int M, bool NTL = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void row_solve_half(
     double* x, int S, const double* __restrict__ rec, BandT<double> bd,
     const double* __restrict__ blocks, int dlo, int dcount) {
+  warm<M - P>(rec);
   row_half_body<P, M, NTL>(x + (long)blockIdx.x * (256 * M), S, rec, bd, blocks, dlo, dcount);
 }
 
@@ -690,6 +692,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void r
     const float* __restrict__ rec, BandT<float> bd, const float* __restrict__ blocks, int dlo,
     int dcount) {
   __shared__ RowLds<P, M, float> sh;
+  warm<(M - P) / 2>(rec);
   row_solve_body<P, M, float, false, float, float>(src, lds, dst, ldd, rows, n, S, R, rec, bd,
                                                    blocks, dlo, dcount, (long)blockIdx.x * R, sh);
 }
@@ -1724,7 +1727,10 @@ hipError_t launch_rows_lds32(const DevChunk& c, const double* src, long lds, dou
 
 hipError_t launch_rows_lds_f32(const DevChunk& c, const float* src, float* dst, int rows,
                                hipStream_t st) {
-  const int R = 256 / c.S;
+  // as many rows per workgroup as it holds, fewer where that leaves less than
+  // two workgroups per CU
+  int R = 256 / c.S;
+  if (rows / 512 < R) R = rows / 512 > 1 ? rows / 512 : 1;
   const long ngroups = ((long)rows + R - 1) / R;
   hipLaunchKernelGGL((row_solve_lds_f32<2, kChunk>), dim3((unsigned)ngroups), dim3(256), 0, st,
                      src, (long)c.n, dst, (long)c.n, rows, c.n, c.S, R, c.rec32,
