@@ -73,6 +73,7 @@ class ChParams(ctypes.Structure):
 
 
 _lib = None
+_torch = None  # imported by the first call that takes a tensor
 _V = ctypes.c_void_p
 _I = ctypes.c_int
 _L = ctypes.c_long
@@ -166,20 +167,33 @@ def _check(st: int, what: str):
         raise ChxError(st, what)
 
 
+# The helpers below run on every call, and a small solve or step is over in
+# the time that a few of them take: pointers and streams go to ctypes as plain
+# numbers (its argtypes convert them), the current stream's handle is read
+# without a Stream object, and a tensor's storage is looked at only where the
+# tensor itself does not already cover what the kernels touch.
+def _th():
+    global _torch
+    if _torch is None:
+        import torch
+        _torch = torch
+    return _torch
+
+
 def _stream(stream):
-    import torch
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
+        c = _th()._C
+        return c._cuda_getCurrentRawStream(c._cuda_getDevice())
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def _devptr(t, what):
-    import torch
+    torch = _torch or _th()
     if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise ChxError(CHX_EINVAL, f"{what} must be a device tensor")
     if t.dtype != torch.float64:
         raise ChxError(CHX_EINVAL, f"{what} must be float64")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _storage_elems(t) -> int:
@@ -187,20 +201,27 @@ def _storage_elems(t) -> int:
     return t.untyped_storage().nbytes() // t.element_size() - t.storage_offset()
 
 
+def _covers(t, count: int) -> bool:
+    """Whether count elements from t's first lie inside its storage."""
+    return (t.is_contiguous() and count <= t.numel()) or count <= _storage_elems(t)
+
+
 def _field_ld(t, nx: int, ny: int, ld, what: str) -> int:
     """Leading dimension of a (ny, >= nx) field with unit column stride whose
     rows, ld apart, lie inside its storage (the kernels read and write
     (ny - 1) * ld + nx elements from its start); ChxError otherwise."""
-    if t.dim() != 2 or t.shape[0] != ny or t.shape[1] < nx:
+    shape = t.shape
+    if len(shape) != 2 or shape[0] != ny or shape[1] < nx:
         raise ChxError(CHX_EINVAL, f"{what} must be a ({ny}, >= {nx}) tensor, got "
-                                   f"{tuple(t.shape)}")
-    if nx > 1 and t.stride(1) != 1:
+                                   f"{tuple(shape)}")
+    s0, s1 = t.stride()
+    if nx > 1 and s1 != 1:
         raise ChxError(CHX_EINVAL, f"{what} must have unit column stride")
-    ld = t.stride(0) if ld is None else int(ld)
-    if (ny > 1 and t.stride(0) != ld) or ld < nx:
+    ld = s0 if ld is None else int(ld)
+    if (ny > 1 and s0 != ld) or ld < nx:
         raise ChxError(CHX_EINVAL, f"{what}: leading dimension {ld} must be its row stride "
                                    f"and >= {nx}")
-    if (ny - 1) * ld + nx > _storage_elems(t):
+    if not _covers(t, (ny - 1) * ld + nx):
         raise ChxError(CHX_EINVAL, f"{what}: rows run past the end of its storage")
     return ld
 
@@ -216,22 +237,22 @@ def _diag(diag_out, count: int, what: str = "diag_out"):
     """Device pointer of an optional float64 diagnostics buffer of >= count
     contiguous values (null when diag_out is None)."""
     if diag_out is None:
-        return ctypes.c_void_p(0)
+        return 0
     if not diag_out.is_contiguous() or diag_out.numel() < count:
         raise ChxError(CHX_EINVAL, f"{what} must be contiguous with >= {count} values")
     return _devptr(diag_out, what)
 
 
 def _workspace(nbytes: int, ws, device):
-    import torch
     if nbytes == 0:
-        return None, ctypes.c_void_p(0), 0
+        return None, 0, 0
     if ws is None:
+        torch = _th()
         ws = torch.empty(nbytes + 256, dtype=torch.uint8, device=device)
     base = ws.data_ptr()
     aligned = (base + 255) & ~255
     avail = ws.numel() * ws.element_size() - (aligned - base)
-    return ws, ctypes.c_void_p(aligned), avail
+    return ws, aligned, avail
 
 
 # ----------------------------------------------------------------------- version
@@ -311,22 +332,24 @@ def _solve_ld(kind, plan, batch, x, ld, layout):
         span = (plan.n - 1) * ld + batch if layout == CHX_INTERLEAVED else (batch - 1) * ld + plan.n
         if x.dim() == 2 and x.stride(-1) != 1:
             raise ChxError(CHX_EINVAL, f"{kind}_solve_batch: x must have unit last stride")
-        if ld >= 1 and span > _storage_elems(x):
+        if ld >= 1 and not _covers(x, span):
             raise ChxError(CHX_EINVAL, f"{kind}_solve_batch: {span} elements needed from x's "
                                        "start, its storage holds fewer")
     return ld
 
 
 def _solve(kind, plan, batch, x, ld, layout, dtype, refine_passes, ws, stream):
-    lib = load()
+    lib = _lib or load()
+    penta = kind == "penta"
     ld = _solve_ld(kind, plan, batch, x, ld, layout)
     xp = _devptr(x, "x")
-    nbytes = getattr(lib, f"{kind}_solve_ws_bytes")(plan.handle, batch, layout, dtype,
-                                                    refine_passes)
+    nbytes = (lib.penta_solve_ws_bytes if penta else lib.tri_solve_ws_bytes)(
+        plan.handle, batch, layout, dtype, refine_passes)
     keep, wsp, avail = _workspace(nbytes, ws, x.device)
-    st = getattr(lib, f"{kind}_solve_batch")(plan.handle, batch, xp, ld, layout,
-                                             dtype, refine_passes, wsp, avail, _stream(stream))
-    _check(st, f"{kind}_solve_batch")
+    st = (lib.penta_solve_batch if penta else lib.tri_solve_batch)(
+        plan.handle, batch, xp, ld, layout, dtype, refine_passes, wsp, avail, _stream(stream))
+    if st != CHX_OK:
+        _check(st, f"{kind}_solve_batch")
     return keep
 
 
@@ -460,14 +483,15 @@ def stencil2d_apply(inp, out, weights, left: int, right: int, top: int, bottom: 
                     periodic: bool = True, premap: int = 0, ld: int | None = None,
                     stream=None) -> None:
     ny, nx = inp.shape
-    ld = inp.stride(0) if ld is None else ld
-    if tuple(out.shape) != (ny, nx):
+    ist, ost = inp.stride(), out.stride()
+    ld = ist[0] if ld is None else ld
+    if out.shape != inp.shape:
         raise ChxError(CHX_EINVAL, "stencil2d_apply: out must have the shape of inp")
-    for t in (inp, out):  # one leading dimension serves both arrays
-        if ny > 1 and t.stride(0) != ld or nx > 1 and t.stride(1) != 1:
+    for st in (ist, ost):  # one leading dimension serves both arrays
+        if ny > 1 and st[0] != ld or nx > 1 and st[1] != 1:
             raise ChxError(CHX_EINVAL, "stencil2d_apply: inp and out must be row-major with "
                                        "leading dimension ld")
-    import torch
+    torch = _torch or _th()
     if inp.dtype not in (torch.float64, torch.float32) or out.dtype != inp.dtype:
         raise ChxError(CHX_EINVAL, "stencil2d_apply: inp and out must both be float64 or "
                                    "both float32")
@@ -475,11 +499,10 @@ def stencil2d_apply(inp, out, weights, left: int, right: int, top: int, bottom: 
     for t, what in ((inp, "in"), (out, "out")):
         if not t.is_cuda:
             raise ChxError(CHX_EINVAL, f"{what} must be a device tensor")
-    w = (ctypes.c_double * len(weights))(*[float(v) for v in weights])
-    _check(load().stencil2d_apply(ctypes.c_void_p(inp.data_ptr()), ctypes.c_void_p(out.data_ptr()),
-                                  nx, ny, ld, dtype, w, left, right, top, bottom,
-                                  int(bool(periodic)), premap, _stream(stream)),
-           "stencil2d_apply")
+    w = (ctypes.c_double * len(weights))(*map(float, weights))
+    _check((_lib or load()).stencil2d_apply(
+        inp.data_ptr(), out.data_ptr(), nx, ny, ld, dtype, w, left, right, top, bottom,
+        int(bool(periodic)), premap, _stream(stream)), "stencil2d_apply")
 
 
 # ----------------------------------------------------------------- Cahn-Hilliard
@@ -525,7 +548,7 @@ def _handle_ws(h, lib, ws, device):
     nbytes = lib.ch_ws_bytes(h.handle)
     if ws is None:
         if h._ws is None or h._ws.numel() < nbytes + 256 or h._ws.device != device:
-            import torch
+            torch = _th()
             h._ws = torch.empty(nbytes + 256, dtype=torch.uint8, device=device)
         ws = h._ws
     return _workspace(nbytes, ws, device)
@@ -855,11 +878,19 @@ def ch_ensemble_step(e: Ensemble, fields, nsteps: int = 1, diag_out=None, use_gr
 def _ens_fields(e: Ensemble, fields):
     if len(fields) != e.nruns:
         raise ChxError(CHX_EINVAL, "one field per run")
-    lds = [_field_ld(f, nx, ny, None, f"field {r}")
-           for r, (f, (nx, ny)) in enumerate(zip(fields, e.shapes))]
-    ptrs = (ctypes.c_void_p * e.nruns)(*[_devptr(f, f"field {r}").value
-                                         for r, f in enumerate(fields)])
-    return ptrs, (ctypes.c_long * e.nruns)(*lds)
+    f64 = _th().float64
+    ptrs, lds = [], []
+    for r, (f, shape) in enumerate(zip(fields, e.shapes)):
+        nx, ny = shape
+        # a plain contiguous field needs none of the general checks
+        if not (getattr(f, "is_cuda", False) and f.dtype is f64 and f.is_contiguous() and
+                f.shape == (ny, nx)):
+            lds.append(_field_ld(f, nx, ny, None, f"field {r}"))
+            ptrs.append(_devptr(f, f"field {r}"))
+        else:
+            lds.append(nx)
+            ptrs.append(f.data_ptr())
+    return (ctypes.c_void_p * e.nruns)(*ptrs), (ctypes.c_long * e.nruns)(*lds)
 
 
 def ch_ensemble_moments(e: Ensemble, fields, stream=None):
