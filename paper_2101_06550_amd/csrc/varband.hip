@@ -11,8 +11,10 @@
 //  - factor / solve: the factors overwrite the diagonals in place (as in the
 //    thesis): b <- beta, c <- 1/alpha, d <- gamma, e <- delta, with a kept as
 //    epsilon; tridiagonal: b <- 1/den, c <- chat.
-//  - rewrite: factor and solve in one kernel that leaves the diagonals alone
-//    and keeps the back sweep's coefficients in the workspace.
+//  - rewrite: factor and solve in one kernel that leaves the diagonals alone;
+//    the back sweep's coefficients are computed a second time from the
+//    diagonals, or, for systems that are not periodic and few or short, kept
+//    in the workspace (the rule and its figures are at rewrite()).
 //  - periodic systems: the last two unknowns are bordered off (Ch.4, Navon)
 //    or the corners split off as a rank-one term (Ch.5, Sherman-Morrison),
 //    both built from each system's own rows.  The correction that the thesis
@@ -37,17 +39,13 @@
 namespace chx_vb {
 
 constexpr int kThreads = 256;
-#ifndef CHX_VB_U
-#define CHX_VB_U 8
-#endif
-constexpr int kU = CHX_VB_U;  // rows staged per batch of loads
+constexpr int kU = 8;  // rows the factor kernels stage per batch of loads
 // The staged loads are non-temporal: every value is used once per pass
-// (measured at n = 1024, 65536 systems: factored solves 2-7 % faster,
-// rewrites 2-3 %).
+// (measured at n = 1024, 65536 systems: factored solves 2-7 % faster).
 // The solve kernels stage fewer rows: with one system per thread the batch
 // gives one wave per SIMD, and at 65536 systems x 1024 both factored solves
 // ran fastest at 6 (penta 1.46 ms against 1.84 ms at 8; tri 0.89 against
-// 1.07), while the fused factor-and-solve kernels were best at 8.
+// 1.07).
 constexpr int kUS = 6;
 
 // ---------------------------------------------------------------------------
@@ -103,17 +101,19 @@ __device__ __forceinline__ void penta_load_tail(int n, long ld, long s, const do
 // b_i (i >= 1), d_i (i <= m-2), e_i (i <= m-3); the entries that wrap past
 // column m-1 form k.  Returns gamma_i, delta_i, 1/alpha_i, beta_i and the
 // forward values through the state.
-template <bool PER, bool RHS>
+// EDGE: row i may be one of the first or last two, whose band entries, k and
+// h differ from the others'; SUMS: the products with h are wanted.
+template <bool PER, bool RHS, bool EDGE = true, bool SUMS = true>
 __device__ __forceinline__ void penta_fwd_row(int i, int m, double ra, double rb, double rc,
                                               double rd, double re, double rf,
                                               const PentaTail& tl, PentaFwd& st,
                                               double& beta, double& inv, double& gam,
                                               double& del, double& g, double& pk0,
                                               double& pk1, double& wh0, double& wh1) {
-  const double ai = (i >= 2) ? ra : 0.0;
-  const double bi = (i >= 1) ? rb : 0.0;
-  const double di = (i <= m - 2) ? rd : 0.0;
-  const double ei = (i <= m - 3) ? re : 0.0;
+  const double ai = (!EDGE || i >= 2) ? ra : 0.0;
+  const double bi = (!EDGE || i >= 1) ? rb : 0.0;
+  const double di = (!EDGE || i <= m - 2) ? rd : 0.0;
+  const double ei = (!EDGE || i <= m - 3) ? re : 0.0;
   beta = bi - ai * st.gm2;
   const double alpha = rc - ai * st.dm2 - beta * st.gm1;
   inv = 1.0 / alpha;
@@ -124,21 +124,21 @@ __device__ __forceinline__ void penta_fwd_row(int i, int m, double ra, double rb
   if (PER) {
     // columns n-2 and n-1 of row i (k), rows n-2 and n-1 at column i (h)
     double k0 = 0.0, k1 = 0.0, h0 = 0.0, h1 = 0.0;
-    if (i == 0) {
+    if (EDGE && i == 0) {
       k0 = ra;
       k1 = rb;
       h0 = tl.h0_0;
       h1 = tl.h1_0;
     }
-    if (i == 1) {
+    if (EDGE && i == 1) {
       k1 = ra;
       h1 = tl.h1_1;
     }
-    if (i == m - 2) {
+    if (EDGE && i == m - 2) {
       k0 = k0 + re;
       h0 = h0 + tl.h0_m2;
     }
-    if (i == m - 1) {
+    if (EDGE && i == m - 1) {
       k0 = k0 + rd;
       k1 = k1 + re;
       h0 = h0 + tl.h0_m1;
@@ -148,24 +148,26 @@ __device__ __forceinline__ void penta_fwd_row(int i, int m, double ra, double rb
     pk1 = (k1 - ai * st.q2 - beta * st.q1) * inv;
     // R^T w = h: R is unit upper triangular with gamma above the diagonal
     // and delta two above
-    wh0 = h0 - st.gm1 * st.u1 - st.dm2 * st.u2;
-    wh1 = h1 - st.gm1 * st.v1 - st.dm2 * st.v2;
-    if (RHS) {
-      st.s0 = st.s0 + wh0 * g;
-      st.s1 = st.s1 + wh1 * g;
+    if (SUMS) {
+      wh0 = h0 - st.gm1 * st.u1 - st.dm2 * st.u2;
+      wh1 = h1 - st.gm1 * st.v1 - st.dm2 * st.v2;
+      if (RHS) {
+        st.s0 = st.s0 + wh0 * g;
+        st.s1 = st.s1 + wh1 * g;
+      }
+      st.m00 = st.m00 + wh0 * pk0;
+      st.m01 = st.m01 + wh0 * pk1;
+      st.m10 = st.m10 + wh1 * pk0;
+      st.m11 = st.m11 + wh1 * pk1;
+      st.u2 = st.u1;
+      st.u1 = wh0;
+      st.v2 = st.v1;
+      st.v1 = wh1;
     }
-    st.m00 = st.m00 + wh0 * pk0;
-    st.m01 = st.m01 + wh0 * pk1;
-    st.m10 = st.m10 + wh1 * pk0;
-    st.m11 = st.m11 + wh1 * pk1;
     st.p2 = st.p1;
     st.p1 = pk0;
     st.q2 = st.q1;
     st.q1 = pk1;
-    st.u2 = st.u1;
-    st.u1 = wh0;
-    st.v2 = st.v1;
-    st.v1 = wh1;
   }
   st.gm2 = st.gm1;
   st.gm1 = gam;
@@ -232,7 +234,8 @@ __device__ __forceinline__ void penta_back(int m, long s, const double* __restri
 
 // Workspace vectors of a periodic penta batch: rows 0..m-1, stride ldw.
 //   factor/solve: [w0 | w1 | pk0 | pk1] then Minv (4 x ldw)
-//   rewrite:      [gamma | delta | pk0 | pk1]        (non-periodic: the first two)
+//   rewrite:      the state of the forward sweep before every block of rows
+//                 (10 x ldw), or, kept and non-periodic, [gamma | delta]
 
 template <bool PER>
 __global__ __launch_bounds__(kThreads) void penta_batch_factor_k(
@@ -373,78 +376,6 @@ __global__ __launch_bounds__(kThreads) void penta_batch_solve_k(
   }
 }
 
-template <bool PER>
-__global__ __launch_bounds__(kThreads) void penta_batch_rewrite_k(
-    int n, int batch, long ld, const double* __restrict__ a, const double* __restrict__ b,
-    const double* __restrict__ c, const double* __restrict__ d, const double* __restrict__ e,
-    double* __restrict__ x, double* __restrict__ ws, long ldw) {
-  const long s = (long)blockIdx.x * kThreads + threadIdx.x;
-  if (s >= batch) return;
-  const int m = PER ? n - 2 : n;
-  PentaTail tl{};
-  if (PER) penta_load_tail<PER, true>(n, ld, s, a, b, c, d, e, x, tl);
-  double* gm = ws;
-  double* dl = ws + (long)m * ldw;
-  double* p0 = PER ? ws + 2L * m * ldw : nullptr;
-  double* p1 = PER ? ws + 3L * m * ldw : nullptr;
-  PentaFwd st;
-  int i = 0;
-  for (; i + kU <= m; i += kU) {
-    double va[kU], vb[kU], vc[kU], vd[kU], ve[kU], vf[kU];
-#pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      const long r = (long)(i + u) * ld + s;
-      va[u] = __builtin_nontemporal_load(&a[r]);
-      vb[u] = __builtin_nontemporal_load(&b[r]);
-      vc[u] = __builtin_nontemporal_load(&c[r]);
-      vd[u] = __builtin_nontemporal_load(&d[r]);
-      ve[u] = __builtin_nontemporal_load(&e[r]);
-      vf[u] = __builtin_nontemporal_load(&x[r]);
-    }
-#pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      double beta, inv, gam, del, g, pk0, pk1, wh0, wh1;
-      penta_fwd_row<PER, true>(i + u, m, va[u], vb[u], vc[u], vd[u], ve[u], vf[u], tl, st, beta,
-                               inv, gam, del, g, pk0, pk1, wh0, wh1);
-      const long rw = (long)(i + u) * ldw + s;
-      x[(long)(i + u) * ld + s] = g;
-      gm[rw] = gam;
-      dl[rw] = del;
-      if (PER) {
-        p0[rw] = pk0;
-        p1[rw] = pk1;
-      }
-    }
-  }
-  for (; i < m; ++i) {
-    const long r = (long)i * ld + s;
-    double beta, inv, gam, del, g, pk0, pk1, wh0, wh1;
-    penta_fwd_row<PER, true>(i, m, a[r], b[r], c[r], d[r], e[r], x[r], tl, st, beta, inv, gam,
-                             del, g, pk0, pk1, wh0, wh1);
-    const long rw = (long)i * ldw + s;
-    x[r] = g;
-    gm[rw] = gam;
-    dl[rw] = del;
-    if (PER) {
-      p0[rw] = pk0;
-      p1[rw] = pk1;
-    }
-  }
-  double t0 = 0.0, t1 = 0.0;
-  if (PER) {
-    double mi[4];
-    penta_minv(tl, st, mi);
-    const double r0 = tl.f0 - st.s0, r1 = tl.f1 - st.s1;
-    t0 = mi[0] * r0 + mi[1] * r1;
-    t1 = mi[2] * r0 + mi[3] * r1;
-  }
-  penta_back<kU, PER>(m, s, gm, ldw, dl, ldw, p0, p1, ldw, t0, t1, x, ld);
-  if (PER) {
-    x[(long)(n - 2) * ld + s] = t0;
-    x[(long)(n - 1) * ld + s] = t1;
-  }
-}
-
 // ---------------------------------------------------------------------------
 // Tridiagonal.  Row i: a_i x_{i-1} + b_i x_i + c_i x_{i+1}.  Periodic: A =
 // A' + u v^T with u = (-b_0, 0, .., 0, c_{n-1}), v = (1, 0, .., 0, -a_0/b_0);
@@ -452,7 +383,8 @@ __global__ __launch_bounds__(kThreads) void penta_batch_rewrite_k(
 // diagonal ends (Ch.5).  A' = L R with den on L's diagonal, a below it, and
 // chat above R's unit diagonal; x = R^{-1}(L^{-1} f - phi L^{-1} u) with
 // phi = (w . L^{-1} f) / (1 + w . L^{-1} u), w = R^{-T} v.
-// Workspace: factor/solve [zu | w] then 1/(1 + v.z); rewrite [chat | zu].
+// Workspace: factor/solve [zu | w] then 1/(1 + v.z); rewrite the state of the
+// forward sweep before every block of rows, or, kept and non-periodic, [chat].
 // ---------------------------------------------------------------------------
 
 struct TriFwd {
@@ -463,29 +395,33 @@ struct TriFwd {
   double sy = 0, sz = 0;
 };
 
-template <bool PER, bool RHS>
+// EDGE: row i may be the first or the last; SUMS: the products with w are
+// wanted.
+template <bool PER, bool RHS, bool EDGE = true, bool SUMS = true>
 __device__ __forceinline__ void tri_fwd_row(int i, int n, double ra, double rb, double rc,
                                             double rf, double a0, double b0, double cl,
                                             TriFwd& st, double& inv, double& ch, double& y,
                                             double& z, double& w) {
-  const double ai = (i >= 1) ? ra : 0.0;
+  const double ai = (!EDGE || i >= 1) ? ra : 0.0;
   double bi = rb;
-  if (PER && i == 0) bi = 2.0 * b0;
-  if (PER && i == n - 1) bi = rb + a0 * cl / b0;
+  if (EDGE && PER && i == 0) bi = 2.0 * b0;
+  if (EDGE && PER && i == n - 1) bi = rb + a0 * cl / b0;
   const double den = bi - ai * st.ch1;
   inv = 1.0 / den;
-  ch = (i <= n - 2) ? rc * inv : 0.0;
+  ch = (!EDGE || i <= n - 2) ? rc * inv : 0.0;
   y = RHS ? (rf - ai * st.y1) * inv : 0.0;
   z = w = 0.0;
   if (PER) {
-    const double ui = (i == 0) ? -b0 : ((i == n - 1) ? cl : 0.0);
-    const double vi = (i == 0) ? 1.0 : ((i == n - 1) ? -a0 / b0 : 0.0);
+    const double ui = (EDGE && i == 0) ? -b0 : ((EDGE && i == n - 1) ? cl : 0.0);
     z = (ui - ai * st.z1) * inv;
-    w = vi - st.ch1 * st.w1;
-    if (RHS) st.sy = st.sy + w * y;
-    st.sz = st.sz + w * z;
     st.z1 = z;
-    st.w1 = w;
+    if (SUMS) {
+      const double vi = (EDGE && i == 0) ? 1.0 : ((EDGE && i == n - 1) ? -a0 / b0 : 0.0);
+      w = vi - st.ch1 * st.w1;
+      if (RHS) st.sy = st.sy + w * y;
+      st.sz = st.sz + w * z;
+      st.w1 = w;
+    }
   }
   st.ch1 = ch;
   st.y1 = y;
@@ -596,50 +532,347 @@ __global__ __launch_bounds__(kThreads) void tri_batch_solve_k(int n, int batch, 
   tri_back<kUS, PER>(n, s, c, ld, PER ? ws : nullptr, ldw, phi, x, ld);
 }
 
+// ---------------------------------------------------------------------------
+// Rewrite: factor and solve in one kernel, one system per thread, one wave
+// per workgroup so that few systems still spread over many CUs.
+//
+// A system is two serial sweeps, and a batch rarely gives more than one wave
+// per SIMD, so nothing hides a wave's own waits.  Both kernels therefore hold
+// two groups of U rows in registers and load one while they work on the
+// other.  Past a few tens of thousands of systems the memory traffic bounds
+// them: a periodic pentadiagonal row costs 136 bytes if its factors are
+// written and read back (6 loads, 5 stores, 5 loads, 1 store) and 109 to 114
+// if its coefficients are read a second time and only the sweep's state is
+// kept every 32 or 16 rows.  Below that the recurrence bounds them (one FP64
+// division and some 25 dependent operations per row).  A branch around the
+// loads of a group costs more than the loads of rows that do not exist: the
+// wait before the other group then covers both (1024 x 16384: 0.50 ms
+// against 0.35).
+// ---------------------------------------------------------------------------
+
+constexpr int kWave = 64;
+
+// The two matrices, as the sweeps below see them.  row(): one row of the
+// factorisation from its coefficients and right-hand side q; o[0] is the
+// forward value, o[1..] what the way back needs beside it (in the order of
+// the workspace's vectors).  border(): the bordering's or rank-one term's
+// values t from the sums of a whole sweep; free(): the forward value without
+// their part.  back(): one row of the back substitution.
 template <bool PER>
-__global__ __launch_bounds__(kThreads) void tri_batch_rewrite_k(
-    int n, int batch, long ld, const double* __restrict__ a, const double* __restrict__ b,
-    const double* __restrict__ c, double* __restrict__ x, double* __restrict__ ws, long ldw) {
-  const long s = (long)blockIdx.x * kThreads + threadIdx.x;
-  if (s >= batch) return;
-  const double a0 = PER ? a[s] : 0.0, b0 = PER ? b[s] : 0.0;
-  const double cl = PER ? c[(long)(n - 1) * ld + s] : 0.0;
-  double* chv = ws;
-  double* zu = PER ? ws + (long)n * ldw : nullptr;
-  TriFwd st;
-  int i = 0;
-  for (; i + kU <= n; i += kU) {
-    double va[kU], vb[kU], vc[kU], vf[kU];
-#pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      const long r = (long)(i + u) * ld + s;
-      va[u] = __builtin_nontemporal_load(&a[r]);
-      vb[u] = __builtin_nontemporal_load(&b[r]);
-      vc[u] = __builtin_nontemporal_load(&c[r]);
-      vf[u] = __builtin_nontemporal_load(&x[r]);
-    }
-#pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      double inv, ch, y, z, w;
-      tri_fwd_row<PER, true>(i + u, n, va[u], vb[u], vc[u], vf[u], a0, b0, cl, st, inv, ch, y,
-                             z, w);
-      const long rw = (long)(i + u) * ldw + s;
-      x[(long)(i + u) * ld + s] = y;
-      chv[rw] = ch;
-      if (PER) zu[rw] = z;
+struct Penta {
+  static constexpr int kBands = 5, kOut = PER ? 5 : 3, kBack = 2, kState = PER ? 10 : 6, kEdge = 2;
+  static constexpr bool kPeriodic = PER;
+  using State = PentaFwd;
+  using Tail = PentaTail;
+  static __device__ __forceinline__ int rows(int n) { return PER ? n - 2 : n; }
+  static __device__ __forceinline__ void tail(int n, long ld, long s, const double* const* q,
+                                              Tail& t) {
+    if (PER) penta_load_tail<PER, true>(n, ld, s, q[0], q[1], q[2], q[3], q[4], q[5], t);
+  }
+  template <bool EDGE, bool SUMS>
+  static __device__ __forceinline__ void row(int i, int m, const double (&q)[6], const Tail& t,
+                                             State& st, double (&o)[kOut]) {
+    double beta, inv, pk0, pk1, wh0, wh1;
+    penta_fwd_row<PER, true, EDGE, SUMS>(i, m, q[0], q[1], q[2], q[3], q[4], q[5], t, st, beta,
+                                         inv, o[1], o[2], o[0], pk0, pk1, wh0, wh1);
+    if constexpr (PER) {
+      o[3] = pk0;
+      o[4] = pk1;
     }
   }
-  for (; i < n; ++i) {
-    const long r = (long)i * ld + s;
-    double inv, ch, y, z, w;
-    tri_fwd_row<PER, true>(i, n, a[r], b[r], c[r], x[r], a0, b0, cl, st, inv, ch, y, z, w);
-    const long rw = (long)i * ldw + s;
-    x[r] = y;
-    chv[rw] = ch;
-    if (PER) zu[rw] = z;
+  static __device__ __forceinline__ void border(const Tail& tl, const State& st, double (&t)[2]) {
+    if (!PER) return;
+    double mi[4];
+    penta_minv(tl, st, mi);
+    const double r0 = tl.f0 - st.s0, r1 = tl.f1 - st.s1;
+    t[0] = mi[0] * r0 + mi[1] * r1;
+    t[1] = mi[2] * r0 + mi[3] * r1;
   }
-  const double phi = PER ? st.sy / (1.0 + st.sz) : 0.0;
-  tri_back<kU, PER>(n, s, chv, ldw, zu, ldw, phi, x, ld);
+  static __device__ __forceinline__ double free(const double (&o)[kOut], const double (&t)[2]) {
+    if constexpr (PER) return o[0] - o[3] * t[0] - o[4] * t[1];
+    return o[0];
+  }
+  static __device__ __forceinline__ double back(double v, double gam, double del, double x1,
+                                                double x2) {
+    return v - gam * x1 - del * x2;
+  }
+  static __device__ __forceinline__ void finish(int n, long ld, int lane, const double (&t)[2],
+                                                double* x) {
+    if (!PER) return;
+    x[(long)(n - 2) * ld + lane] = t[0];
+    x[(long)(n - 1) * ld + lane] = t[1];
+  }
+  static __device__ __forceinline__ void save(const State& st, double (&k)[kState]) {
+    k[0] = st.gm1, k[1] = st.gm2, k[2] = st.dm1, k[3] = st.dm2, k[4] = st.g1;
+    k[5] = st.g2;
+    if constexpr (PER) k[6] = st.p1, k[7] = st.p2, k[8] = st.q1, k[9] = st.q2;
+  }
+  static __device__ __forceinline__ void restore(const double (&k)[kState], State& st) {
+    st.gm1 = k[0], st.gm2 = k[1], st.dm1 = k[2], st.dm2 = k[3], st.g1 = k[4];
+    st.g2 = k[5];
+    if constexpr (PER) st.p1 = k[6], st.p2 = k[7], st.q1 = k[8], st.q2 = k[9];
+  }
+};
+
+struct TriTail {
+  double a0, b0, cl;
+};
+
+template <bool PER>
+struct Tri {
+  static constexpr int kBands = 3, kOut = PER ? 3 : 2, kBack = 1, kState = PER ? 3 : 2, kEdge = 1;
+  static constexpr bool kPeriodic = PER;
+  using State = TriFwd;
+  using Tail = TriTail;
+  static __device__ __forceinline__ int rows(int n) { return n; }
+  static __device__ __forceinline__ void tail(int n, long ld, long s, const double* const* q,
+                                              Tail& t) {
+    if (!PER) return;
+    t.a0 = q[0][s];
+    t.b0 = q[1][s];
+    t.cl = q[2][(long)(n - 1) * ld + s];
+  }
+  template <bool EDGE, bool SUMS>
+  static __device__ __forceinline__ void row(int i, int n, const double (&q)[4], const Tail& t,
+                                             State& st, double (&o)[kOut]) {
+    double inv, z, w;
+    tri_fwd_row<PER, true, EDGE, SUMS>(i, n, q[0], q[1], q[2], q[3], t.a0, t.b0, t.cl, st, inv,
+                                       o[1], o[0], z, w);
+    if constexpr (PER) o[2] = z;
+  }
+  static __device__ __forceinline__ void border(const Tail&, const State& st, double (&t)[2]) {
+    if (PER) t[0] = st.sy / (1.0 + st.sz);
+  }
+  static __device__ __forceinline__ double free(const double (&o)[kOut], const double (&t)[2]) {
+    if constexpr (PER) return o[0] - t[0] * o[2];
+    return o[0];
+  }
+  static __device__ __forceinline__ double back(double v, double ch, double, double x1, double) {
+    return v - ch * x1;
+  }
+  static __device__ __forceinline__ void finish(int, long, int, const double (&)[2], double*) {}
+  static __device__ __forceinline__ void save(const State& st, double (&k)[kState]) {
+    k[0] = st.ch1, k[1] = st.y1;
+    if constexpr (PER) k[2] = st.z1;
+  }
+  static __device__ __forceinline__ void restore(const double (&k)[kState], State& st) {
+    st.ch1 = k[0], st.y1 = k[1];
+    if constexpr (PER) st.z1 = k[2];
+  }
+};
+
+// The bands in order, then the right-hand sides.
+template <int Q>
+struct Columns {
+  const double* p[Q];
+};
+
+// U rows of Q arrays, from row i on; rows past the last are its copies, and
+// groups past it one element of it.
+template <int U, int Q>
+struct Group {
+  double v[U][Q];
+  __device__ __forceinline__ void load(const double* const* p, int i, int last, long ld,
+                                       int lane) {
+    const unsigned off = i <= last ? 8u * lane : 0u;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const long r = (long)min(max(i + u, 0), last) * ld;
+#pragma unroll
+      for (int j = 0; j < Q; ++j)
+        v[u][j] = __builtin_nontemporal_load(reinterpret_cast<const double*>(
+            reinterpret_cast<const char*>(p[j] + r) + off));
+    }
+  }
+};
+
+template <class S, bool SUMS, int U, class F>
+__device__ __forceinline__ void sweep_group(int i, int m, const Group<U, S::kBands + 1>& g,
+                                            const typename S::Tail& tl, typename S::State& st,
+                                            const F& f) {
+  double o[S::kOut];
+  if (i >= S::kEdge && i + U <= m - S::kEdge) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      S::template row<false, SUMS>(i + u, m, g.v[u], tl, st, o);
+      f(u, o);
+    }
+  } else {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (i + u < m) {
+        S::template row<true, SUMS>(i + u, m, g.v[u], tl, st, o);
+        f(u, o);
+      }
+  }
+}
+
+// Kept factors: the forward sweep leaves its values in x and the workspace,
+// the back sweep reads them.  Systems that are not periodic only: of the
+// others' factors more would have to be kept, and at no size did that win.
+template <class S, int U>
+__global__ __launch_bounds__(kWave, 1) void rewrite_once_k(int n, int batch, long ld,
+                                                           Columns<S::kBands + 1> in, double* x,
+                                                           double* ws, long ldw) {
+  static_assert(!S::kPeriodic);
+  const long s0 = (long)blockIdx.x * kWave;
+  const int lane = threadIdx.x;
+  if (s0 + lane >= batch) return;
+  const int m = S::rows(n);
+  const typename S::Tail tl{};
+#pragma unroll
+  for (int j = 0; j <= S::kBands; ++j) in.p[j] += s0;
+  x += s0;
+  ws += s0;
+  typename S::State st;
+  {
+    Group<U, S::kBands + 1> A, B;
+    const auto put = [&](int i) {
+      return [=](int u, const double (&o)[S::kOut]) {
+        x[(long)(i + u) * ld + lane] = o[0];
+#pragma unroll
+        for (int j = 1; j < S::kOut; ++j) ws[((long)(j - 1) * m + i + u) * ldw + lane] = o[j];
+      };
+    };
+    A.load(in.p, 0, m - 1, ld, lane);
+    for (int i = 0; i < m; i += 2 * U) {
+      B.load(in.p, i + U, m - 1, ld, lane);
+      sweep_group<S, false, U>(i, m, A, tl, st, put(i));
+      A.load(in.p, i + 2 * U, m - 1, ld, lane);
+      sweep_group<S, false, U>(i + U, m, B, tl, st, put(i + U));
+    }
+  }
+  double x1 = 0.0, x2 = 0.0;
+  struct Way {
+    double v[U][S::kOut];
+  };
+  const auto get = [&](int i, Way& g) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int r = max(i - u, 0);
+      g.v[u][0] = __builtin_nontemporal_load(x + (long)r * ld + lane);
+#pragma unroll
+      for (int j = 1; j < S::kOut; ++j)
+        g.v[u][j] = __builtin_nontemporal_load(ws + ((long)(j - 1) * m + r) * ldw + lane);
+    }
+  };
+  const auto back = [&](int i, const Way& g) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (i - u >= 0) {
+        const double v = S::back(g.v[u][0], g.v[u][1], S::kBack > 1 ? g.v[u][2] : 0.0, x1, x2);
+        x[(long)(i - u) * ld + lane] = v;
+        x2 = x1;
+        x1 = v;
+      }
+  };
+  Way A, B;
+  get(m - 1, A);
+  for (int i = m - 1; i >= 0; i -= 2 * U) {
+    get(i - U, B);
+    back(i, A);
+    get(i - 2 * U, A);
+    back(i - U, B);
+  }
+}
+
+// Factors computed twice: the forward sweep stores only its state before
+// every block of U * SUB rows; the way back takes the blocks in reverse,
+// factors each again from its state and substitutes.  All groups of a block
+// but the last wait for the substitution in LDS: 36 KB a wave for 32 rows of
+// the pentadiagonal, so that four waves, one per SIMD, fit a CU.  The result
+// is stored past the caches: 1024 x 65536 takes 1.26 ms against 1.33.
+template <class S, int U, int SUB>
+__global__ __launch_bounds__(kWave, 1) void rewrite_twice_k(int n, int batch, long ld,
+                                                            Columns<S::kBands + 1> in, double* x,
+                                                            double* ws, long ldw) {
+  static_assert(SUB % 2 == 0, "groups alternate between two sets of registers");
+  constexpr int kBlock = U * SUB, kVal = 1 + S::kBack;
+  __shared__ double rows[(SUB - 1) * U][kVal][kWave];
+  const long s0 = (long)blockIdx.x * kWave;
+  const int lane = threadIdx.x;
+  if (s0 + lane >= batch) return;
+  const int m = S::rows(n);
+  typename S::Tail tl{};
+  S::tail(n, ld, s0 + lane, in.p, tl);
+#pragma unroll
+  for (int j = 0; j <= S::kBands; ++j) in.p[j] += s0;
+  x += s0;
+  ws += s0;
+  const int nb = (m + kBlock - 1) / kBlock;
+  typename S::State st;
+  Group<U, S::kBands + 1> A, B;
+  double kept[S::kState];
+  A.load(in.p, 0, m - 1, ld, lane);
+  for (int k = 0; k < nb; ++k) {
+    if (k > 0) {
+      S::save(st, kept);
+#pragma unroll
+      for (int j = 0; j < S::kState; ++j)
+        ws[((long)(k - 1) * S::kState + j) * ldw + lane] = kept[j];
+    }
+#pragma unroll
+    for (int g = 0; g < SUB; ++g) {
+      const int i = k * kBlock + g * U;
+      ((g & 1) ? A : B).load(in.p, i + U, m - 1, ld, lane);
+      sweep_group<S, true, U>(i, m, (g & 1) ? B : A, tl, st,
+                              [](int, const double (&)[S::kOut]) {});
+    }
+  }
+  double t[2] = {0.0, 0.0};
+  S::border(tl, st, t);
+
+  double x1 = 0.0, x2 = 0.0;
+  const auto fetch = [&](int k) {
+#pragma unroll
+    for (int j = 0; j < S::kState; ++j)
+      kept[j] = k > 0 ? __builtin_nontemporal_load(
+                            ws + ((long)(k - 1) * S::kState + j) * ldw + lane)
+                      : 0.0;
+  };
+  fetch(nb - 1);
+  A.load(in.p, (nb - 1) * kBlock, m - 1, ld, lane);
+  for (int k = nb - 1; k >= 0; --k) {
+    S::restore(kept, st);
+    double r[U][kVal];
+#pragma unroll
+    for (int g = 0; g < SUB; ++g) {
+      const int i = k * kBlock + g * U;
+      if (g == SUB - 1) fetch(k - 1);
+      ((g & 1) ? A : B).load(in.p, g < SUB - 1 ? i + U : (k - 1) * kBlock, m - 1, ld, lane);
+      sweep_group<S, false, U>(i, m, (g & 1) ? B : A, tl, st,
+                               [&](int u, const double (&o)[S::kOut]) {
+                                 r[u][0] = S::free(o, t);
+#pragma unroll
+                                 for (int j = 1; j < kVal; ++j) r[u][j] = o[j];
+                               });
+      if (g < SUB - 1) {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+          for (int j = 0; j < kVal; ++j) rows[g * U + u][j][lane] = r[u][j];
+      }
+    }
+#pragma unroll
+    for (int g = SUB - 1; g >= 0; --g) {
+      if (g < SUB - 1) {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+          for (int j = 0; j < kVal; ++j) r[u][j] = rows[g * U + u][j][lane];
+      }
+      const int i = k * kBlock + g * U;
+#pragma unroll
+      for (int u = U - 1; u >= 0; --u)
+        if (i + u < m) {
+          const double v = S::back(r[u][0], r[u][1], kVal > 2 ? r[u][2] : 0.0, x1, x2);
+          __builtin_nontemporal_store(v, x + (long)(i + u) * ld + lane);
+          x2 = x1;
+          x1 = v;
+        }
+    }
+  }
+  S::finish(n, ld, lane, t, x);
 }
 
 // ---------------------------------------------------------------------------
@@ -675,6 +908,42 @@ int check_ws(const void* ws, size_t ws_bytes, size_t need_doubles) {
 }
 
 dim3 grid_of(int batch) { return dim3((unsigned)((batch + kThreads - 1) / kThreads)); }
+
+// Which kernel (ms, FP64, against 1.72 penta and 1.05 tri at 1024 x 65536 for
+// kept factors without the double set of rows):
+//  - periodic: always twice.  1024 x 65536: penta 1.31, tri 0.84, against 1.72
+//    and 1.07 kept; 512 x 4096: 0.161 and 0.114 against 0.180 and 0.128.
+//  - not periodic: twice only where the batch streams from memory, 0.317
+//    against 0.349 (penta) and 0.216 against 0.297 (tri) at 1024 x 16384;
+//    kept below, 0.133 against 0.135 and 0.107 against 0.107 at 512 x 4096,
+//    and for short systems, whose factors stay in the last-level cache
+//    (100 x 65536: 0.108 against 0.124, 0.076 against 0.078).
+//  - groups of 4 rows for the pentadiagonal below half a wave per SIMD, where
+//    the smaller kernel keeps clear of the accumulation registers (1024 x
+//    16384: 0.337 against 0.353), of 8 above (1024 x 65536: 1.31 against
+//    1.37); the tridiagonal fits at 8 (1024 x 16384: 0.228 against 0.264).
+constexpr int kTwiceBatch = 16384, kTwiceRows = 256, kWideBatch = 32768;
+
+template <class S>
+void rewrite(int n, int batch, long ld, const Columns<S::kBands + 1>& in, double* x, double* ws,
+             hipStream_t st) {
+  const dim3 grid((unsigned)((batch + kWave - 1) / kWave));
+  const long ldw = ws_ld(batch);
+  if constexpr (!S::kPeriodic)
+    if (batch < kTwiceBatch || n < kTwiceRows) {
+      hipLaunchKernelGGL((rewrite_once_k<S, 4>), grid, dim3(kWave), 0, st, n, batch, ld, in, x, ws,
+                         ldw);
+      return;
+    }
+  if constexpr (S::kBands == 5)
+    if (batch < kWideBatch) {
+      hipLaunchKernelGGL((rewrite_twice_k<S, 4, 4>), grid, dim3(kWave), 0, st, n, batch, ld, in, x,
+                         ws, ldw);
+      return;
+    }
+  hipLaunchKernelGGL((rewrite_twice_k<S, 8, 4>), grid, dim3(kWave), 0, st, n, batch, ld, in, x, ws,
+                     ldw);
+}
 
 int launched() { return hipGetLastError() == hipSuccess ? CHX_OK : CHX_EHIP; }
 
@@ -721,15 +990,13 @@ size_t vb_rewrite_ws_bytes(int P, int n, int batch) {
 
 hipError_t vb_penta_rewrite_periodic(int n, int batch, const double* const* b, long ld, double* x,
                                      double* ws, hipStream_t st) {
-  hipLaunchKernelGGL(penta_batch_rewrite_k<true>, grid_of(batch), dim3(kThreads), 0, st, n, batch,
-                     ld, b[0], b[1], b[2], b[3], b[4], x, ws, ws_ld(batch));
+  rewrite<Penta<true>>(n, batch, ld, {b[0], b[1], b[2], b[3], b[4], x}, x, ws, st);
   return hipGetLastError();
 }
 
 hipError_t vb_tri_rewrite_periodic(int n, int batch, const double* const* b, long ld, double* x,
                                    double* ws, hipStream_t st) {
-  hipLaunchKernelGGL(tri_batch_rewrite_k<true>, grid_of(batch), dim3(kThreads), 0, st, n, batch,
-                     ld, b[0], b[1], b[2], x, ws, ws_ld(batch));
+  rewrite<Tri<true>>(n, batch, ld, {b[0], b[1], b[2], x}, x, ws, st);
   return hipGetLastError();
 }
 
@@ -800,11 +1067,9 @@ int penta_batch_rewrite(int n, int batch, int periodic, const double* a, const d
   hipStream_t st = static_cast<hipStream_t>(s);
   double* w = static_cast<double*>(ws);
   if (periodic)
-    hipLaunchKernelGGL(penta_batch_rewrite_k<true>, grid_of(batch), dim3(kThreads), 0, st, n,
-                       batch, ld, a, b, c, d, e, x, w, ws_ld(batch));
+    rewrite<Penta<true>>(n, batch, ld, {a, b, c, d, e, x}, x, w, st);
   else
-    hipLaunchKernelGGL(penta_batch_rewrite_k<false>, grid_of(batch), dim3(kThreads), 0, st, n,
-                       batch, ld, a, b, c, d, e, x, w, ws_ld(batch));
+    rewrite<Penta<false>>(n, batch, ld, {a, b, c, d, e, x}, x, w, st);
   return launched();
 }
 
@@ -859,11 +1124,9 @@ int tri_batch_rewrite(int n, int batch, int periodic, const double* a, const dou
   hipStream_t st = static_cast<hipStream_t>(s);
   double* w = static_cast<double*>(ws);
   if (periodic)
-    hipLaunchKernelGGL(tri_batch_rewrite_k<true>, grid_of(batch), dim3(kThreads), 0, st, n, batch,
-                       ld, a, b, c, x, w, ws_ld(batch));
+    rewrite<Tri<true>>(n, batch, ld, {a, b, c, x}, x, w, st);
   else
-    hipLaunchKernelGGL(tri_batch_rewrite_k<false>, grid_of(batch), dim3(kThreads), 0, st, n,
-                       batch, ld, a, b, c, x, w, ws_ld(batch));
+    rewrite<Tri<false>>(n, batch, ld, {a, b, c, x}, x, w, st);
   return launched();
 }
 

@@ -221,3 +221,30 @@ def test_penta_rewrite_argument_errors_leave_the_arrays_untouched(chx, orc):
     torch.cuda.synchronize()
     ref = orc.penta_rows_batch(*host, True)
     assert _err(x.cpu().numpy(), ref) < 1e-12
+
+
+# Rewrites at the edges of their groups of 4 and 8 rows and their blocks of 16
+# and 32 (a periodic pentadiagonal system's sweep has n - 2 rows), and on both
+# sides of the batches and lengths at which the kernel changes.  Each system
+# is one of 97: the answer of the others is a repeated one.
+EDGES = [(n, 65, per) for n in (9, 10, 11, 17, 18, 19, 33, 34, 35, 50, 65, 66) for per in
+         (False, True)] + [(n, b, False) for n in (255, 256) for b in (16383, 16384)] + \
+        [(35, b, True) for b in (32767, 32768)] + [(290, 32768, False)]
+
+
+@pytest.mark.parametrize("n,batch,periodic", EDGES)
+def test_rewrite_at_group_block_and_batch_edges(chx, orc, n, batch, periodic):
+    print(f"[rewrite edges] n={n} batch={batch} periodic={periodic}", flush=True)
+    pick = np.arange(batch) % min(batch, 97)
+    for P, rows, solve, rewrite in ((2, _penta_system, orc.penta_rows_batch,
+                                     chx.penta_batch_rewrite),
+                                    (1, _tri_system, orc.tri_rows_batch, chx.tri_batch_rewrite)):
+        few = rows(n, min(batch, 97), 7 * n + P)
+        ref = solve(*few, periodic)
+        *A, x = [_dev(np.ascontiguousarray(v[:, pick]), batch + 1) for v in few]
+        rewrite(*A, x, periodic=periodic, batch=batch)
+        torch.cuda.synchronize()
+        assert torch.isnan(x[:, batch:]).all()
+        xr = x[:, :batch].cpu().numpy()
+        assert _err(xr[:, :ref.shape[1]], ref) < 1e-12
+        assert np.array_equal(xr, xr[:, pick])
