@@ -253,6 +253,38 @@ def test_stencil_parity_f32(chx, orc, shape, ext, periodic, premap):
     assert np.all(err <= bound), float(np.max(err / bound))
 
 
+# Rows that are whole 16-byte vectors (2 FP64 or 4 FP32 columns) and rows that
+# are not, around the 64 vectors of a tile; fields as wide as the reach, and
+# fields that start off a vector's boundary.
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("nx,ny,offset", [(4, 4, 0), (8, 15, 0), (64, 16, 0), (66, 17, 0),
+                                          (126, 33, 0), (128, 16, 1), (128, 31, 0), (130, 32, 0),
+                                          (252, 18, 0), (256, 16, 1), (256, 17, 0), (260, 47, 0),
+                                          (261, 16, 0)])
+def test_stencil_vectors_and_single_columns(chx, orc, nx, ny, offset, dtype):
+    T, eps = (torch.float64, 2.0 ** -53) if dtype == "f64" else (torch.float32, 2.0 ** -24)
+    x = torch.tensor(inputs.uniform(16, (ny, nx), -1, 1)).to(T)
+    for ext in ((1, 1, 1, 1), (4, 0, 2, 4), (2, 3, 0, 0)):
+        left, right, top, bottom = ext
+        w = torch.tensor(inputs.uniform(17, ((top + bottom + 1) * (left + right + 1),), -1, 1)).to(T)
+        W = w.double().numpy().reshape(top + bottom + 1, left + right + 1)
+        for periodic in (True, False):
+            print(f"[case] stencil {dtype} {nx}x{ny} ext={ext} periodic={periodic}", flush=True)
+            bufs = [torch.full((ny * nx + 5,), 3.5, dtype=T, device="cuda") for _ in range(2)]
+            xin, xo = [b[offset:offset + ny * nx].view(ny, nx) for b in bufs]
+            xin.copy_(x)
+            chx.stencil2d_apply(xin, xo, w.tolist(), left, right, top, bottom, periodic=periodic)
+            torch.cuda.synchronize()
+            ref = orc.stencil2d(x.double().numpy(), W, left, right, top, bottom,
+                                periodic=periodic, out=np.full((ny, nx), 3.5))
+            mag = orc.stencil2d(np.abs(x.double().numpy()), np.abs(W), left, right, top, bottom,
+                                periodic=periodic, out=np.zeros((ny, nx)))
+            err = np.abs(xo.double().cpu().numpy() - ref)
+            assert np.all(err <= 2 * (W.size + 1) * eps * mag + 1e-300)
+            rest = torch.cat([bufs[1][:offset], bufs[1][offset + ny * nx:]])
+            assert torch.all(rest == 3.5)
+
+
 @pytest.mark.parametrize("ext,premap", [((1, 1, 1, 1), 1), ((2, 2, 2, 2), 0), ((4, 4, 4, 4), 0),
                                          ((3, 0, 4, 1), 1)])
 def test_stencil_full_size_sampled(chx, orc, ext, premap):
