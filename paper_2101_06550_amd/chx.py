@@ -879,17 +879,14 @@ def _ens_fields(e: Ensemble, fields):
     if len(fields) != e.nruns:
         raise ChxError(CHX_EINVAL, "one field per run")
     f64 = _th().float64
-    ptrs, lds = [], []
-    for r, (f, shape) in enumerate(zip(fields, e.shapes)):
-        nx, ny = shape
-        # a plain contiguous field needs none of the general checks
-        if not (getattr(f, "is_cuda", False) and f.dtype is f64 and f.is_contiguous() and
-                f.shape == (ny, nx)):
-            lds.append(_field_ld(f, nx, ny, None, f"field {r}"))
-            ptrs.append(_devptr(f, f"field {r}"))
-        else:
-            lds.append(nx)
-            ptrs.append(f.data_ptr())
+    plain = [getattr(f, "is_cuda", False) and f.dtype is f64 and f.is_contiguous() and
+             f.shape == (ny, nx) for f, (nx, ny) in zip(fields, e.shapes)]
+    # a plain contiguous field needs none of the general checks; every field's
+    # shape is looked at before any field's device and type
+    lds = [nx if ok else _field_ld(f, nx, ny, None, f"field {r}")
+           for r, (f, (nx, ny), ok) in enumerate(zip(fields, e.shapes, plain))]
+    ptrs = [f.data_ptr() if ok else _devptr(f, f"field {r}")
+            for r, (f, ok) in enumerate(zip(fields, plain))]
     return (ctypes.c_void_p * e.nruns)(*ptrs), (ctypes.c_long * e.nruns)(*lds)
 
 
