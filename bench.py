@@ -324,8 +324,8 @@ def solve_throughput(chx, torch, reps=10):
     n, batch, a = 1024, 131072, 0.5
     plan = chx.penta_factor(n, a, -4 * a, 1 + 6 * a, -4 * a, a)
     out = {}
-    for name, layout, shape, bpu in (("interleaved", 0, (n, batch), None),
-                                     ("contiguous", 1, (batch, n), 16)):
+    bpu = 16  # either layout: one launch that reads f and writes x
+    for name, layout, shape in (("interleaved", 0, (n, batch)), ("contiguous", 1, (batch, n))):
         x = torch.tensor(inputs.uniform(2, shape, -1, 1), device="cuda")
         ws = torch.empty(chx.penta_solve_ws_bytes(plan, batch, layout) + 256, dtype=torch.uint8,
                          device="cuda")
@@ -338,12 +338,6 @@ def solve_throughput(chx, torch, reps=10):
         e1.record()
         torch.cuda.synchronize()
         ms = e0.elapsed_time(e1) / reps
-        if bpu is None:
-            # first pass (read f, write 4 separator parts per chunk) + separators
-            # + second pass (read the interior of f and the separators of the
-            # chunk and its predecessor, write the interior of x)
-            mi = CHUNK - 2
-            bpu = (8 + 32 / CHUNK) + (32 + 16) / CHUNK + (2 * 8 * mi / CHUNK + 32 / CHUNK)
         gbs = bpu * n * batch / (ms * 1e-3) / 1e9
         out[name] = {"systems": batch, "n": n, "ms_per_solve_batch": round(ms, 4),
                      "solves_per_s": batch / (ms * 1e-3),
@@ -362,9 +356,9 @@ def per_system_throughput(chx, torch, reps=10):
     dt = 1e-8, n = 1024, 65536 systems, each stored with its own diagonals),
     in the factor-once mode and in the Rewrite mode (factor and solve at every
     call); the tridiagonal analogue with beta = 0.5.  Algorithmic bytes: the
-    accesses a one-thread-per-system two-pass solve must make per unknown
-    (periodic penta: rewrite 17, solve 13; tri: rewrite 11, solve 9; 8 B
-    each)."""
+    accesses of the kernels per unknown, 8 B each (periodic penta: rewrite 13
+    and the sweep's state of 10 values written and read every 32 rows, solve
+    13; tri: rewrite 9 and 3 values, solve 9)."""
     from paper_2101_06550_amd import inputs
     n, batch = 1024, 65536
     sig = 1e-8 / (2 * (1.0 / n) ** 4)
@@ -394,7 +388,7 @@ def per_system_throughput(chx, torch, reps=10):
     x = f.clone()
     ws = torch.empty(chx.penta_batch_ws_bytes(n, batch, True, chx.CHX_BATCH_REWRITE) + 256,
                      dtype=torch.uint8, device="cuda")
-    out["penta_rewrite"] = entry(timed(lambda: chx.penta_batch_rewrite(*diag, x, ws=ws)), 17)
+    out["penta_rewrite"] = entry(timed(lambda: chx.penta_batch_rewrite(*diag, x, ws=ws)), 13.625)
     del ws
     fws = chx.penta_batch_factor(*diag)
     out["penta_solve_factored"] = entry(
@@ -403,7 +397,7 @@ def per_system_throughput(chx, torch, reps=10):
     tri = [torch.full((n, batch), v, **dev) for v in (-0.5, 2.0, -0.5)]
     ws = torch.empty(chx.tri_batch_ws_bytes(n, batch, True, chx.CHX_BATCH_REWRITE) + 256,
                      dtype=torch.uint8, device="cuda")
-    out["tri_rewrite"] = entry(timed(lambda: chx.tri_batch_rewrite(*tri, x, ws=ws)), 11)
+    out["tri_rewrite"] = entry(timed(lambda: chx.tri_batch_rewrite(*tri, x, ws=ws)), 9.1875)
     del ws
     fws = chx.tri_batch_factor(*tri)
     out["tri_solve_factored"] = entry(timed(lambda: chx.tri_batch_solve(*tri, x, ws=fws)), 9)
@@ -660,10 +654,9 @@ def batch1d_run(chx, torch):
     """Batched 1D periodic schemes: the 1D Cahn-Hilliard batch of the thesis's
     coarsening statistics (2^20 systems of N = 256 on (0, 2 pi), gamma = 0.01,
     dt = 0.1 dx, U[-0.1, 0.1], Ch.6-7) and Crank-Nicolson hyperdiffusion
-    (65536 systems of N = 1024, dt = 1e-12, the Ch.4 scheme); FP64, 100 steps;
-    algorithmic traffic 18 B per unknown per step (sweep: read the state,
-    write the chunk interior and 4 parts per 32 unknowns; separators: 1.5 B),
-    the correction deferred into the next sweep."""
+    (65536 systems of N = 1024, dt = 1e-12, the Ch.4 scheme); FP64, 100 steps
+    in one call; algorithmic traffic 16 B per unknown and call (the state is
+    read and written once and stays in registers between the steps)."""
     from paper_2101_06550_amd import inputs
     out = {}
     for name, kind, n, batch, L, dt, a in (
@@ -681,12 +674,12 @@ def batch1d_run(chx, torch):
         el = time.perf_counter() - t0
         out[name] = {"steps": k, "ms_per_step": round(1e3 * el / k, 5),
                      "system_steps_per_s": batch * k / el,
-                     "algorithmic_GBps": round(18.0 * n * batch * k / el / 1e9, 1),
+                     "algorithmic_GBps": round(16.0 * n * batch / el / 1e9, 1),
                      "finite": bool(torch.isfinite(x).all())}
         if kind == 0:
             # the thesis's Rewrite mode on the same batch: diagonals written and
-            # every system factored and solved afresh each step; 192 B per unknown
-            # (right-hand side 16, five bands 40, fused factor-and-solve 136)
+            # every system factored and solved afresh each step; 165 B per unknown
+            # (right-hand side 16, five bands 40, fused factor-and-solve 109)
             ws = chx.batch1d_step_rewrite(b, x, nsteps=2)
             torch.cuda.synchronize()
             kr = 20
@@ -696,7 +689,7 @@ def batch1d_run(chx, torch):
             el = time.perf_counter() - t0
             out[name + "_rewrite"] = {"steps": kr, "ms_per_step": round(1e3 * el / kr, 5),
                                       "system_steps_per_s": batch * kr / el,
-                                      "algorithmic_GBps": round(192.0 * n * batch * kr / el / 1e9, 1),
+                                      "algorithmic_GBps": round(165.0 * n * batch * kr / el / 1e9, 1),
                                       "finite": bool(torch.isfinite(x).all())}
             del ws
         del x, b

@@ -518,8 +518,9 @@ int ch_k1(chx_ch h, const double* c, long ld, double* k1, chx_stream s);
  *   CHX_SCHEME_P1 and one dtype.  CHX_F64: nx % 64 == 0, ny % 32 == 0,
  *   nx <= 8192, at most 8 distinct (grid, D, gamma, dt) classes; ensembles
  *   solve with 32-point chunks, so a run advances bitwise as a single
- *   handle whose CHX_TUNE_COLUMN_CHUNK and CHX_TUNE_ROW_CHUNK are 32 would
- *   (to rounding as one tuned to 16).
+ *   handle whose CHX_TUNE_COLUMN_CHUNK and CHX_TUNE_ROW_CHUNK have been set
+ *   to 32 would (to rounding as one that steps by two launches or is tuned
+ *   to 16).
  *   CHX_F32_REFINED (the precision pattern of ch_create's refined step):
  *   each run as ch_create accepts it (refine_passes may differ between
  *   runs), at most 8 distinct (grid, D, gamma, dt) classes; every phase of
