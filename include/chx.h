@@ -432,8 +432,8 @@ int ch_adi_step_timed(chx_ch h, double* c_inout, long ld, int nsteps,
  *   rounding: results agree to rounding, not bitwise.
  * ch_get_tuning: *value = the current choice of `what`.
  * ch_set_tuning: set it from now on; CHX_EINVAL for a NULL handle, an unknown
- *   `what` or a value out of range.  Not to be called while work of h is
- *   queued on a stream that is being captured. */
+ *   `what` or a value out of range, and then no choice changes.  Not to be
+ *   called while work of h is queued on a stream that is being captured. */
 #define CHX_TUNE_REDUCED_SHAPE 0
 #define CHX_TUNE_SMALL_PATH 1
 #define CHX_TUNE_ROW_SPLIT 2

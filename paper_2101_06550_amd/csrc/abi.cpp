@@ -1602,51 +1602,43 @@ int ch_get_tuning(chx_ch h, int what, int* value) {
   }
 }
 
-int ch_set_tuning(chx_ch h, int what, int value) {
-  if (!h) return CHX_EINVAL;
-  h->drop_graph();  // a captured call holds the old choices
-  if (what != CHX_TUNE_GRAPH && h->fast) h->pair = false;
+// Whether h takes the value for the choice.
+static bool tuning_fits(const chx_ch_s* h, int what, int value) {
   switch (what) {
-    case CHX_TUNE_GRAPH:
-      if (value != 0 && value != 1) return CHX_EINVAL;
-      h->use_graph = value == 1;
-      return CHX_OK;
-    case CHX_TUNE_REDUCED_SHAPE:
-      if (value < 0 || value >= kNumRedShapes) return CHX_EINVAL;
-      h->py->dchunk.red_shape = value;
-      return CHX_OK;
-    case CHX_TUNE_SMALL_PATH:
-      if (value != 0 && (value != 1 || !h->small_ok)) return CHX_EINVAL;
-      h->small = value == 1;
-      return CHX_OK;
+    case CHX_TUNE_GRAPH: return value == 0 || value == 1;
+    case CHX_TUNE_REDUCED_SHAPE: return value >= 0 && value < kNumRedShapes;
+    case CHX_TUNE_SMALL_PATH: return value == 0 || (value == 1 && h->small_ok);
     case CHX_TUNE_ROW_SPLIT:
       // the fused split forms are forms of the 32-point chunks; the
       // overlapped order takes either length
-      if (value >= 0 && (h->mcol != kChunk || h->mrow != kChunk)) return CHX_EINVAL;
-      if (value == kSplitOverlap) {
-        if (!h->side) return CHX_EINVAL;
-      } else if (value != -1 && !(h->fast && h->prm.dtype == CHX_F64 &&
-                                  split_fits(h->py->dchunk, h->px->dchunk, value))) {
-        return CHX_EINVAL;
-      }
-      h->split = value;
-      return CHX_OK;
+      if (value >= 0 && (h->mcol != kChunk || h->mrow != kChunk)) return false;
+      if (value == kSplitOverlap) return h->side != nullptr;
+      return value == -1 || (h->fast && h->prm.dtype == CHX_F64 &&
+                             split_fits(h->py->dchunk, h->px->dchunk, value));
     case CHX_TUNE_COLUMN_CHUNK:
-      if (value != kChunk && !(value == 16 && h->fast && h->py->has_chunk16)) return CHX_EINVAL;
-      if (value != kChunk && h->split >= 0) return CHX_EINVAL;
-      h->mcol = value;
-      return CHX_OK;
+      return value == kChunk ||
+             (value == 16 && h->fast && h->py->has_chunk16 && h->split < 0);
     case CHX_TUNE_ROW_CHUNK:
-      if (value != kChunk && !(value == 16 && h->fast && rows16_fit(h->px))) return CHX_EINVAL;
-      if (value != kChunk && h->split >= 0) return CHX_EINVAL;
-      h->mrow = value;
-      return CHX_OK;
-    case CHX_TUNE_COLUMN_ORDER:
-      if (value < 0 || value >= CHX_NUM_COLUMN_ORDERS) return CHX_EINVAL;
-      h->col_order = value;
-      return CHX_OK;
-    default: return CHX_EINVAL;
+      return value == kChunk || (value == 16 && h->fast && rows16_fit(h->px) && h->split < 0);
+    case CHX_TUNE_COLUMN_ORDER: return value >= 0 && value < CHX_NUM_COLUMN_ORDERS;
+    default: return false;
   }
+}
+
+int ch_set_tuning(chx_ch h, int what, int value) {
+  if (!h || !tuning_fits(h, what, value)) return CHX_EINVAL;
+  h->drop_graph();  // a captured call holds the old choices
+  if (what != CHX_TUNE_GRAPH && h->fast) h->pair = false;
+  switch (what) {
+    case CHX_TUNE_GRAPH: h->use_graph = value == 1; break;
+    case CHX_TUNE_REDUCED_SHAPE: h->py->dchunk.red_shape = value; break;
+    case CHX_TUNE_SMALL_PATH: h->small = value == 1; break;
+    case CHX_TUNE_ROW_SPLIT: h->split = value; break;
+    case CHX_TUNE_COLUMN_CHUNK: h->mcol = value; break;
+    case CHX_TUNE_ROW_CHUNK: h->mrow = value; break;
+    case CHX_TUNE_COLUMN_ORDER: h->col_order = value; break;
+  }
+  return CHX_OK;
 }
 
 int ch_destroy(chx_ch h) {
