@@ -546,8 +546,10 @@ def small_run(chx, torch, steps=1000):
     out = {"points": n * n, "steps": steps}
     h = chx.ch_create(n, n, L, L, 1.0, 0.01, 1e-4)
     res = {}
-    for name, small in (("single_workgroup_lds", 1), ("multi_kernel", 0)):
-        chx.ch_set_tuning(h, small, what=chx.CHX_TUNE_SMALL_PATH)
+    for name, what, value in (("two_launches", chx.CHX_TUNE_TWO_LAUNCH, 1),
+                              ("single_workgroup_lds", chx.CHX_TUNE_SMALL_PATH, 1),
+                              ("multi_kernel", chx.CHX_TUNE_SMALL_PATH, 0)):
+        chx.ch_set_tuning(h, value, what=what)
         c = torch.tensor(c0, device="cuda")
         chx.ch_adi_step(h, c, nsteps=10)
         torch.cuda.synchronize()

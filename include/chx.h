@@ -361,17 +361,24 @@ int ch_adi_step_timed(chx_ch h, double* c_inout, long ld, int nsteps,
                       double* diag_out, void* ws, size_t ws_bytes, chx_stream s,
                       int sample_every, double* phase_ms, int* phase_launches);
 
-/* Kernel choices of the FP64 step (autotuning).  Unforced P1 handles of up to
- * 2^20 points and 1024 rows, and of any size that the chunked passes do not
- * take (as far as one workgroup holds a few of its columns), step by two
- * launches of their own: whole columns, then rows.  Setting any choice but
- * CHX_TUNE_GRAPH turns that off for a grid that the chunked passes take, and
- * the choices below then apply; the two agree to rounding.
+/* Kernel choices of the FP64 step (autotuning).
+ * CHX_TUNE_TWO_LAUNCH: 1, the default where a handle has it, makes unforced
+ *   steps two launches: whole columns, then rows, in chunks of 8, 16 or 32
+ *   points.  P1 handles have it up to 2^20 points and 1024 rows, and at any
+ *   size that the chunked passes do not take, as far as one workgroup holds a
+ *   few of the columns; P2 handles likewise, by a bound of their own.  While
+ *   it is 1 the other choices but CHX_TUNE_GRAPH are only kept; 0 makes the
+ *   handle step by them (a grid that the chunked passes do not take steps one
+ *   system to a thread then).  On a P1 grid that the chunked passes take,
+ *   setting any of the others sets it to 0: to put a handle back, set it to 1
+ *   last.  The two agree to rounding, not bitwise.  Setting 1 on a handle that
+ *   does not have it is CHX_EINVAL.
  * CHX_TUNE_SMALL_PATH: grids with nx % 64 == 0, ny % 32 == 0, nx ny <= 16384
  *   and an LDS footprint of 9.25 bytes per point (151.5 KB at 128 x 128) that
- *   the device's per-workgroup LDS holds run every step of a call in ONE
+ *   the device's per-workgroup LDS holds can run every step of a call in ONE
  *   workgroup with the field resident in LDS (value 1, the default where it
- *   fits); value 0 selects the multi-kernel path.  The two paths apply the
+ *   fits: forced steps, and unforced ones with CHX_TUNE_TWO_LAUNCH 0); value 0
+ *   selects the multi-kernel path.  The two paths apply the
  *   column correction at different times and agree to rounding, not bit for
  *   bit.  Setting 1 where it does not fit is CHX_EINVAL.
  * CHX_TUNE_REDUCED_SHAPE: tile shape of the multi-kernel path's column
@@ -445,6 +452,7 @@ int ch_adi_step_timed(chx_ch h, double* c_inout, long ld, int nsteps,
 #define CHX_TUNE_GRAPH 4
 #define CHX_TUNE_COLUMN_CHUNK 5
 #define CHX_TUNE_ROW_CHUNK 6
+#define CHX_TUNE_TWO_LAUNCH 7
 int ch_get_tuning(chx_ch h, int what, int* value);
 int ch_set_tuning(chx_ch h, int what, int value);
 
@@ -518,9 +526,8 @@ int ch_k1(chx_ch h, const double* c, long ld, double* k1, chx_stream s);
  *   CHX_SCHEME_P1 and one dtype.  CHX_F64: nx % 64 == 0, ny % 32 == 0,
  *   nx <= 8192, at most 8 distinct (grid, D, gamma, dt) classes; ensembles
  *   solve with 32-point chunks, so a run advances bitwise as a single
- *   handle whose CHX_TUNE_COLUMN_CHUNK and CHX_TUNE_ROW_CHUNK have been set
- *   to 32 would (to rounding as one that steps by two launches or is tuned
- *   to 16).
+ *   handle whose CHX_TUNE_COLUMN_CHUNK and CHX_TUNE_ROW_CHUNK are 32 and
+ *   whose CHX_TUNE_TWO_LAUNCH is 0 would (to rounding as any other).
  *   CHX_F32_REFINED (the precision pattern of ch_create's refined step):
  *   each run as ch_create accepts it (refine_passes may differ between
  *   runs), at most 8 distinct (grid, D, gamma, dt) classes; every phase of

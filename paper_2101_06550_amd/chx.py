@@ -694,11 +694,12 @@ CHX_TUNE_GRAPH = 4
 CHX_NUM_ENS_REDUCED_SHAPES = 4
 CHX_TUNE_COLUMN_CHUNK = 5
 CHX_TUNE_ROW_CHUNK = 6
+CHX_TUNE_TWO_LAUNCH = 7
 
 
 def ch_get_tuning(h: CH, what: int = CHX_TUNE_REDUCED_SHAPE) -> int:
     """Current kernel choice `what` of the handle (separator tile shape, or
-    1/0 for the single-workgroup small-grid path)."""
+    1/0 for the two-launch step and the single-workgroup small-grid path)."""
     v = ctypes.c_int()
     _check(load().ch_get_tuning(h.handle, int(what), ctypes.byref(v)), "ch_get_tuning")
     return v.value

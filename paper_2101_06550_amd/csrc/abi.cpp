@@ -385,8 +385,9 @@ struct chx_ch_s {
   bool fast = false;
   bool small_ok = false;  // the single-workgroup LDS-resident path fits
   bool small = false;     // ... and is in use
-  // two launches per step (whole columns, rows), each direction in this plan
-  // (the plans' ragged tables)
+  // two launches per step (whole columns, rows) from the plans' ragged tables:
+  // the handle has them, and steps so (CHX_TUNE_TWO_LAUNCH)
+  bool pair_ok = false;
   bool pair = false;
   int split = -1;         // split row pass shape (-1: plain separators + rows,
                           // kSplitOverlap: separators beside the interior rows)
@@ -1472,6 +1473,7 @@ int ch_create(const chx_ch_params* prm, chx_ch* out) {
   int rc = make_plan(2, q.nx, cxs, 1, &h->px, c16, pair_x);
   if (rc == CHX_OK) rc = make_plan(2, q.ny, cys, 1, &h->py, c16, pair_y);
   h->pair = h->pair && rc == CHX_OK && h->px->has_ragged && h->py->has_ragged;
+  h->pair_ok = h->pair;
   if (rc != CHX_OK) {
     delete h;
     return rc;
@@ -1598,6 +1600,7 @@ int ch_get_tuning(chx_ch h, int what, int* value) {
     case CHX_TUNE_GRAPH: *value = h->use_graph ? 1 : 0; return CHX_OK;
     case CHX_TUNE_COLUMN_CHUNK: *value = h->mcol; return CHX_OK;
     case CHX_TUNE_ROW_CHUNK: *value = h->mrow; return CHX_OK;
+    case CHX_TUNE_TWO_LAUNCH: *value = h->pair ? 1 : 0; return CHX_OK;
     default: return CHX_EINVAL;
   }
 }
@@ -1621,6 +1624,7 @@ static bool tuning_fits(const chx_ch_s* h, int what, int value) {
     case CHX_TUNE_ROW_CHUNK:
       return value == kChunk || (value == 16 && h->fast && rows16_fit(h->px) && h->split < 0);
     case CHX_TUNE_COLUMN_ORDER: return value >= 0 && value < CHX_NUM_COLUMN_ORDERS;
+    case CHX_TUNE_TWO_LAUNCH: return value == 0 || (value == 1 && h->pair_ok);
     default: return false;
   }
 }
@@ -1628,6 +1632,7 @@ static bool tuning_fits(const chx_ch_s* h, int what, int value) {
 int ch_set_tuning(chx_ch h, int what, int value) {
   if (!h || !tuning_fits(h, what, value)) return CHX_EINVAL;
   h->drop_graph();  // a captured call holds the old choices
+  // a choice of the chunked passes is for a handle to step by them
   if (what != CHX_TUNE_GRAPH && h->fast) h->pair = false;
   switch (what) {
     case CHX_TUNE_GRAPH: h->use_graph = value == 1; break;
@@ -1637,6 +1642,7 @@ int ch_set_tuning(chx_ch h, int what, int value) {
     case CHX_TUNE_COLUMN_CHUNK: h->mcol = value; break;
     case CHX_TUNE_ROW_CHUNK: h->mrow = value; break;
     case CHX_TUNE_COLUMN_ORDER: h->col_order = value; break;
+    case CHX_TUNE_TWO_LAUNCH: h->pair = value == 1; break;
   }
   return CHX_OK;
 }

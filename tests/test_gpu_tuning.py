@@ -48,3 +48,67 @@ def test_refused_choice_changes_nothing(chx, ny, nx):  # noqa: F811
         assert ei.value.status == chx.CHX_EINVAL, (what, value)
         assert [chx.ch_get_tuning(h, w) for w in whats] == before, (what, value)
         assert same(stepped(chx, h, c0), ref), (what, value)
+
+
+@pytest.mark.parametrize("ny,nx,scheme,two", [
+    (64, 64, 0, 1), (128, 128, 0, 1), (1024, 1024, 0, 1), (90, 203, 0, 1), (2048, 64, 0, 0),
+    (5, 130, 0, 0), (128, 128, 1, 1), (90, 203, 1, 1), (4096, 1024, 1, 0)])
+def test_two_launch_choice_is_read_cleared_and_restored(chx, ny, nx, scheme, two):  # noqa: F811
+    """CHX_TUNE_TWO_LAUNCH says how unforced steps run; 0 leaves the other
+    routes, to rounding; 1 brings the same bits back, and is refused where
+    the handle has no such route."""
+    c0, p0 = inputs.noise_field(ny, nx, 32), inputs.noise_field(ny, nx, 33)
+    h = chx.ch_create(nx, ny, L, L, 1.0, 0.01, 1e-6, scheme=scheme)
+    what = chx.CHX_TUNE_TWO_LAUNCH
+
+    def run():
+        if scheme == chx.CHX_SCHEME_P1:
+            return stepped(chx, h, c0)
+        c, p = torch.tensor(c0, device="cuda"), torch.tensor(p0, device="cuda")
+        chx.ch_adi_step_p2(h, c, p, nsteps=3)
+        torch.cuda.synchronize()
+        return c.cpu().numpy(), p.cpu().numpy()
+
+    print(f"[case] two-launch choice {ny}x{nx} scheme {scheme}", flush=True)
+    assert chx.ch_get_tuning(h, what) == two
+    ref = run()
+    chx.ch_set_tuning(h, 0, what=what)
+    assert chx.ch_get_tuning(h, what) == 0
+    other = run()
+    # three steps' solves to 20 eps (1 + 16 s); the thesis scheme doubles
+    # what it carries on in every step
+    s = 0.01 * 1e-6 / (L / max(nx, ny)) ** 4
+    tol = 3 * max(1e-12, 20 * np.finfo(float).eps * (1 + 16 * s)) * (8 if scheme else 1)
+    assert np.max(np.abs(other[0] - ref[0])) < tol * np.max(np.abs(ref[0]))
+    if two:
+        assert not np.array_equal(other[0], ref[0])  # another route did run
+        chx.ch_set_tuning(h, 1, what=what)
+        assert chx.ch_get_tuning(h, what) == 1
+        assert same(run(), ref)
+    else:
+        assert same(other, ref)
+        with pytest.raises(chx.ChxError):
+            chx.ch_set_tuning(h, 1, what=what)
+
+
+@pytest.mark.parametrize("ny,nx", [(128, 128), (256, 256), (64, 4096)])
+def test_choices_written_back_restore_the_steps(chx, ny, nx):  # noqa: F811
+    """Every choice read, changed and written back in the order of the
+    choices: the steps are bit for bit what they were."""
+    c0 = inputs.noise_field(ny, nx, 34)
+    h = chx.ch_create(nx, ny, L, L, 1.0, 0.01, 1e-6)
+    whats = range(chx.CHX_TUNE_REDUCED_SHAPE, chx.CHX_TUNE_TWO_LAUNCH + 1)
+    before = [chx.ch_get_tuning(h, w) for w in whats]
+    print(f"[case] choices written back {ny}x{nx}", flush=True)
+    ref = stepped(chx, h, c0)
+    chx.ch_set_tuning(h, 0, what=chx.CHX_TUNE_SMALL_PATH)
+    chx.ch_set_tuning(h, -1, what=chx.CHX_TUNE_ROW_SPLIT)
+    for w in (chx.CHX_TUNE_COLUMN_CHUNK, chx.CHX_TUNE_ROW_CHUNK):
+        chx.ch_set_tuning(h, 32, what=w)
+    assert chx.ch_get_tuning(h, chx.CHX_TUNE_TWO_LAUNCH) == 0
+    stepped(chx, h, c0)
+    split = chx.CHX_TUNE_ROW_SPLIT  # a fused split needs the chunks back first, and they its absence
+    for w in sorted(whats, key=lambda w: (w == chx.CHX_TUNE_TWO_LAUNCH, w == split)):
+        chx.ch_set_tuning(h, before[w], what=w)
+    assert [chx.ch_get_tuning(h, w) for w in whats] == before
+    assert same(stepped(chx, h, c0), ref)

@@ -425,3 +425,8 @@ def test_solve_binding_rejects_short_buffers():
     with pytest.raises(chx.ChxError, match="unit last stride"):
         chx.penta_solve_batch(P(), 10, torch.zeros((64, 40), dtype=torch.float64)[:, ::2],
                               ld=40)
+
+
+def test_two_launch_choice_matches_header():
+    m = re.search(r"#define\s+CHX_TUNE_TWO_LAUNCH\s+(\d+)", open(HEADER).read())
+    assert m and int(m.group(1)) == chx.CHX_TUNE_TWO_LAUNCH
