@@ -384,7 +384,7 @@ struct chx_ch_s {
   BandPlan* py = nullptr;  // columns: length ny, sigma_y
   bool fast = false;
   bool small_ok = false;  // the single-workgroup LDS-resident path fits
-  bool small = false;     // ... and is in use
+  bool small = false;     // ... and is chosen (forced steps; unforced ones without pair)
   // two launches per step (whole columns, rows) from the plans' ragged tables:
   // the handle has them, and steps so (CHX_TUNE_TWO_LAUNCH)
   bool pair_ok = false;
@@ -2097,8 +2097,9 @@ int ch_adi_step(chx_ch h, double* c, long ld, int nsteps, double* diag_out, void
                 size_t ws_bytes, chx_stream s) {
   hipStream_t st = static_cast<hipStream_t>(s);
   // forced handles draw new noise every call (host-side step counter) and
-  // the single-workgroup path is one launch already: both run eagerly
-  if (!h || !h->use_graph || h->sigma > 0 || h->small)
+  // the single-workgroup path, where it runs, is one launch already: both run
+  // eagerly
+  if (!h || !h->use_graph || h->sigma > 0 || (h->small && !h->pair))
     return run_steps(h, c, ld, nsteps, diag_out, ws, ws_bytes, st, nullptr);
   // the argument checks run_steps makes, before anything is captured
   if (!c || h->prm.scheme != CHX_SCHEME_P1 || ld < h->prm.nx || nsteps < 1) return CHX_EINVAL;

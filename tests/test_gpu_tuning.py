@@ -112,3 +112,50 @@ def test_choices_written_back_restore_the_steps(chx, ny, nx):  # noqa: F811
         chx.ch_set_tuning(h, before[w], what=w)
     assert [chx.ch_get_tuning(h, w) for w in whats] == before
     assert same(stepped(chx, h, c0), ref)
+
+
+def launched(call):
+    """Names and counts of what a call did on the device's runtime."""
+    from torch.profiler import ProfilerActivity, profile
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CPU, ProfilerActivity.CUDA]) as p:
+        call()
+        torch.cuda.synchronize()
+    return {e.key: e.count for e in p.key_averages()}
+
+
+@pytest.mark.parametrize("ny,nx,small", [(64, 64, 0), (128, 128, 0), (256, 256, 0), (90, 203, 0),
+                                         (128, 128, 1)])
+def test_graph_choice_replays_the_two_launch_step(chx, ny, nx, small):  # noqa: F811
+    """With CHX_TUNE_GRAPH a call of the two-launch step is one graph launch
+    (grids that the single-workgroup path and the chunked passes also take
+    among them), the single-workgroup path still launches directly; replays
+    with eager work between give the eager bits."""
+    c0 = inputs.noise_field(ny, nx, 35)
+    h = chx.ch_create(nx, ny, L, L, 1.0, 0.01, 1e-6)
+    if small:
+        chx.ch_set_tuning(h, 1, what=chx.CHX_TUNE_SMALL_PATH)
+    c = torch.empty((ny, nx), dtype=torch.float64, device="cuda")
+    d = torch.zeros(8, dtype=torch.float64, device="cuda")
+    ws = torch.empty(chx.ch_ws_bytes(h) + 256, dtype=torch.uint8, device="cuda")
+
+    def call():
+        chx.ch_adi_step(h, c, nsteps=3, diag_out=d, ws=ws)
+
+    outs = []
+    for k in range(5):
+        if k == 1:
+            chx.ch_set_tuning(h, 1, what=chx.CHX_TUNE_GRAPH)
+        print(f"[case] graph {ny}x{nx} small {small} call {k}", flush=True)
+        c.copy_(torch.from_numpy(c0))
+        d.zero_()
+        if k == 3:
+            seen = launched(call)
+            assert seen.get("hipGraphLaunch", 0) == (0 if small else 1), seen
+            assert seen.get("hipLaunchKernel", 0) == (1 if small else 0), seen
+        else:
+            call()
+        torch.cuda.synchronize()
+        outs.append((c.cpu().numpy(), d.cpu().numpy()))
+    for o in outs[1:]:
+        assert same(o, outs[0])
