@@ -17,9 +17,11 @@
 // The extents are rounded up to a class (0, 1, 2 or 4 per direction), the
 // weights padded with zeros; each class is its own instantiation with the
 // loops fully unrolled.  Tiles are numbered so that the tiles one XCD runs
-// (blocks go to the XCDs round robin) form a contiguous band of the field,
+// (blocks go to the XCDs round robin) form a contiguous band of the field, the
+// up to seven tiles past eight equal bands last,
 // so the halo rows two tiles share meet in one L2 (measured at 8192^2, single
-// columns: the 5-point stencil 0.223 ms banded, 0.255 ms in plain order); the
+// columns: the 5-point stencil 0.223 ms banded, 0.255 ms in plain order; 3333 x
+// 6000, whose tiles are no multiple of eight, 44.8 us against 57.9); the
 // outputs are written with non-temporal stores (plain stores: 0.226 ms).
 // Memory bounds it: 8192^2 5-point FP64 moves 1.07 GB in 0.183 ms, 5.9 TB/s.
 // A second load of every row for the halo columns had cost as many requests
@@ -76,7 +78,7 @@ __global__ __launch_bounds__(256) void stencil2d_tiled(const T* __restrict__ in,
   typedef T Vec __attribute__((ext_vector_type(VX)));
   __shared__ __attribute__((aligned(16))) T tile[HY * PX];
   const int b = blockIdx.x;
-  const int t = per_xcd ? (b & 7) * per_xcd + (b >> 3) : b;
+  const int t = b < 8 * per_xcd ? (b & 7) * per_xcd + (b >> 3) : b;
   const int by = t / ntx, bx = t - by * ntx;
   const int i0 = bx * TX, j0 = by * TY;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -136,7 +138,7 @@ __global__ __launch_bounds__(256) void stencil2d_tiled(const T* __restrict__ in,
     }
   }
   __syncthreads();
-  if (!cin) return;
+  if (!cin || (!wrap && (ci + VX - 1 < left || ci + right >= nx))) return;  // no outputs
 
   T acc[R][VX];
 #pragma unroll
@@ -196,21 +198,33 @@ void launch_tiles(hipStream_t st, const T* in, T* out, int nx, int ny, long ld,
                   int bottom) {
   const long ntx = tiles(nx, 64 * VX), ntiles = ntx * tiles(ny, 4 * R);
   hipLaunchKernelGGL((stencil2d_tiled<EX, EY, VX, R, T>), dim3((unsigned)ntiles), dim3(256), 0, st,
-                     in, out, nx, ny, ld, W, (int)ntx, ntiles % 8 == 0 ? (int)(ntiles / 8) : 0,
-                     wrap, premap, left, right, top, bottom);
+                     in, out, nx, ny, ld, W, (int)ntx, (int)(ntiles / 8), wrap,
+                     premap, left, right, top, bottom);
 }
 
-// Vectors of 16 bytes wherever the rows are whole aligned vectors (and the
-// field at least as large as the stencil's reach), single columns otherwise.
+// Vectors of 16 bytes where the rows are whole aligned vectors (and the field
+// at least as large as the stencil's reach), and where the tiles of vectors, 64
+// of them wide, are not much wider than the row: a third more columns than
+// the tiles of 64 single ones cover, a fifth more for the widest stencils,
+// whose idle columns cost most, and twice as many in FP32 for stencils of one
+// column.
 // us, 16-byte vectors against single columns: 8192^2 5-point FP64 183 / 203,
 // FP32 92 / 113, 9 x 9 FP64 292 / 380, FP32 176 / 232; 1000 x 3000 5 x 5 FP32
-// 7.2 / 8.9; 66 x 8000 9 x 9 FP64 10.2 / 14.7; 512^2 5-point 6.7 / 6.7.
+// 7.2 / 8.9; 66 x 8000 9 x 9 FP64 10.2 / 14.7; 512^2 5-point 6.7 / 6.7.  Fields
+// of 2^24 points in rows of 64 FP32 columns (a tile of vectors covers 256): 9 x
+// 9 2.73 to 2.92 times as long with vectors, 5-point 1.69 to 2.07; of 260 (1.6
+// times the columns) 9 x 9 1.37, 5 x 5 1.07; of 132 (1.33) 9 x 9 1.33, 5-point
+// 0.73 to 0.89; of 400 (1.14) 0.90 and 0.75.  FP64 rows of 64 (128) 1.22 to
+// 1.27 and 1.07 to 1.40, of 192 (1.33) 0.97 and 1.00; 1 x 5 FP32 rows of 68
+// (twice) 0.94.
 template <int EX, int EY, typename T>
 void launch_class(hipStream_t st, const T* in, T* out, int nx, int ny, long ld,
                   const StencilW<T>& W, int wrap, int premap, int left, int right, int top,
                   int bottom) {
   constexpr int VX = 16 / (int)sizeof(T);
+  constexpr int kCover = EX == kMaxExt ? 18 : (EX == 0 && VX == 4 ? 30 : 20);  // fifteenths
   if (nx % VX == 0 && ld % VX == 0 && wrap != 2 &&
+      15 * VX * tiles(nx, 64 * VX) <= kCover * tiles(nx, 64) &&
       ((reinterpret_cast<uintptr_t>(in) | reinterpret_cast<uintptr_t>(out)) & 15) == 0)
     launch_tiles<EX, EY, VX, kRowsWide>(st, in, out, nx, ny, ld, W, wrap, premap, left, right, top,
                                         bottom);

@@ -285,6 +285,63 @@ def test_stencil_vectors_and_single_columns(chx, orc, nx, ny, offset, dtype):
             assert torch.all(rest == 3.5)
 
 
+# widths at which tiles of vectors begin to cover a row as well as single
+# columns do, and on either side; heights whose tile counts leave 0 .. 7 tiles
+# past eight equal bands
+@pytest.mark.parametrize("ny,nx", [(131, 4), (67, 8), (33, 60), (161, 64), (97, 68), (65, 96),
+                                   (129, 128), (49, 130), (81, 158), (113, 160), (33, 192),
+                                   (145, 196), (17, 200), (177, 256), (35, 260), (21, 640)])
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+def test_stencil_rows_of_any_width(chx, orc, ny, nx, dtype):
+    """Against the oracle, every tile its own values: FP64 to 1e-13, FP32 to
+    (terms + 2) eps of the sum of the magnitudes."""
+    x = torch.from_numpy(inputs.uniform(41, (ny, nx), -1, 1)).to(dtype)
+    for ext in ((1, 1, 1, 1), (2, 0, 1, 3), (0, 0, 2, 2), (4, 4, 4, 4)):
+        left, right, top, bottom = ext
+        w = torch.from_numpy(inputs.uniform(42, ((top + bottom + 1) * (left + right + 1),), -1,
+                                            1)).to(dtype)
+        W = w.double().numpy().reshape(top + bottom + 1, left + right + 1)
+        for periodic in (True, False):
+            print(f"[case] stencil {dtype} {ny}x{nx} ext={ext} periodic={periodic}", flush=True)
+            xo = torch.full((ny, nx), 3.5, dtype=dtype, device="cuda")
+            chx.stencil2d_apply(x.cuda(), xo, w.tolist(), left, right, top, bottom,
+                                periodic=periodic)
+            torch.cuda.synchronize()
+            kw = dict(periodic=periodic, premap=0)
+            ref = orc.stencil2d(x.double().numpy(), W, left, right, top, bottom,
+                                out=np.full((ny, nx), 3.5), **kw)
+            mag = orc.stencil2d(np.abs(x.double().numpy()), np.abs(W), left, right, top, bottom,
+                                out=np.zeros((ny, nx)), **kw)
+            tol = 1e-13 if dtype == torch.float64 else \
+                (W.size + 2) * np.finfo(np.float32).eps * mag
+            assert np.all(np.abs(xo.cpu().double().numpy() - ref) <= tol)
+
+
+def test_narrow_stencil_is_not_tiled_for_wide_rows(chx):
+    """Rows of 4 FP32 columns take about the time of rows of 5, whose length
+    rules vectors out (13 us and 14; 76 in tiles of vectors), and rows of 130
+    FP64 columns no more than rows of 131."""
+    for dtype, ny, nx, ext in ((torch.float32, 100000, 4, 4), (torch.float64, 20000, 130, 0)):
+        w = [0.1] * ((2 * ext + 1) * 9)
+        best = []
+        for n in (nx, nx + 1):
+            x = torch.zeros((ny, n), dtype=dtype, device="cuda")
+            o = torch.empty_like(x)
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            ms = []
+            for _ in range(12):
+                e0.record()
+                for _ in range(20):
+                    chx.stencil2d_apply(x, o, w, ext, ext, 4, 4, periodic=False)
+                e1.record()
+                torch.cuda.synchronize()
+                ms.append(e0.elapsed_time(e1) / 20)
+            best.append(min(ms))
+        print(f"[case] stencil {dtype} {ny}x{nx}: {best[0]:.4f} ms against {best[1]:.4f}",
+              flush=True)
+        assert best[0] < 1.6 * best[1]
+
+
 @pytest.mark.parametrize("ext,premap", [((1, 1, 1, 1), 1), ((2, 2, 2, 2), 0), ((4, 4, 4, 4), 0),
                                          ((3, 0, 4, 1), 1)])
 def test_stencil_full_size_sampled(chx, orc, ext, premap):
