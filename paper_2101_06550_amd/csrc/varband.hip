@@ -13,8 +13,8 @@
 //    epsilon; tridiagonal: b <- 1/den, c <- chat.
 //  - rewrite: factor and solve in one kernel that leaves the diagonals alone;
 //    the back sweep's coefficients are computed a second time from the
-//    diagonals, or, for systems that are not periodic and few or short, kept
-//    in the workspace (the rule and its figures are at rewrite()).
+//    diagonals, or, for few systems and for some that are not periodic, kept
+//    in the workspace (the rule and its figures are at rewrite_kind()).
 //  - periodic systems: the last two unknowns are bordered off (Ch.4, Navon)
 //    or the corners split off as a rank-one term (Ch.5, Sherman-Morrison),
 //    both built from each system's own rows.  The correction that the thesis
@@ -39,7 +39,7 @@
 namespace chx_vb {
 
 constexpr int kThreads = 256;
-constexpr int kU = 8;  // rows the factor kernels stage per batch of loads
+constexpr int kU = 8;  // rows the factor and plain rewrite kernels stage per batch of loads
 // The staged loads are non-temporal: every value is used once per pass
 // (measured at n = 1024, 65536 systems: factored solves 2-7 % faster).
 // The solve kernels stage fewer rows: with one system per thread the batch
@@ -235,7 +235,8 @@ __device__ __forceinline__ void penta_back(int m, long s, const double* __restri
 // Workspace vectors of a periodic penta batch: rows 0..m-1, stride ldw.
 //   factor/solve: [w0 | w1 | pk0 | pk1] then Minv (4 x ldw)
 //   rewrite:      the state of the forward sweep before every block of rows
-//                 (10 x ldw), or, kept and non-periodic, [gamma | delta]
+//                 (10 x ldw), or, kept, [gamma | delta | pk0 | pk1], of which
+//                 a system that is not periodic has the first two
 
 template <bool PER>
 __global__ __launch_bounds__(kThreads) void penta_batch_factor_k(
@@ -384,7 +385,8 @@ __global__ __launch_bounds__(kThreads) void penta_batch_solve_k(
 // chat above R's unit diagonal; x = R^{-1}(L^{-1} f - phi L^{-1} u) with
 // phi = (w . L^{-1} f) / (1 + w . L^{-1} u), w = R^{-T} v.
 // Workspace: factor/solve [zu | w] then 1/(1 + v.z); rewrite the state of the
-// forward sweep before every block of rows, or, kept and non-periodic, [chat].
+// forward sweep before every block of rows, or, kept, [chat | zu], of which a
+// system that is not periodic has the first.
 // ---------------------------------------------------------------------------
 
 struct TriFwd {
@@ -709,7 +711,7 @@ __device__ __forceinline__ void sweep_group(int i, int m, const Group<U, S::kBan
 
 // Kept factors: the forward sweep leaves its values in x and the workspace,
 // the back sweep reads them.  Systems that are not periodic only: of the
-// others' factors more would have to be kept, and at no size did that win.
+// others' factors more would have to be kept.
 template <class S, int U>
 __global__ __launch_bounds__(kWave, 1) void rewrite_once_k(int n, int batch, long ld,
                                                            Columns<S::kBands + 1> in, double* x,
@@ -875,6 +877,117 @@ __global__ __launch_bounds__(kWave, 1) void rewrite_twice_k(int n, int batch, lo
   S::finish(n, ld, lane, t, x);
 }
 
+// Kept factors, one group of rows loaded and worked on at a time: fewer
+// instructions a row than the kernels above, which is what a batch of one
+// wave waits for as long as its rows come out of the cache.
+__global__ __launch_bounds__(kThreads) void penta_rewrite_plain_k(
+    int n, int batch, long ld, const double* __restrict__ a, const double* __restrict__ b,
+    const double* __restrict__ c, const double* __restrict__ d, const double* __restrict__ e,
+    double* __restrict__ x, double* __restrict__ ws, long ldw) {
+  const long s = (long)blockIdx.x * kThreads + threadIdx.x;
+  if (s >= batch) return;
+  const int m = n - 2;
+  PentaTail tl{};
+  penta_load_tail<true, true>(n, ld, s, a, b, c, d, e, x, tl);
+  double* gm = ws;
+  double* dl = ws + (long)m * ldw;
+  double* p0 = ws + 2L * m * ldw;
+  double* p1 = ws + 3L * m * ldw;
+  PentaFwd st;
+  int i = 0;
+  for (; i + kU <= m; i += kU) {
+    double va[kU], vb[kU], vc[kU], vd[kU], ve[kU], vf[kU];
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      const long r = (long)(i + u) * ld + s;
+      va[u] = __builtin_nontemporal_load(&a[r]);
+      vb[u] = __builtin_nontemporal_load(&b[r]);
+      vc[u] = __builtin_nontemporal_load(&c[r]);
+      vd[u] = __builtin_nontemporal_load(&d[r]);
+      ve[u] = __builtin_nontemporal_load(&e[r]);
+      vf[u] = __builtin_nontemporal_load(&x[r]);
+    }
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      double beta, inv, gam, del, g, pk0, pk1, wh0, wh1;
+      penta_fwd_row<true, true>(i + u, m, va[u], vb[u], vc[u], vd[u], ve[u], vf[u], tl, st, beta,
+                               inv, gam, del, g, pk0, pk1, wh0, wh1);
+      const long rw = (long)(i + u) * ldw + s;
+      x[(long)(i + u) * ld + s] = g;
+      gm[rw] = gam;
+      dl[rw] = del;
+      p0[rw] = pk0;
+      p1[rw] = pk1;
+    }
+  }
+  for (; i < m; ++i) {
+    const long r = (long)i * ld + s;
+    double beta, inv, gam, del, g, pk0, pk1, wh0, wh1;
+    penta_fwd_row<true, true>(i, m, a[r], b[r], c[r], d[r], e[r], x[r], tl, st, beta, inv, gam,
+                             del, g, pk0, pk1, wh0, wh1);
+    const long rw = (long)i * ldw + s;
+    x[r] = g;
+    gm[rw] = gam;
+    dl[rw] = del;
+    p0[rw] = pk0;
+    p1[rw] = pk1;
+  }
+  double mi[4];
+  penta_minv(tl, st, mi);
+  const double r0 = tl.f0 - st.s0, r1 = tl.f1 - st.s1;
+  const double t0 = mi[0] * r0 + mi[1] * r1;
+  const double t1 = mi[2] * r0 + mi[3] * r1;
+  penta_back<kU, true>(m, s, gm, ldw, dl, ldw, p0, p1, ldw, t0, t1, x, ld);
+  x[(long)(n - 2) * ld + s] = t0;
+  x[(long)(n - 1) * ld + s] = t1;
+}
+
+template <bool PER>
+__global__ __launch_bounds__(kThreads) void tri_rewrite_plain_k(
+    int n, int batch, long ld, const double* __restrict__ a, const double* __restrict__ b,
+    const double* __restrict__ c, double* __restrict__ x, double* __restrict__ ws, long ldw) {
+  const long s = (long)blockIdx.x * kThreads + threadIdx.x;
+  if (s >= batch) return;
+  const double a0 = PER ? a[s] : 0.0, b0 = PER ? b[s] : 0.0;
+  const double cl = PER ? c[(long)(n - 1) * ld + s] : 0.0;
+  double* chv = ws;
+  double* zu = PER ? ws + (long)n * ldw : nullptr;
+  TriFwd st;
+  int i = 0;
+  for (; i + kU <= n; i += kU) {
+    double va[kU], vb[kU], vc[kU], vf[kU];
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      const long r = (long)(i + u) * ld + s;
+      va[u] = __builtin_nontemporal_load(&a[r]);
+      vb[u] = __builtin_nontemporal_load(&b[r]);
+      vc[u] = __builtin_nontemporal_load(&c[r]);
+      vf[u] = __builtin_nontemporal_load(&x[r]);
+    }
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      double inv, ch, y, z, w;
+      tri_fwd_row<PER, true>(i + u, n, va[u], vb[u], vc[u], vf[u], a0, b0, cl, st, inv, ch, y,
+                             z, w);
+      const long rw = (long)(i + u) * ldw + s;
+      x[(long)(i + u) * ld + s] = y;
+      chv[rw] = ch;
+      if (PER) zu[rw] = z;
+    }
+  }
+  for (; i < n; ++i) {
+    const long r = (long)i * ld + s;
+    double inv, ch, y, z, w;
+    tri_fwd_row<PER, true>(i, n, a[r], b[r], c[r], x[r], a0, b0, cl, st, inv, ch, y, z, w);
+    const long rw = (long)i * ldw + s;
+    x[r] = y;
+    chv[rw] = ch;
+    if (PER) zu[rw] = z;
+  }
+  const double phi = PER ? st.sy / (1.0 + st.sz) : 0.0;
+  tri_back<kU, PER>(n, s, chv, ldw, zu, ldw, phi, x, ld);
+}
+
 // ---------------------------------------------------------------------------
 // Host side: argument checks, workspace layout, launches.
 // ---------------------------------------------------------------------------
@@ -909,40 +1022,92 @@ int check_ws(const void* ws, size_t ws_bytes, size_t need_doubles) {
 
 dim3 grid_of(int batch) { return dim3((unsigned)((batch + kThreads - 1) / kThreads)); }
 
-// Which kernel (ms, FP64, against 1.72 penta and 1.05 tri at 1024 x 65536 for
-// kept factors without the double set of rows):
-//  - periodic: always twice.  1024 x 65536: penta 1.31, tri 0.84, against 1.72
-//    and 1.07 kept; 512 x 4096: 0.161 and 0.114 against 0.180 and 0.128.
-//  - not periodic: twice only where the batch streams from memory, 0.317
+// Which kernel (ms unless us, FP64; "kept" the double set of rows unless plain):
+//  - periodic: twice.  1024 x 65536: penta 1.31, tri 0.84, against 1.72 and
+//    1.07 kept plain; 512 x 4096: 0.161 and 0.114 against 0.180 and 0.128.
+//  - not periodic: twice only where it hides what the batch waits for, 0.317
 //    against 0.349 (penta) and 0.216 against 0.297 (tri) at 1024 x 16384;
 //    kept below, 0.133 against 0.135 and 0.107 against 0.107 at 512 x 4096,
 //    and for short systems, whose factors stay in the last-level cache
-//    (100 x 65536: 0.108 against 0.124, 0.076 against 0.078).
+//    (100 x 65536: 0.108 against 0.124, 0.076 against 0.078).  Tridiagonal
+//    batches of more than three waves a CU are bound by bandwidth, where 72
+//    bytes a row kept lose to 64 (plain up to one wave per SIMD, 512 x 50000
+//    0.304 against 0.347; two groups of 8 above, 256 x 100000 0.301 against
+//    0.352) until the factors pass the last-level cache (1024 x 65536 0.82
+//    twice, 0.84 kept).
+//  - at most a wave of systems: plain while a periodic batch is small (us, 100 x
+//    64: tri 22.8 against 28.4 twice, penta 32.1 against 36.0; 1024 x 1: tri 206
+//    against 233, penta 320 against 336; but 256 x 64, by where its arrays lie:
+//    tri 52 to 90 against 58), and for all tridiagonals that are not periodic
+//    (256 x 1: 34.3 against 44.7; 1024 x 64: 143 against 168).
 //  - groups of 4 rows for the pentadiagonal below half a wave per SIMD, where
 //    the smaller kernel keeps clear of the accumulation registers (1024 x
 //    16384: 0.337 against 0.353), of 8 above (1024 x 65536: 1.31 against
 //    1.37); the tridiagonal fits at 8 (1024 x 16384: 0.228 against 0.264).
+//  - short systems: blocks of 16 rows below 64 and of 8 up to 8, as a block's
+//    loads are issued whether or not it has the rows (us, periodic, 100000
+//    systems: penta of 8 rows 15.0 in blocks of 8, 22.0 of 16, 37.2 of 32, 19.3
+//    plain; of 16 32.6, 30.8, 46.7; tri of 8 10.0, 13.7, 23.0, of 40 50.4 of 16
+//    and 60.6 of 32).
 constexpr int kTwiceBatch = 16384, kTwiceRows = 256, kWideBatch = 32768;
+constexpr int kBandwidthBatch = 3 * 256 * kWave, kSimdBatch = 4 * 256 * kWave;
+constexpr int kCachedRows = 768, kShortRows = 64, kTinyRows = 8;
+constexpr long kLoneRows = 8000;
+
+enum class Rewrite { kPlain, kOnce4, kOnce8, kTwice4x2, kTwice4x4, kTwice8x4 };
+
+template <class S>
+Rewrite rewrite_kind(int n, int batch) {
+  constexpr bool tri = S::kBands == 3;
+  if (batch <= kWave && (S::kPeriodic ? n * (long)batch < kLoneRows : tri)) return Rewrite::kPlain;
+  if (S::kPeriodic) {
+    if ((tri ? n : n - 2) <= kTinyRows) return Rewrite::kTwice4x2;
+    if (n < kShortRows || (!tri && batch < kWideBatch)) return Rewrite::kTwice4x4;
+    return Rewrite::kTwice8x4;
+  }
+  if (batch < kTwiceBatch || n < kTwiceRows) return Rewrite::kOnce4;
+  if (tri && batch > kBandwidthBatch) {
+    if (batch < kSimdBatch) return Rewrite::kPlain;
+    if (n < kCachedRows) return Rewrite::kOnce8;
+  }
+  return !tri && batch < kWideBatch ? Rewrite::kTwice4x4 : Rewrite::kTwice8x4;
+}
 
 template <class S>
 void rewrite(int n, int batch, long ld, const Columns<S::kBands + 1>& in, double* x, double* ws,
              hipStream_t st) {
-  const dim3 grid((unsigned)((batch + kWave - 1) / kWave));
+  const dim3 grid((unsigned)((batch + kWave - 1) / kWave)), block(kWave);
   const long ldw = ws_ld(batch);
-  if constexpr (!S::kPeriodic)
-    if (batch < kTwiceBatch || n < kTwiceRows) {
-      hipLaunchKernelGGL((rewrite_once_k<S, 4>), grid, dim3(kWave), 0, st, n, batch, ld, in, x, ws,
+  switch (rewrite_kind<S>(n, batch)) {
+    case Rewrite::kPlain:
+      if constexpr (S::kBands == 3)
+        hipLaunchKernelGGL(tri_rewrite_plain_k<S::kPeriodic>, grid_of(batch), dim3(kThreads), 0, st,
+                           n, batch, ld, in.p[0], in.p[1], in.p[2], x, ws, ldw);
+      else if constexpr (S::kPeriodic)
+        hipLaunchKernelGGL(penta_rewrite_plain_k, grid_of(batch), dim3(kThreads), 0, st, n,
+                           batch, ld, in.p[0], in.p[1], in.p[2], in.p[3], in.p[4], x, ws, ldw);
+      return;
+    case Rewrite::kOnce4:
+      if constexpr (!S::kPeriodic)
+        hipLaunchKernelGGL((rewrite_once_k<S, 4>), grid, block, 0, st, n, batch, ld, in, x, ws, ldw);
+      return;
+    case Rewrite::kOnce8:
+      if constexpr (!S::kPeriodic)
+        hipLaunchKernelGGL((rewrite_once_k<S, 8>), grid, block, 0, st, n, batch, ld, in, x, ws, ldw);
+      return;
+    case Rewrite::kTwice4x2:
+      hipLaunchKernelGGL((rewrite_twice_k<S, 4, 2>), grid, block, 0, st, n, batch, ld, in, x, ws,
                          ldw);
       return;
-    }
-  if constexpr (S::kBands == 5)
-    if (batch < kWideBatch) {
-      hipLaunchKernelGGL((rewrite_twice_k<S, 4, 4>), grid, dim3(kWave), 0, st, n, batch, ld, in, x,
-                         ws, ldw);
+    case Rewrite::kTwice4x4:
+      hipLaunchKernelGGL((rewrite_twice_k<S, 4, 4>), grid, block, 0, st, n, batch, ld, in, x, ws,
+                         ldw);
       return;
-    }
-  hipLaunchKernelGGL((rewrite_twice_k<S, 8, 4>), grid, dim3(kWave), 0, st, n, batch, ld, in, x, ws,
-                     ldw);
+    case Rewrite::kTwice8x4:
+      hipLaunchKernelGGL((rewrite_twice_k<S, 8, 4>), grid, block, 0, st, n, batch, ld, in, x, ws,
+                         ldw);
+      return;
+  }
 }
 
 int launched() { return hipGetLastError() == hipSuccess ? CHX_OK : CHX_EHIP; }

@@ -248,3 +248,44 @@ def test_rewrite_at_group_block_and_batch_edges(chx, orc, n, batch, periodic):
         xr = x[:, :batch].cpu().numpy()
         assert _err(xr[:, :ref.shape[1]], ref) < 1e-12
         assert np.array_equal(xr, xr[:, pick])
+
+
+# ... and of the lengths and batches at which the kernel changes again: blocks
+# of 8 and 16 rows for short systems, at most a wave of systems, and
+# tridiagonal batches past three waves a CU
+ROUTES = [(n, b, True) for n in (7, 8, 9, 10, 11, 62, 63, 64) for b in (66, 33000)] + \
+         [(n, b, per) for n in (30, 124, 125) for b in (1, 64, 65) for per in (False, True)] + \
+         [(n, b, False) for n in (256, 300) for b in (49152, 49153, 65535, 65536)] + \
+         [(n, 65536, False) for n in (255, 767, 768)] + [(499, 16, True), (500, 16, True)]
+
+
+@pytest.mark.parametrize("n,batch,periodic", ROUTES)
+def test_rewrite_at_the_lines_between_its_kernels(chx, orc, n, batch, periodic):
+    test_rewrite_at_group_block_and_batch_edges(chx, orc, n, batch, periodic)
+
+
+def test_short_periodic_rewrite_costs_what_its_rows_do(chx):
+    """100000 periodic systems of 8 rows take about the time of 100000 that
+    are not periodic (us: 15 and 15 pentadiagonal, 10 and 11 tridiagonal; 39
+    and 25 in blocks of 32 rows)."""
+    n, batch = 8, 100000
+    for bands, rewrite in (((0.5, -2.0, 4.0, -2.0, 0.5), chx.penta_batch_rewrite),
+                           ((-0.5, 2.0, -0.5), chx.tri_batch_rewrite)):
+        A = [torch.full((n, batch), v, dtype=torch.float64, device="cuda") for v in bands]
+        x = torch.ones((n, batch), dtype=torch.float64, device="cuda")
+        e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        best = []
+        for periodic in (True, False):
+            ws = rewrite(*A, x, periodic=periodic)
+            ms = []
+            for _ in range(12):
+                e0.record()
+                for _ in range(20):
+                    rewrite(*A, x, periodic=periodic, ws=ws)
+                e1.record()
+                torch.cuda.synchronize()
+                ms.append(e0.elapsed_time(e1) / 20)
+            best.append(min(ms))
+        print(f"[case] rewrite {len(bands)} bands: {best[0]:.4f} ms against {best[1]:.4f}",
+              flush=True)
+        assert best[0] < 1.7 * best[1]
