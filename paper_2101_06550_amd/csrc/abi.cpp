@@ -1403,10 +1403,16 @@ static_assert(kNumSplitShapes == CHX_NUM_SPLIT_SHAPES, "shape count mismatch");
 // 176: long columns leave few workgroups).
 constexpr long kPairPoints = 1L << 20;
 constexpr int kPairColumn = 1024;
-// The thesis scheme's two launches against its three and the diagnostics' two
-// (four steps a call: 512 x 512 61 us against 121, 1024 x 1024 117 against 158,
-// 2048 x 1536 282 against 300, 2048 x 2048 363 against 351).
-constexpr long kPairPoints2 = 3L << 20;
+// The thesis scheme's two launches against its three and the diagnostics' two,
+// on grids that both take (us, four steps a call, without and with mass and
+// energy: 512 x 512 55 and 60 against 83 and 112; 1024 x 1024 104 and 113
+// against 106 and 139; 1280 x 2048 209 and 229 against 194 and 245; 2048 x
+// 1024 172 and 189 against 169 and 210; past the points 1536 x 2048 246 and 267
+// against 211 and 274, 2048 x 1536 276 and 297 against 224 and 282).  Columns
+// of more than kPairColumn2 rows want a workgroup for every CU, which kPairWide
+// columns are (2048 x 512 132 and 145 against 107 and 141).
+constexpr long kPairPoints2 = 5L << 19;
+constexpr int kPairColumn2 = 1536, kPairWide = 1024;
 // ... and of this many take their final mass and energy in one launch.
 constexpr long kDiagSmall = 1L << 15;
 
@@ -1458,7 +1464,8 @@ int ch_create(const chx_ch_params* prm, chx_ch* out) {
   const bool chunked = q.nx % 64 == 0 && q.ny % kChunk == 0 && q.nx / kChunk <= 256;
   int pair_y = 0, pair_x = 0;
   if (q.scheme == CHX_SCHEME_P2 &&
-      (!chunked || (long)q.nx * q.ny <= kPairPoints2)) {
+      (!chunked || ((long)q.nx * q.ny <= kPairPoints2 &&
+                    (q.ny <= kPairColumn2 || q.nx >= kPairWide)))) {
     pair_y = pair_chunk(q.ny, true, 4);  // tiles of four columns
     pair_x = pair_chunk(q.nx, false, 4);
     h->pair = pair_y > 0 && pair_y < kChunk && pair_x > 0;

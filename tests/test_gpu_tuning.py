@@ -52,7 +52,9 @@ def test_refused_choice_changes_nothing(chx, ny, nx):  # noqa: F811
 
 @pytest.mark.parametrize("ny,nx,scheme,two", [
     (64, 64, 0, 1), (128, 128, 0, 1), (1024, 1024, 0, 1), (90, 203, 0, 1), (2048, 64, 0, 0),
-    (5, 130, 0, 0), (128, 128, 1, 1), (90, 203, 1, 1), (4096, 1024, 1, 0)])
+    (5, 130, 0, 0), (128, 128, 1, 1), (90, 203, 1, 1), (4096, 1024, 1, 0),
+    (1280, 2048, 1, 1), (1312, 2048, 1, 0), (1536, 64, 1, 1), (1568, 64, 1, 0),
+    (1568, 1024, 1, 1), (1568, 960, 1, 0), (2048, 70, 1, 1)])
 def test_two_launch_choice_is_read_cleared_and_restored(chx, ny, nx, scheme, two):  # noqa: F811
     """CHX_TUNE_TWO_LAUNCH says how unforced steps run; 0 leaves the other
     routes, to rounding; 1 brings the same bits back, and is refused where
