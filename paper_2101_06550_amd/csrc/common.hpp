@@ -54,14 +54,15 @@ __device__ __forceinline__ double wave_sum(double v) {
 }
 
 // Brings a plan table of N lines of 64 bytes into the scalar cache: one load
-// per line, all in flight together, while the chunk's own loads are.  A
+// per line, all in flight together, while the chunk's own loads are, which the
+// caller has issued before (the loads behind these wait with them).  A
 // kernel starts with that cache empty, and the sweeps that read the table
 // hold few lines at a time, so without this the first of them wait on memory
-// again and again (FP32-refined 1024 x 1024, five steps: 406 us against 382;
-// rows of the 8192 x 8192 step: three steps 1.451 ms against 1.437).  Not in
-// kernels that read the pointer out of memory: it costs the ensemble's row
-// kernel its scalar table (0.94 ms against 1.13), and the FP64 column passes
-// gain nothing, their tables' first use lying behind the field's loads.
+// again and again (four steps in 32-point chunks at 1024^2 108.8 us against
+// 102.1, 2048 x 1024 127.6 against 115.3).  Not in kernels that read the pointer
+// out of memory: it costs the ensemble's row kernel its scalar table (0.94 ms
+// against 1.13), and the FP64 column passes gain nothing, their tables' first
+// use lying behind the field's loads.
 template <int N>
 __device__ __forceinline__ void warm(const void* p) {
   using Line = const __attribute__((address_space(4))) unsigned*;

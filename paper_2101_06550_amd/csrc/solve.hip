@@ -552,7 +552,10 @@ constexpr bool kRowsHalfTile = true;
 // the group streams in with non-temporal loads (the standalone solves; in
 // the ADI step they slowed the row pass more than they sped up the column
 // pass that follows it: 0.182 -> 0.216 and 0.216 -> 0.198 ms at 8192^2).
-template <int P, int M, bool NTL = false>
+// WARM: the plan table goes into the scalar cache behind the group's loads (in
+// front of them, four steps at 2048^2 156 us against 152, in 16-point chunks
+// 143 against 139; without, 166 and 138).
+template <int P, int M, bool NTL = false, bool WARM = false>
 __device__ __forceinline__ void row_half_body(double* xg, int S, const double* __restrict__ rec,
                                               const BandT<double>& bd,
                                               const double* __restrict__ blocks, int dlo,
@@ -576,6 +579,7 @@ __device__ __forceinline__ void row_half_body(double* xg, int S, const double* _
       vin[u] = b2[t + 256 * u];
     }
   }
+  if constexpr (WARM) warm<M - P>(rec);
   // element e = 2t + 512u of the group lies in half u / (M/4); within its
   // half at e' = e - half NG/2, LDS slot e' + e' / M
   double f[M];
@@ -676,12 +680,12 @@ __device__ __forceinline__ void row_half_body(double* xg, int S, const double* _
   }
 }
 
-template <int P, int M, bool NTL = false>
+template <int P, int M, bool NTL = false, bool WARM = true>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void row_solve_half(
     double* x, int S, const double* __restrict__ rec, BandT<double> bd,
     const double* __restrict__ blocks, int dlo, int dcount) {
-  warm<M - P>(rec);
-  row_half_body<P, M, NTL>(x + (long)blockIdx.x * (256 * M), S, rec, bd, blocks, dlo, dcount);
+  row_half_body<P, M, NTL, WARM>(x + (long)blockIdx.x * (256 * M), S, rec, bd, blocks, dlo,
+                                 dcount);
 }
 
 // FP32 rows in, FP32 rows out (the refined step's row solves of its FP32
@@ -1689,7 +1693,15 @@ hipError_t launch_rows_lds(const DevChunk& c, double* x, long ld, int rows, hipS
   const long ngroups = ((long)rows + R - 1) / R;
   // dense rows in whole groups of 256 chunks: the half-tile kernel
   const bool half = kRowsHalfTile && P == 2 && ld == c.n && 256 % c.S == 0 && rows % R == 0;
-  if (half && c.M == kChunk && stream_in)
+  // streamed solves of more groups than the CUs hold at once find the table in
+  // the cache after the first round, and fetching it again holds up their
+  // loads (us without and with: 1250 groups 26.8 and 30.3, 2048 48.9 and 47.5;
+  // 256 groups 9.0 and 8.4, 768 14.3 and 13.5)
+  if (half && c.M == kChunk && stream_in && ngroups > 1024)
+    hipLaunchKernelGGL((row_solve_half<2, kChunk, true, false>), dim3((unsigned)ngroups),
+                       dim3(256), 0, st, x, c.S, c.rec, band_of<double>(c.coef), c.blocks, c.dlo,
+                       c.dcount);
+  else if (half && c.M == kChunk && stream_in)
     hipLaunchKernelGGL((row_solve_half<2, kChunk, true>), dim3((unsigned)ngroups), dim3(256), 0,
                        st, x, c.S, c.rec, band_of<double>(c.coef), c.blocks, c.dlo, c.dcount);
   else if (half && c.M == kChunk)
