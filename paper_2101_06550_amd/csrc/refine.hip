@@ -151,8 +151,8 @@ __device__ __forceinline__ double vsum(const BV& B, long j, int nx, int i) {
 // previous step's solution, rebuilt from its deferred FP32 solutions
 // V_0 .. V_{NB-1} as it is read (so the state is not written and read back
 // between the steps of a call).
-template <bool DIAG, int NB = 0, typename CP = const double*, typename TP32 = const float*,
-          typename BV = RBufs, typename TP = const double*>
+template <bool DIAG, int NB = 0, bool WARM = false, typename CP = const double*,
+          typename TP32 = const float*, typename BV = RBufs, typename TP = const double*>
 __device__ __forceinline__ void rstep_first_body(CP __restrict__ c, long ld,
                                                  double* __restrict__ rbuf,
                                                  float* __restrict__ y32,
@@ -205,6 +205,10 @@ __device__ __forceinline__ void rstep_first_body(CP __restrict__ c, long ld,
   };
 #pragma unroll
   for (int t = 0; t < kPfR; ++t) load(t);
+  if constexpr (WARM) {
+    warm<MI / 2>(rec32);
+    if (NB > 0) warm<MI>(rec);
+  }
   double XL[Q], XR[Q];
   float f[M];
   double msum = 0.0, esum = 0.0;
@@ -253,7 +257,7 @@ __device__ __forceinline__ void rstep_first_body(CP __restrict__ c, long ld,
 // Later pass k = NB of a refined step: x = sum of the rebuilt V_0 .. V_{NB-1}
 // (window rows kc M - 2 .. kc M + M + 1, separators of chunks kc - 1, kc,
 // kc + 1 first), R = r - (I + sx Px)(I + sy Py) x in FP64, swept in FP32.
-template <int NB, typename BV, typename TP, typename TP32>
+template <int NB, bool WARM = false, typename BV, typename TP, typename TP32>
 __device__ __forceinline__ void rstep_resid_body(const double* __restrict__ rbuf, const BV& B,
                                                  float* __restrict__ y32,
                                                  float* __restrict__ rho, int nx, int ny,
@@ -284,6 +288,10 @@ __device__ __forceinline__ void rstep_resid_body(const double* __restrict__ rbuf
   };
 #pragma unroll
   for (int t = 0; t < kPfR; ++t) load(t);
+  if constexpr (WARM) {
+    warm<MI / 2>(rec32);
+    warm<MI>(rec);
+  }
   double X[Q], XH[Q];
   float f[M];
   const float eps = bd.c[0];
@@ -328,7 +336,7 @@ __device__ __forceinline__ void rstep_resid_body(const double* __restrict__ rbuf
 
 // End of a refined step: x = sum of the rebuilt V_0 .. V_{NB-1}, written to
 // c (FP64); DIAG: mass and free energy of x.  Window rows kc M .. kc M + M.
-template <int NB, bool DIAG, typename BV, typename CP, typename TP>
+template <int NB, bool DIAG, bool WARM = false, typename BV, typename CP, typename TP>
 __device__ __forceinline__ void rstep_final_body(const BV& B, CP __restrict__ c, long ld,
                                                  int nx, int ny, int nseg, int Sc,
                                                  TP __restrict__ rec, const ChCoef& K,
@@ -356,6 +364,7 @@ __device__ __forceinline__ void rstep_final_body(const BV& B, CP __restrict__ c,
   };
 #pragma unroll
   for (int t = 0; t < kPfR; ++t) load(t);
+  if constexpr (WARM) warm<MI>(rec);
   double X[Q], XH[Q];
   double msum = 0.0, esum = 0.0;
 #pragma unroll
@@ -413,9 +422,7 @@ __global__ __launch_bounds__(256) void rstep_first(const double* __restrict__ c,
   const int li = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
   const int seg = li % nseg, kc = li / nseg;
   if (kc >= Sc) return;  // no barrier in this kernel
-  warm<MI / 2>(rec32);
-  if (NB > 0) warm<MI>(rec);
-  rstep_first_body<DIAG, NB>(c, ld, rbuf, y32, rho, nx, ny, nseg, rec32, bd, K, part, seg, kc,
+  rstep_first_body<DIAG, NB, true>(c, ld, rbuf, y32, rho, nx, ny, nseg, rec32, bd, K, part, seg, kc,
                              Bv, Sc, rec);
 }
 
@@ -431,9 +438,7 @@ __global__ __launch_bounds__(256) void rstep_resid(const double* __restrict__ rb
   const int li = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
   const int seg = li % nseg, kc = li / nseg;
   if (kc >= Sc) return;  // no barrier in this kernel
-  warm<MI / 2>(rec32);
-  warm<MI>(rec);
-  rstep_resid_body<NB>(rbuf, B, y32, rho, nx, ny, Sc, rec, rec32, bd, ax, ay, seg, kc);
+  rstep_resid_body<NB, true>(rbuf, B, y32, rho, nx, ny, Sc, rec, rec32, bd, ax, ay, seg, kc);
 }
 
 template <int NB, bool DIAG>
@@ -444,8 +449,7 @@ __global__ __launch_bounds__(256) void rstep_final(RBufs B, double* __restrict__
   const int li = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
   const int seg = li % nseg, kc = li / nseg;
   if (kc >= Sc) return;  // no barrier in this kernel
-  warm<MI>(rec);
-  rstep_final_body<NB, DIAG>(B, c, ld, nx, ny, nseg, Sc, rec, K, part, seg, kc);
+  rstep_final_body<NB, DIAG, true>(B, c, ld, nx, ny, nseg, Sc, rec, K, part, seg, kc);
 }
 
 // Ensemble kernels: block = work item {run, segment block, chunk}; each run
@@ -562,10 +566,14 @@ hipError_t launch_ens_rstep_final(const EnsRun* runs, const EnsClasses& cls, con
 int rstep_segments(int nx) { return (nx + kSegR - 1) / kSegR; }
 long rstep_parts(int nx, int ny) { return (long)rstep_segments(nx) * (ny / M); }
 
-// (segment, chunk) pairs per block: four, or one on grids whose pairs do not
-// fill the SIMDs twice, so that every CU gets some (with the rows' smaller
-// groups, 1024 x 1024 five steps 426 -> 410 us).
-static int rstep_waves(int nx, int ny) { return rstep_parts(nx, ny) < 2048 ? 1 : 4; }
+// (segment, chunk) pairs per block: four, or one on grids of long rows whose
+// pairs do not fill the SIMDs twice, so that every CU gets some (means over one
+// and five steps of one and two passes, against four: 64 x 1024 0.97, 64 x 8192
+// 0.96, 1024^2 0.98); on short rows a block's four pairs are most of the columns
+// two chunks share (128^2 1.14 with one, 2048 x 64 1.10, 256 x 256 1.14).
+static int rstep_waves(int nx, int ny) {
+  return nx >= 1024 && rstep_parts(nx, ny) < 2048 ? 1 : 4;
+}
 static dim3 rstep_block(int nx, int ny) { return dim3(64 * rstep_waves(nx, ny)); }
 static dim3 rstep_grid(int nx, int ny) {
   const int w = rstep_waves(nx, ny);
