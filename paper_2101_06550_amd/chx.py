@@ -170,8 +170,8 @@ def _check(st: int, what: str):
 # The helpers below run on every call, and a small solve or step is over in
 # the time that a few of them take: pointers and streams go to ctypes as plain
 # numbers (its argtypes convert them), the current stream's handle is read
-# without a Stream object, and a tensor's storage is looked at only where the
-# tensor itself does not already cover what the kernels touch.
+# without a Stream object where torch can, and a tensor's storage is looked at
+# only where the tensor itself does not already cover what the kernels touch.
 def _th():
     global _torch
     if _torch is None:
@@ -180,10 +180,25 @@ def _th():
     return _torch
 
 
+_raw_stream = None  # gives the current stream's handle; chosen by the first call
+
+
+def _current_raw_stream():
+    """The current stream's handle by torch's own shortcut, or through a Stream
+    object where this torch has none."""
+    global _raw_stream
+    if _raw_stream is None:
+        torch = _th()
+        get = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        dev = getattr(torch._C, "_cuda_getDevice", None)
+        _raw_stream = ((lambda: get(dev())) if get and dev
+                       else (lambda: torch.cuda.current_stream().cuda_stream))
+    return _raw_stream()
+
+
 def _stream(stream):
     if stream is None:
-        c = _th()._C
-        return c._cuda_getCurrentRawStream(c._cuda_getDevice())
+        return _current_raw_stream()
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 

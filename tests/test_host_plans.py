@@ -430,3 +430,20 @@ def test_solve_binding_rejects_short_buffers():
 def test_two_launch_choice_matches_header():
     m = re.search(r"#define\s+CHX_TUNE_TWO_LAUNCH\s+(\d+)", open(HEADER).read())
     assert m and int(m.group(1)) == chx.CHX_TUNE_TWO_LAUNCH
+
+
+@pytest.mark.parametrize("missing", ["_cuda_getCurrentRawStream", "_cuda_getDevice", None])
+def test_current_stream_with_and_without_torchs_shortcut(monkeypatch, missing):
+    """The stream handle comes through torch's own shortcut or, where a torch
+    lacks either function of it, through the Stream object."""
+    from types import SimpleNamespace
+    names = {"_cuda_getCurrentRawStream": lambda dev: 100 + dev, "_cuda_getDevice": lambda: 3}
+    names.pop(missing, None)
+    torch = SimpleNamespace(_C=SimpleNamespace(**names), cuda=SimpleNamespace(
+        current_stream=lambda: SimpleNamespace(cuda_stream=42)))
+    monkeypatch.setattr(chx, "_torch", torch)
+    monkeypatch.setattr(chx, "_raw_stream", None, raising=False)
+    for _ in range(2):
+        assert chx._stream(None) == (42 if missing else 103)
+    assert chx._stream(7) == 7
+    assert chx._stream(SimpleNamespace(cuda_stream=9)) == 9
