@@ -612,12 +612,24 @@ int ch_ensemble_k1(chx_ens e, double* const* c_runs, const long* ld_runs,
  *   doubles); reduced-system blocks B_d, d = dlo..dlo+dcount-1, as 2x2
  *   row-major (blocks, capacity blocks_cap doubles); info[0..3] = {m-P, n/m,
  *   dlo, dcount}.  Arrays that are NULL or too small are skipped.
+ * chx_host_ragged_tables: tables for chunks of any length up to M >= 3P (n >=
+ *   3P; CHX_EINVAL otherwise): S chunks, the first S-1 of m <= M unknowns and
+ *   the last of r, 3P <= r <= m; info[0..4] = {m, r, S, dlo, dcount}.  rec as
+ *   above for a chunk of m, recl for the last one (both M-P positions, zero
+ *   beyond the interior; recl's first four values per position are rec's);
+ *   rec_cap doubles each.  blocks: three families of dcount 2x2 blocks, from
+ *   the chunk d after or before along the ring: 0 where the way from one's
+ *   separators to the other's is d chunks of m, 1 where it is m - r more and 2
+ *   where it is m - r less, for it passes the short chunk.
  * chx_host_whole_tables: bordering tables of the whole system: per position
  *   i < mi, {1/alpha, L(i,i-1), R(i,i+1), R(i,i+2), q_0, q_1, Z_0, Z_1}; minv =
  *   [C22 - h^T E^{-1} k]^{-1} (2x2, row-major); *mi_out = n-P (periodic) or n.
  */
 int chx_host_chunk_tables(int P, const double* coef, int n, int m, double* rec,
                           int rec_cap, double* blocks, int blocks_cap, int* info);
+int chx_host_ragged_tables(int P, const double* coef, int n, int M, double* rec,
+                           double* recl, int rec_cap, double* blocks, int blocks_cap,
+                           int* info);
 int chx_host_whole_tables(int P, const double* coef, int n, int periodic,
                           double* rec, int rec_cap, double* minv, int* mi_out);
 

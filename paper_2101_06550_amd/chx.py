@@ -53,7 +53,7 @@ EXPORTED = [
     "ch_ensemble_create", "ch_ensemble_destroy", "ch_ensemble_ws_bytes", "ch_ensemble_step",
     "ch_ensemble_moments", "ch_ensemble_k1", "ch_ensemble_set_noise",
     "ch_ensemble_get_noise_step", "ch_ensemble_get_tuning", "ch_ensemble_set_tuning",
-    "chx_host_chunk_tables", "chx_host_whole_tables",
+    "chx_host_chunk_tables", "chx_host_ragged_tables", "chx_host_whole_tables",
 ]
 
 
@@ -147,6 +147,7 @@ def load(path: str | None = None):
         "ch_ensemble_moments": (_I, [_V, ctypes.POINTER(_V), ctypes.POINTER(_L), _DP, _V]),
         "ch_ensemble_k1": (_I, [_V, ctypes.POINTER(_V), ctypes.POINTER(_L), _DP, _V]),
         "chx_host_chunk_tables": (_I, [_I, _DP, _I, _I, _DP, _I, _DP, _I, _IP]),
+        "chx_host_ragged_tables": (_I, [_I, _DP, _I, _I, _DP, _DP, _I, _DP, _I, _IP]),
         "chx_host_whole_tables": (_I, [_I, _DP, _I, _I, _DP, _I, _DP, _IP]),
     }
     for name, (res, args) in sig.items():
@@ -796,6 +797,25 @@ def chx_host_chunk_tables(P: int, coef, n: int, m: int):
                                      blocks.ctypes.data_as(_DP), blocks.size, info),
            "chunk tables")
     return rec.reshape(mi, 8), blocks.reshape(dcount, 2, 2), dlo
+
+
+def chx_host_ragged_tables(P: int, coef, n: int, M: int):
+    """Host-only: (rec[M-P,8], recl[M-P,8], blocks[3,dcount,2,2], (m, r, S, dlo))
+    of the tables for chunks of any length up to M."""
+    import numpy as np
+    lib = load()
+    cf = (ctypes.c_double * 5)(*[float(v) for v in coef])
+    info = (ctypes.c_int * 5)()
+    _check(lib.chx_host_ragged_tables(P, cf, n, M, None, None, 0, None, 0, info), "ragged tables")
+    m, r, S, dlo, dcount = list(info)
+    rec, recl = np.zeros((M - P) * 8), np.zeros((M - P) * 8)
+    blocks = np.zeros(3 * dcount * 4)
+    _check(lib.chx_host_ragged_tables(P, cf, n, M, rec.ctypes.data_as(_DP),
+                                      recl.ctypes.data_as(_DP), rec.size,
+                                      blocks.ctypes.data_as(_DP), blocks.size, info),
+           "ragged tables")
+    return (rec.reshape(M - P, 8), recl.reshape(M - P, 8), blocks.reshape(3, dcount, 2, 2),
+            (m, r, S, dlo))
 
 
 def chx_host_whole_tables(P: int, coef, n: int, periodic: bool = True):

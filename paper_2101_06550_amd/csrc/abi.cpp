@@ -2901,6 +2901,28 @@ int chx_host_chunk_tables(int P, const double* coef, int n, int m, double* rec, 
   return CHX_OK;
 }
 
+int chx_host_ragged_tables(int P, const double* coef, int n, int M, double* rec, double* recl,
+                           int rec_cap, double* blocks, int blocks_cap, int* info) {
+  if ((P != 1 && P != 2) || !coef || !info || M < 3 * P || n < 3 * P) return CHX_EINVAL;
+  Band band;
+  band.P = P;
+  band.periodic = true;
+  for (int k = 0; k < 2 * P + 1; ++k) band.coef[k] = coef[k];
+  RaggedTables t;
+  int rc = build_ragged(band, n, M, &t);
+  if (rc) return rc;
+  info[0] = t.m;
+  info[1] = t.r;
+  info[2] = t.S;
+  info[3] = t.dlo;
+  info[4] = t.dcount;
+  if (rec && rec_cap >= (int)t.rec.size()) std::memcpy(rec, t.rec.data(), t.rec.size() * 8);
+  if (recl && rec_cap >= (int)t.recl.size()) std::memcpy(recl, t.recl.data(), t.recl.size() * 8);
+  if (blocks && blocks_cap >= (int)t.blocks.size())
+    std::memcpy(blocks, t.blocks.data(), t.blocks.size() * 8);
+  return CHX_OK;
+}
+
 int chx_host_whole_tables(int P, const double* coef, int n, int periodic, double* rec,
                           int rec_cap, double* minv, int* mi_out) {
   if ((P != 1 && P != 2) || !coef || !mi_out) return CHX_EINVAL;

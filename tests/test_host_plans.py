@@ -447,3 +447,96 @@ def test_current_stream_with_and_without_torchs_shortcut(monkeypatch, missing):
         assert chx._stream(None) == (42 if missing else 103)
     assert chx._stream(7) == 7
     assert chx._stream(SimpleNamespace(cuda_stream=9)) == 9
+
+
+# ------------------------------------------------------- chunks of any length
+def replay_ragged(P, coef, f, M):
+    """Replay of a solve in chunks of m unknowns and a last one of r with the
+    library's tables; a block's family follows from how far apart the two
+    chunks' separators lie along the ring."""
+    n, batch = f.shape
+    rec, recl, blocks, (m, r, S, dlo) = chx.chx_host_ragged_tables(P, coef, n, M)
+    assert S * m - (m - r) == n and 3 * P <= r <= m <= M
+    assert np.array_equal(rec[:r - P, :2], recl[:r - P, :2])  # one LR serves both
+    x = np.zeros_like(f)
+    pa, pb, sep = [np.zeros((S, P, batch)) for _ in range(3)]
+    for k in range(S):
+        li = (r if k == S - 1 else m) - P
+        ch = f[k * m:k * m + li + P]
+        g, y = np.zeros((li, batch)), np.zeros((li, batch))
+        for p in range(li):
+            v = ch[p] - (coef[0] * g[p - 2] if P == 2 and p >= 2 else 0)
+            v = v - (rec[p, 1] * g[p - 1] if p >= 1 else 0)
+            g[p] = v * rec[p, 0]
+        for p in range(li - 1, -1, -1):
+            v = g[p] - (rec[p, 3] * y[p + 2] if P == 2 and p + 2 < li else 0)
+            y[p] = v - (rec[p, 2] * y[p + 1] if p + 1 < li else 0)
+        x[k * m:k * m + li] = y
+        for a in range(P):
+            pa[k, a] = ch[li + a] - sum(coef[p - li - a + P] * y[p]
+                                        for p in range(li + a - P, li))
+            pb[k, a] = sum(coef[q + 2 * P - a] * y[q] for q in range(a + 1))
+
+    def place(j):  # of chunk j's separators on the unrolled ring
+        turn, k = divmod(j, S)
+        return turn * n + k * m + (r if k == S - 1 else m) - P
+
+    for k in range(S):
+        for t in range(blocks.shape[1]):
+            j = k + dlo + t
+            off = place(j) - place(k) - (dlo + t) * m
+            fam = {0: 0, m - r: 1, r - m: 2}[off] if m > r else 0
+            sep[k] += blocks[fam, t, :P, :P] @ (pa[j % S] - pb[(j + 1) % S])
+    for k in range(S):
+        z, li = (recl, r - P) if k == S - 1 else (rec, m - P)
+        for p in range(li):
+            x[k * m + p] -= z[p, 4:4 + P] @ sep[k - 1] + z[p, 6:6 + P] @ sep[k]
+        x[k * m + li:k * m + li + P] = sep[k]
+    return x
+
+
+# one chunk; two, the last as short as it may be, or as long as the first;
+# lengths with no even split; a window that leaves blocks out (1001, 2003)
+@pytest.mark.parametrize("M", [8, 16, 32])
+@pytest.mark.parametrize("n", [6, 7, 8, 14, 16, 22, 31, 33, 37, 38, 64, 65, 97, 100, 257, 1001,
+                               2003])
+def test_ragged_replay_matches_oracle(orc, n, M):
+    for P, co, cond in ((2, penta(0.5), 9), (2, penta(70.547), 1130),
+                        (2, (0.21, -0.7, 3.9, 0.45, -0.33), 9), (1, (-0.5, 2.0, -0.5), 4),
+                        (1, (0.4, 2.5, -0.7), 4)):
+        # s chunks of q but for a last one of n - (s - 1) q
+        if not any(3 * P <= n - (s - 1) * q <= q for s in range(1, n + 1)
+                   for q in range(3 * P, M + 1)):
+            with pytest.raises(chx.ChxError):
+                chx.chx_host_ragged_tables(P, co, n, M)
+            continue
+        f = inputs.uniform(24 + n, (n, 3), -1, 1)
+        x = replay_ragged(P, co, f, M)
+        solve = orc.cyclic_penta_solve if P == 2 else orc.cyclic_tri_solve
+        ref = np.stack([solve(co, f[:, s]) for s in range(3)], axis=1)
+        # two FP64 direct solvers differ by at most ~ kappa * eps
+        tol = max(1e-13, 20 * 2.2e-16 * cond)
+        assert np.max(np.abs(x - ref)) < tol * np.max(np.abs(ref)), (P, co)
+
+
+def test_ragged_window_is_cut_and_an_even_split_gives_the_chunk_tables():
+    co = penta(0.5)
+    rec, _, blocks, (m, r, S, dlo) = chx.chx_host_ragged_tables(2, co, 2003, 16)
+    assert blocks.shape[1] < S and m > r
+    crec, cblocks, cdlo = chx.chx_host_chunk_tables(2, co, 2048, 32)
+    erec, erecl, eblocks, (em, er, eS, edlo) = chx.chx_host_ragged_tables(2, co, 2048, 32)
+    assert (em, er, eS, edlo) == (32, 32, 64, cdlo)
+    assert np.array_equal(erec, crec) and np.array_equal(erecl, crec)
+    for fam in range(3):
+        assert np.array_equal(eblocks[fam], cblocks)
+
+
+def test_ragged_tables_reject_bad_arguments(lib):
+    import ctypes
+    co = (ctypes.c_double * 5)(*penta(0.5))
+    info = (ctypes.c_int * 5)()
+    for P, n, M in ((2, 5, 32), (2, 64, 5), (2, 64, 0), (1, 2, 8), (3, 64, 32)):
+        assert lib.chx_host_ragged_tables(P, co, n, M, None, None, 0, None, 0,
+                                          info) == chx.CHX_EINVAL
+    assert lib.chx_host_ragged_tables(2, None, 64, 32, None, None, 0, None, 0,
+                                      info) == chx.CHX_EINVAL
