@@ -190,3 +190,44 @@ def test_thesis_steps_of_any_grid(chx, orc, ny, nx, n):  # noqa: F811
     assert rel(out[1][:, :nx], p) < 4 ** n * tol
     if n == 1:
         assert np.array_equal(out[1][:, :nx], c0)
+
+
+# the even splits into 16- and 32-point chunks, columns and rows, and tiles of 8
+# and 16 columns over the other kind of split than GRIDS has
+EVEN = [(2000, 70), (4096, 70), (70, 4000), (70, 8000), (504, 2049), (121, 4097)]
+
+
+@pytest.mark.parametrize("ny,nx", EVEN)
+def test_even_chunks_of_either_direction(chx, orc, ny, nx):  # noqa: F811
+    """test_steps_of_any_grid on these grids; the steps without diagnostics
+    are bit for bit those with."""
+    test_steps_of_any_grid(chx, orc, ny, nx)
+    L = 2 * math.pi
+    c0 = inputs.noise_field(ny, nx, 95)
+    h = chx.ch_create(nx, ny, L, L, 1.0, 0.01, 1e-6)
+    assert chx.ch_get_tuning(h, chx.CHX_TUNE_TWO_LAUNCH) == 1
+    outs = []
+    for d in (None, torch.zeros(8, dtype=torch.float64, device="cuda")):
+        c = torch.tensor(c0, device="cuda")
+        chx.ch_adi_step(h, c, nsteps=3, diag_out=d)
+        torch.cuda.synchronize()
+        outs.append(c.cpu().numpy())
+    assert np.array_equal(*outs)
+
+
+@pytest.mark.parametrize("ny,nx", [(70, 4000), (70, 8000), (2000, 70)])
+def test_even_chunks_of_the_thesis_step(chx, orc, ny, nx):  # noqa: F811
+    """test_thesis_steps_of_any_grid on these grids, and without diagnostics
+    the same bits."""
+    test_thesis_steps_of_any_grid(chx, orc, ny, nx, 3)
+    L = 2 * math.pi
+    c0, p0 = inputs.noise_field(ny, nx, 96), inputs.noise_field(ny, nx, 97)
+    h = chx.ch_create(nx, ny, L, L, 1.0, 0.01, 1e-6, scheme=chx.CHX_SCHEME_P2)
+    assert chx.ch_get_tuning(h, chx.CHX_TUNE_TWO_LAUNCH) == 1
+    outs = []
+    for d in (None, torch.zeros(8, dtype=torch.float64, device="cuda")):
+        c, p = torch.tensor(c0, device="cuda"), torch.tensor(p0, device="cuda")
+        chx.ch_adi_step_p2(h, c, p, nsteps=3, diag_out=d)
+        torch.cuda.synchronize()
+        outs.append((c.cpu().numpy(), p.cpu().numpy()))
+    assert np.array_equal(outs[0][0], outs[1][0]) and np.array_equal(outs[0][1], outs[1][1])

@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 
 from paper_2101_06550_amd import inputs
-from test_gpu_solves import chx  # noqa: F401
+from test_gpu_solves import chx, rel  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
@@ -161,3 +161,71 @@ def test_graph_choice_replays_the_two_launch_step(chx, ny, nx, small):  # noqa: 
         outs.append((c.cpu().numpy(), d.cpu().numpy()))
     for o in outs[1:]:
         assert same(o, outs[0])
+
+
+# (ny, nx, two launches, single workgroup, graph): every way a P1 FP64 step runs
+WAYS = [(128, 128, 1, 0, 0), (128, 128, 1, 0, 1), (128, 128, 0, 1, 0), (128, 128, 0, 0, 0),
+        (128, 128, 0, 0, 1), (1024, 1024, 1, 0, 1), (1024, 1024, 0, 0, 0), (1024, 1024, 0, 0, 1),
+        (90, 203, 1, 0, 0), (90, 203, 0, 0, 0)]
+
+
+def handle_for(chx, ny, nx, two, small, graph, dt):  # noqa: F811
+    h = chx.ch_create(nx, ny, L, L, 1.0, 0.01, dt)
+    if nx % 64 == 0 and nx * ny <= 16384:
+        chx.ch_set_tuning(h, small, what=chx.CHX_TUNE_SMALL_PATH)
+    chx.ch_set_tuning(h, two, what=chx.CHX_TUNE_TWO_LAUNCH)
+    chx.ch_set_tuning(h, graph, what=chx.CHX_TUNE_GRAPH)
+    return h
+
+
+@pytest.mark.parametrize("ny,nx,two,small,graph", WAYS)
+def test_every_way_keeps_to_the_columns_of_a_padded_field(chx, orc, ny, nx, two, small,  # noqa: F811
+                                                          graph):
+    """Two calls of one step in a field of leading dimension nx + 72: the
+    oracle's result, the padding as it was."""
+    dt = 1e-6
+    c0 = inputs.noise_field(ny, nx, 36)
+    h = handle_for(chx, ny, nx, two, small, graph, dt)
+    big = torch.full((ny, nx + 72), 7.0, dtype=torch.float64, device="cuda")
+    big[:, :nx] = torch.tensor(c0, device="cuda")
+    ws = torch.empty(chx.ch_ws_bytes(h) + 256, dtype=torch.uint8, device="cuda")
+    print(f"[case] padded field {ny}x{nx} two {two} small {small} graph {graph}", flush=True)
+    for _ in range(2):
+        chx.ch_adi_step(h, big, nsteps=1, ws=ws)
+    torch.cuda.synchronize()
+    b = big.cpu().numpy()
+    ref = orc.ch_step(orc.ch_step(c0, L, L, 1.0, 0.01, dt), L, L, 1.0, 0.01, dt)
+    assert rel(b[:, :nx], ref) < 2e-12
+    assert np.all(b[:, nx:] == 7.0)
+
+
+@pytest.mark.parametrize("ny,nx,two,small,graph", WAYS)
+def test_every_way_refuses_bad_arguments_before_it_writes(chx, orc, ny, nx, two, small,  # noqa: F811
+                                                          graph):
+    """Through the C-ABI: a null field, ld < nx, nsteps < 1 and a workspace
+    missing, short or off its alignment are refused with their codes, the
+    field and the next valid call are as if they had not been made."""
+    lib = chx.load()
+    dt = 1e-6
+    c0 = inputs.noise_field(ny, nx, 37)
+    h = handle_for(chx, ny, nx, two, small, graph, dt)
+    c = torch.tensor(c0, device="cuda")
+    need = lib.ch_ws_bytes(h.handle)
+    ws = torch.zeros(need + 512, dtype=torch.uint8, device="cuda")
+    aligned = (ws.data_ptr() + 255) // 256 * 256
+    st = chx._stream(None)
+    print(f"[case] bad arguments {ny}x{nx} two {two} small {small} graph {graph}", flush=True)
+    good = dict(c=c.data_ptr(), ld=nx, nsteps=2, ws=aligned, avail=need)
+    for over, code in ((dict(c=None), chx.CHX_EINVAL), (dict(ld=nx - 1), chx.CHX_EINVAL),
+                       (dict(nsteps=0), chx.CHX_EINVAL), (dict(nsteps=-3), chx.CHX_EINVAL),
+                       (dict(ws=None), chx.CHX_ENOMEM), (dict(avail=need - 8), chx.CHX_ENOMEM),
+                       (dict(ws=aligned + 8), chx.CHX_EINVAL)):
+        a = dict(good, **over)
+        rc = lib.ch_adi_step(h.handle, a["c"], a["ld"], a["nsteps"], None, a["ws"], a["avail"], st)
+        assert rc == code, (over, rc)
+    torch.cuda.synchronize()
+    assert np.array_equal(c.cpu().numpy(), c0)
+    assert lib.ch_adi_step(h.handle, good["c"], nx, 2, None, aligned, need, st) == chx.CHX_OK
+    torch.cuda.synchronize()
+    ref = orc.ch_step(orc.ch_step(c0, L, L, 1.0, 0.01, dt), L, L, 1.0, 0.01, dt)
+    assert rel(c.cpu().numpy(), ref) < 2e-12
