@@ -231,3 +231,22 @@ def test_even_chunks_of_the_thesis_step(chx, orc, ny, nx):  # noqa: F811
         torch.cuda.synchronize()
         outs.append((c.cpu().numpy(), p.cpu().numpy()))
     assert np.array_equal(outs[0][0], outs[1][0]) and np.array_equal(outs[0][1], outs[1][1])
+
+
+@pytest.mark.parametrize("kind,n,batch,L,dt,a,D", [
+    (0, 2080, 20, 1.0, 1e-14, 1.0, 1.0), (0, 4096, 65, 1.0, 1e-15, 1.0, 1.0),
+    (1, 2080, 33, 1.0, 1e-7, 1.0, 1.0), (1, 4096, 20, 1.0, 1e-8, 1.0, 1.0),
+    (2, 2080, 65, 2 * math.pi, 1e-6, 0.01, 1.0), (2, 4096, 20, 2 * math.pi, 1e-7, 0.01, 1.0),
+    (1, 2049, 17, 1.0, 1e-7, 1.0, 1.0)])
+def test_steps_of_systems_longer_than_a_workgroup_holds(chx, orc, kind, n, batch, L, dt, a,  # noqa: F811
+                                                        D):
+    """The stepwise kernels, which shorter systems no longer take."""
+    test_steps_in_one_call(chx, orc, kind, n, batch, L, dt, a, D)
+
+
+@pytest.mark.parametrize("n", [2080, 4096])
+def test_solves_of_systems_longer_than_a_workgroup_holds(chx, orc, n):  # noqa: F811
+    """The three chunked passes of the interleaved solve, which shorter
+    systems no longer take."""
+    for layout in (0, 1):
+        test_any_length(chx, orc, n, layout)
