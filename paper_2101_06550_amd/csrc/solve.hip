@@ -1693,11 +1693,12 @@ hipError_t launch_rows_lds(const DevChunk& c, double* x, long ld, int rows, hipS
   const long ngroups = ((long)rows + R - 1) / R;
   // dense rows in whole groups of 256 chunks: the half-tile kernel
   const bool half = kRowsHalfTile && P == 2 && ld == c.n && 256 % c.S == 0 && rows % R == 0;
-  // streamed solves of more groups than the CUs hold at once find the table in
-  // the cache after the first round, and fetching it again holds up their
-  // loads (us without and with: 1250 groups 26.8 and 30.3, 2048 48.9 and 47.5;
-  // 256 groups 9.0 and 8.4, 768 14.3 and 13.5)
-  if (half && c.M == kChunk && stream_in && ngroups > 1024)
+  // streamed solves of about one and a half rounds of workgroups (three to a
+  // CU) wait longer for the table than it saves; shorter and longer ones gain
+  // (us without and with it: 256 groups 9.0 and 8.4, 768 14.3 and 13.5, 1024
+  // 22.1 and 21.8, 1088 23.9 and 25.4, 1250 26.8 and 30.3, 1280 28.6 and 30.5,
+  // 1536 35.5 and 35.9, 1800 43.5 and 42.5, 3072 74.0 and 72.2)
+  if (half && c.M == kChunk && stream_in && ngroups > 1024 && ngroups < 1536)
     hipLaunchKernelGGL((row_solve_half<2, kChunk, true, false>), dim3((unsigned)ngroups),
                        dim3(256), 0, st, x, c.S, c.rec, band_of<double>(c.coef), c.blocks, c.dlo,
                        c.dcount);
