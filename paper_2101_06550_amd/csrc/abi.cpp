@@ -315,7 +315,8 @@ hipError_t solve_refined(const BandPlan* p, int batch, double* x, long ld, int l
 
 // FP64 solves in place.  Interleaved: one launch where a workgroup holds whole
 // systems, the chunked passes for longer ones, one thread per system where
-// neither applies (no tables, or no rho for the chunked passes).  Contiguous: rows through LDS up to 256 chunks.
+// neither applies (no tables, or no rho for the chunked passes).  Contiguous:
+// rows through LDS up to 256 chunks.
 hipError_t solve_il(const BandPlan* p, double* x, long ld, int batch, double* rho,
                     hipStream_t st) {
   if (p->has_chunk && il_fused_systems(p->dchunk.S, batch) > 0)
@@ -1813,7 +1814,8 @@ static int run_steps(chx_ch h, double* c, long ld, int nsteps, double* diag_out,
       if (ok()) {
         tail.out = diag_out ? diag_out + 2 * n : nullptr;
         B();
-        e = launch_rows_any(h->px->dragged, r, nx, c, ld, ny, diag_out ? &tail : nullptr, false, st);
+        e = launch_rows_any(h->px->dragged, r, nx, c, ld, ny, diag_out ? &tail : nullptr, false,
+                            st);
         E(2);
       }
     }

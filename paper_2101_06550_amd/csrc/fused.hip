@@ -113,8 +113,8 @@ __device__ __forceinline__ void ragged_parts(const double (&f)[M], const double 
   }
 }
 
-// x = y - Zl sp - Zr so in the interior.  A wave that holds last chunks runs both tables, each chunk's separators masked to
-// zero for the other's.
+// x = y - Zl sp - Zr so in the interior.  A wave that holds last chunks runs
+// both tables, each chunk's separators masked to zero for the other's.
 template <int P, int M>
 __device__ __forceinline__ void ragged_correct(double (&f)[M], bool last, TabD rec, TabD recl,
                                                const double (&sp)[P], const double (&so)[P]) {

@@ -590,8 +590,8 @@ hipError_t launch_rstep_first(const double* c, long ld, double* rbuf, float* y32
   RBufs B{};
   for (int b = 0; b < nbprev; ++b) B.v[b] = vprev[b];
 #define CHX_RFIRST(D_, NB_)                                                                     \
-  hipLaunchKernelGGL((rstep_first<D_, NB_>), rstep_grid(nx, ny), rstep_block(nx, ny), 0, st, c, ld, rbuf, \
-                     y32, rho, nx, ny, nseg, cy.rec32, bd, K, part, B, cy.S, cy.rec)
+  hipLaunchKernelGGL((rstep_first<D_, NB_>), rstep_grid(nx, ny), rstep_block(nx, ny), 0, st, c, \
+                     ld, rbuf, y32, rho, nx, ny, nseg, cy.rec32, bd, K, part, B, cy.S, cy.rec)
   const bool d = part != nullptr;
   switch (nbprev) {
     case 0: if (d) CHX_RFIRST(true, 0); else CHX_RFIRST(false, 0); break;
@@ -619,8 +619,8 @@ hipError_t launch_rstep_resid(const double* rbuf, const float* const* v, int nb,
   for (int b = 0; b < nb; ++b) B.v[b] = v[b];
   const int nseg = (nx + kSegR - 1) / kSegR;
 #define CHX_RRES(NB_)                                                                           \
-  hipLaunchKernelGGL((rstep_resid<NB_>), rstep_grid(nx, ny), rstep_block(nx, ny), 0, st, rbuf, B, y32, rho, \
-                     nx, ny, nseg, cy.S, cy.rec, cy.rec32, bd, ax, ay)
+  hipLaunchKernelGGL((rstep_resid<NB_>), rstep_grid(nx, ny), rstep_block(nx, ny), 0, st, rbuf, B, \
+                     y32, rho, nx, ny, nseg, cy.S, cy.rec, cy.rec32, bd, ax, ay)
   if (nb == 1) CHX_RRES(1);
   else if (nb == 2) CHX_RRES(2);
   else CHX_RRES(3);
@@ -636,8 +636,8 @@ hipError_t launch_rstep_final(const float* const* v, int nb, double* c, long ld,
   for (int b = 0; b < nb; ++b) B.v[b] = v[b];
   const int nseg = (nx + kSegR - 1) / kSegR;
 #define CHX_RFIN(NB_, D_)                                                                         \
-  hipLaunchKernelGGL((rstep_final<NB_, D_>), rstep_grid(nx, ny), rstep_block(nx, ny), 0, st, B, c, ld, nx, \
-                     ny, nseg, cy.S, cy.rec, K, part)
+  hipLaunchKernelGGL((rstep_final<NB_, D_>), rstep_grid(nx, ny), rstep_block(nx, ny), 0, st, B, \
+                     c, ld, nx, ny, nseg, cy.S, cy.rec, K, part)
   if (diag_out) {
     if (nb == 1) CHX_RFIN(1, true);
     else if (nb == 2) CHX_RFIN(2, true);

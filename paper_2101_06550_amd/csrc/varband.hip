@@ -1089,11 +1089,13 @@ void rewrite(int n, int batch, long ld, const Columns<S::kBands + 1>& in, double
       return;
     case Rewrite::kOnce4:
       if constexpr (!S::kPeriodic)
-        hipLaunchKernelGGL((rewrite_once_k<S, 4>), grid, block, 0, st, n, batch, ld, in, x, ws, ldw);
+        hipLaunchKernelGGL((rewrite_once_k<S, 4>), grid, block, 0, st, n, batch, ld, in, x, ws,
+                           ldw);
       return;
     case Rewrite::kOnce8:
       if constexpr (!S::kPeriodic)
-        hipLaunchKernelGGL((rewrite_once_k<S, 8>), grid, block, 0, st, n, batch, ld, in, x, ws, ldw);
+        hipLaunchKernelGGL((rewrite_once_k<S, 8>), grid, block, 0, st, n, batch, ld, in, x, ws,
+                           ldw);
       return;
     case Rewrite::kTwice4x2:
       hipLaunchKernelGGL((rewrite_twice_k<S, 4, 2>), grid, block, 0, st, n, batch, ld, in, x, ws,
