@@ -877,81 +877,14 @@ __global__ __launch_bounds__(kWave, 1) void rewrite_twice_k(int n, int batch, lo
   S::finish(n, ld, lane, t, x);
 }
 
-// Kept factors, one group of rows loaded and worked on at a time: fewer
-// instructions a row than the kernels above, which is what a batch of one
-// wave waits for as long as its rows come out of the cache.
-__global__ __launch_bounds__(kThreads) void penta_rewrite_plain_k(
-    int n, int batch, long ld, const double* __restrict__ a, const double* __restrict__ b,
-    const double* __restrict__ c, const double* __restrict__ d, const double* __restrict__ e,
-    double* __restrict__ x, double* __restrict__ ws, long ldw) {
-  const long s = (long)blockIdx.x * kThreads + threadIdx.x;
-  if (s >= batch) return;
-  const int m = n - 2;
-  PentaTail tl{};
-  penta_load_tail<true, true>(n, ld, s, a, b, c, d, e, x, tl);
-  double* gm = ws;
-  double* dl = ws + (long)m * ldw;
-  double* p0 = ws + 2L * m * ldw;
-  double* p1 = ws + 3L * m * ldw;
-  PentaFwd st;
-  int i = 0;
-  for (; i + kU <= m; i += kU) {
-    double va[kU], vb[kU], vc[kU], vd[kU], ve[kU], vf[kU];
-#pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      const long r = (long)(i + u) * ld + s;
-      va[u] = __builtin_nontemporal_load(&a[r]);
-      vb[u] = __builtin_nontemporal_load(&b[r]);
-      vc[u] = __builtin_nontemporal_load(&c[r]);
-      vd[u] = __builtin_nontemporal_load(&d[r]);
-      ve[u] = __builtin_nontemporal_load(&e[r]);
-      vf[u] = __builtin_nontemporal_load(&x[r]);
-    }
-#pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      double beta, inv, gam, del, g, pk0, pk1, wh0, wh1;
-      penta_fwd_row<true, true>(i + u, m, va[u], vb[u], vc[u], vd[u], ve[u], vf[u], tl, st, beta,
-                               inv, gam, del, g, pk0, pk1, wh0, wh1);
-      const long rw = (long)(i + u) * ldw + s;
-      x[(long)(i + u) * ld + s] = g;
-      gm[rw] = gam;
-      dl[rw] = del;
-      p0[rw] = pk0;
-      p1[rw] = pk1;
-    }
-  }
-  for (; i < m; ++i) {
-    const long r = (long)i * ld + s;
-    double beta, inv, gam, del, g, pk0, pk1, wh0, wh1;
-    penta_fwd_row<true, true>(i, m, a[r], b[r], c[r], d[r], e[r], x[r], tl, st, beta, inv, gam,
-                             del, g, pk0, pk1, wh0, wh1);
-    const long rw = (long)i * ldw + s;
-    x[r] = g;
-    gm[rw] = gam;
-    dl[rw] = del;
-    p0[rw] = pk0;
-    p1[rw] = pk1;
-  }
-  double mi[4];
-  penta_minv(tl, st, mi);
-  const double r0 = tl.f0 - st.s0, r1 = tl.f1 - st.s1;
-  const double t0 = mi[0] * r0 + mi[1] * r1;
-  const double t1 = mi[2] * r0 + mi[3] * r1;
-  penta_back<kU, true>(m, s, gm, ldw, dl, ldw, p0, p1, ldw, t0, t1, x, ld);
-  x[(long)(n - 2) * ld + s] = t0;
-  x[(long)(n - 1) * ld + s] = t1;
-}
-
-template <bool PER>
+// Kept factors, one group of rows loaded and worked on at a time, for
+// tridiagonal systems that are not periodic: 64 bytes a row where bandwidth
+// bounds, against 72 of the kernels above.
 __global__ __launch_bounds__(kThreads) void tri_rewrite_plain_k(
     int n, int batch, long ld, const double* __restrict__ a, const double* __restrict__ b,
     const double* __restrict__ c, double* __restrict__ x, double* __restrict__ ws, long ldw) {
   const long s = (long)blockIdx.x * kThreads + threadIdx.x;
   if (s >= batch) return;
-  const double a0 = PER ? a[s] : 0.0, b0 = PER ? b[s] : 0.0;
-  const double cl = PER ? c[(long)(n - 1) * ld + s] : 0.0;
-  double* chv = ws;
-  double* zu = PER ? ws + (long)n * ldw : nullptr;
   TriFwd st;
   int i = 0;
   for (; i + kU <= n; i += kU) {
@@ -967,25 +900,20 @@ __global__ __launch_bounds__(kThreads) void tri_rewrite_plain_k(
 #pragma unroll
     for (int u = 0; u < kU; ++u) {
       double inv, ch, y, z, w;
-      tri_fwd_row<PER, true>(i + u, n, va[u], vb[u], vc[u], vf[u], a0, b0, cl, st, inv, ch, y,
-                             z, w);
-      const long rw = (long)(i + u) * ldw + s;
+      tri_fwd_row<false, true>(i + u, n, va[u], vb[u], vc[u], vf[u], 0.0, 0.0, 0.0, st, inv, ch,
+                               y, z, w);
       x[(long)(i + u) * ld + s] = y;
-      chv[rw] = ch;
-      if (PER) zu[rw] = z;
+      ws[(long)(i + u) * ldw + s] = ch;
     }
   }
   for (; i < n; ++i) {
     const long r = (long)i * ld + s;
     double inv, ch, y, z, w;
-    tri_fwd_row<PER, true>(i, n, a[r], b[r], c[r], x[r], a0, b0, cl, st, inv, ch, y, z, w);
-    const long rw = (long)i * ldw + s;
+    tri_fwd_row<false, true>(i, n, a[r], b[r], c[r], x[r], 0.0, 0.0, 0.0, st, inv, ch, y, z, w);
     x[r] = y;
-    chv[rw] = ch;
-    if (PER) zu[rw] = z;
+    ws[(long)i * ldw + s] = ch;
   }
-  const double phi = PER ? st.sy / (1.0 + st.sz) : 0.0;
-  tri_back<kU, PER>(n, s, chv, ldw, zu, ldw, phi, x, ld);
+  tri_back<kU, false>(n, s, ws, ldw, nullptr, ldw, 0.0, x, ld);
 }
 
 // ---------------------------------------------------------------------------
@@ -1035,41 +963,49 @@ dim3 grid_of(int batch) { return dim3((unsigned)((batch + kThreads - 1) / kThrea
 //    0.304 against 0.347; two groups of 8 above, 256 x 100000 0.301 against
 //    0.352) until the factors pass the last-level cache (1024 x 65536 0.82
 //    twice, 0.84 kept).
-//  - at most a wave of systems: plain while a periodic batch is small (us, 100 x
-//    64: tri 22.8 against 28.4 twice, penta 32.1 against 36.0; 1024 x 1: tri 206
-//    against 233, penta 320 against 336; but 256 x 64, by where its arrays lie:
-//    tri 52 to 90 against 58), and for all tridiagonals that are not periodic
-//    (256 x 1: 34.3 against 44.7; 1024 x 64: 143 against 168).
+//    Past three waves a CU the waves hide what each waits for, so the plain
+//    kernel's bytes decide past 48 rows (100 x 55000: 73 us against 77).
+//  - kept factors in groups of 8 rows rather than 4 for tridiagonals from 64
+//    rows on: with one wave per SIMD the loads of 4 rows are not back in time
+//    (us, arrays in L2 and not: 256 x 64 45 and 46 against 46 and 59, 1000 x
+//    4096 167 and 168 against 211 and 220).  Plain takes 36 and 77 at 256 x 64
+//    and 240 and 294 at 1000 x 64: it has nothing in flight while it computes.
+//    Shorter systems are over before it matters (56 x 64: 15.1 and 14.9
+//    against 13.9 and 17.0, 8 x 200: 10.7 and 7.3 against 10.6 and 6.7); past three waves a CU 4 are as good (100 x
+//    200000: 233 against 250).
+//  - few periodic systems likewise: twice 31 and 31 us, plain 24 and 47 (tri of
+//    100 x 64), 39 and 39, 36 and 46 (penta).
 //  - groups of 4 rows for the pentadiagonal below half a wave per SIMD, where
 //    the smaller kernel keeps clear of the accumulation registers (1024 x
 //    16384: 0.337 against 0.353), of 8 above (1024 x 65536: 1.31 against
 //    1.37); the tridiagonal fits at 8 (1024 x 16384: 0.228 against 0.264).
-//  - short systems: blocks of 16 rows below 64 and of 8 up to 8, as a block's
-//    loads are issued whether or not it has the rows (us, periodic, 100000
+//  - short systems: blocks of 16 rows up to 48 and of 8 up to 8, as a block's
+//    loads are issued whether or not it has the rows; 49 to 64 rows fill the same
+//    64 in blocks of 32, and more states would be stored (us, periodic, 100000
 //    systems: penta of 8 rows 15.0 in blocks of 8, 22.0 of 16, 37.2 of 32, 19.3
 //    plain; of 16 32.6, 30.8, 46.7; tri of 8 10.0, 13.7, 23.0, of 40 50.4 of 16
 //    and 60.6 of 32).
 constexpr int kTwiceBatch = 16384, kTwiceRows = 256, kWideBatch = 32768;
 constexpr int kBandwidthBatch = 3 * 256 * kWave, kSimdBatch = 4 * 256 * kWave;
-constexpr int kCachedRows = 768, kShortRows = 64, kTinyRows = 8;
-constexpr long kLoneRows = 8000;
+constexpr int kCachedRows = 768, kGroupRows = 64, kShortRows = 48, kTinyRows = 8;
 
 enum class Rewrite { kPlain, kOnce4, kOnce8, kTwice4x2, kTwice4x4, kTwice8x4 };
 
 template <class S>
 Rewrite rewrite_kind(int n, int batch) {
   constexpr bool tri = S::kBands == 3;
-  if (batch <= kWave && (S::kPeriodic ? n * (long)batch < kLoneRows : tri)) return Rewrite::kPlain;
   if (S::kPeriodic) {
-    if ((tri ? n : n - 2) <= kTinyRows) return Rewrite::kTwice4x2;
-    if (n < kShortRows || (!tri && batch < kWideBatch)) return Rewrite::kTwice4x4;
+    const int m = tri ? n : n - 2;
+    if (m <= kTinyRows) return Rewrite::kTwice4x2;
+    if (m <= kShortRows || (!tri && batch < kWideBatch)) return Rewrite::kTwice4x4;
     return Rewrite::kTwice8x4;
   }
-  if (batch < kTwiceBatch || n < kTwiceRows) return Rewrite::kOnce4;
-  if (tri && batch > kBandwidthBatch) {
-    if (batch < kSimdBatch) return Rewrite::kPlain;
-    if (n < kCachedRows) return Rewrite::kOnce8;
-  }
+  const bool kept = batch < kTwiceBatch || n < kTwiceRows;
+  if (tri && n > kShortRows && batch > kBandwidthBatch && batch < kSimdBatch)
+    return Rewrite::kPlain;
+  if (tri && n >= kGroupRows && (batch > kBandwidthBatch ? !kept && n < kCachedRows : kept))
+    return Rewrite::kOnce8;
+  if (kept) return Rewrite::kOnce4;
   return !tri && batch < kWideBatch ? Rewrite::kTwice4x4 : Rewrite::kTwice8x4;
 }
 
@@ -1080,12 +1016,9 @@ void rewrite(int n, int batch, long ld, const Columns<S::kBands + 1>& in, double
   const long ldw = ws_ld(batch);
   switch (rewrite_kind<S>(n, batch)) {
     case Rewrite::kPlain:
-      if constexpr (S::kBands == 3)
-        hipLaunchKernelGGL(tri_rewrite_plain_k<S::kPeriodic>, grid_of(batch), dim3(kThreads), 0, st,
-                           n, batch, ld, in.p[0], in.p[1], in.p[2], x, ws, ldw);
-      else if constexpr (S::kPeriodic)
-        hipLaunchKernelGGL(penta_rewrite_plain_k, grid_of(batch), dim3(kThreads), 0, st, n,
-                           batch, ld, in.p[0], in.p[1], in.p[2], in.p[3], in.p[4], x, ws, ldw);
+      if constexpr (S::kBands == 3 && !S::kPeriodic)
+        hipLaunchKernelGGL(tri_rewrite_plain_k, grid_of(batch), dim3(kThreads), 0, st, n, batch, ld,
+                           in.p[0], in.p[1], in.p[2], x, ws, ldw);
       return;
     case Rewrite::kOnce4:
       if constexpr (!S::kPeriodic)

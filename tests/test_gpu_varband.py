@@ -251,12 +251,14 @@ def test_rewrite_at_group_block_and_batch_edges(chx, orc, n, batch, periodic):
 
 
 # ... and of the lengths and batches at which the kernel changes again: blocks
-# of 8 and 16 rows for short systems, at most a wave of systems, and
+# of 8 and 16 rows for short systems, groups of 8 rows for longer ones, and
 # tridiagonal batches past three waves a CU
-ROUTES = [(n, b, True) for n in (7, 8, 9, 10, 11, 62, 63, 64) for b in (66, 33000)] + \
+ROUTES = [(n, b, True) for n in (7, 8, 9, 10, 11, 48, 49, 50, 51) for b in (66, 33000)] + \
          [(n, b, per) for n in (30, 124, 125) for b in (1, 64, 65) for per in (False, True)] + \
          [(n, b, False) for n in (256, 300) for b in (49152, 49153, 65535, 65536)] + \
-         [(n, 65536, False) for n in (255, 767, 768)] + [(499, 16, True), (500, 16, True)]
+         [(n, 65536, False) for n in (255, 767, 768)] + [(499, 16, True), (500, 16, True)] + \
+         [(n, b, False) for n in (48, 49, 63, 64, 71) for b in (64, 49152, 49153, 65535, 65536)] + \
+         [(255, b, False) for b in (16384, 49152, 49153, 65535)]
 
 
 @pytest.mark.parametrize("n,batch,periodic", ROUTES)
