@@ -566,13 +566,15 @@ hipError_t launch_ens_rstep_final(const EnsRun* runs, const EnsClasses& cls, con
 int rstep_segments(int nx) { return (nx + kSegR - 1) / kSegR; }
 long rstep_parts(int nx, int ny) { return (long)rstep_segments(nx) * (ny / M); }
 
-// (segment, chunk) pairs per block: four, or one on grids of long rows whose
-// pairs do not fill the SIMDs twice, so that every CU gets some (means over one
-// and five steps of one and two passes, against four: 64 x 1024 0.97, 64 x 8192
-// 0.96, 1024^2 0.98); on short rows a block's four pairs are most of the columns
-// two chunks share (128^2 1.14 with one, 2048 x 64 1.10, 256 x 256 1.14).
+// (segment, chunk) pairs per block: four, or one where the pairs do not fill the
+// SIMDs twice, so that every CU gets some (means over one and four steps of one
+// and two passes, against four: 320 x 352 0.94, 768^2 0.98, 1088 x 1952 0.98, 4096
+// x 128 0.94, 1024^2 0.97).  Short rows of a power of two keep four, most of the
+// columns two chunks share (128^2 1.11 with one, 256^2 1.11, 64 x 8192 1.14; 512^2
+// 1.00).
 static int rstep_waves(int nx, int ny) {
-  return nx >= 1024 && rstep_parts(nx, ny) < 2048 ? 1 : 4;
+  const bool spread = nx >= 1024 || 256 % (nx / M);
+  return spread && rstep_parts(nx, ny) < 2048 ? 1 : 4;
 }
 static dim3 rstep_block(int nx, int ny) { return dim3(64 * rstep_waves(nx, ny)); }
 static dim3 rstep_grid(int nx, int ny) {

@@ -1740,10 +1740,14 @@ hipError_t launch_rows_lds32(const DevChunk& c, const double* src, long lds, dou
 
 hipError_t launch_rows_lds_f32(const DevChunk& c, const float* src, float* dst, int rows,
                                hipStream_t st) {
-  // as many rows per workgroup as it holds (fewer to a workgroup on small grids,
-  // two workgroups per CU, steps of 128 x 128 to 4096 x 128 1.10 to 1.15 times
-  // as long: a workgroup is four waves whatever it holds)
-  const int R = 256 / c.S;
+  // As many rows per workgroup as it holds: two workgroups per CU take 1.10 to
+  // 1.15 times as long for steps of 128 x 128 to 4096 x 128, as a workgroup is
+  // four waves whatever it holds.  Where the rows' chunks do not fill its 256
+  // threads it stages element by element, not in 16-byte pieces, and fewer
+  // rows are through sooner (steps of 320 x 352 0.94 of the time, 448 x 832 and
+  // 1216 x 1504 0.97, 1536^2 0.97).
+  int R = 256 / c.S;
+  if (256 % c.S && rows / 512 < R) R = rows / 512 > 1 ? rows / 512 : 1;
   const long ngroups = ((long)rows + R - 1) / R;
   hipLaunchKernelGGL((row_solve_lds_f32<2, kChunk>), dim3((unsigned)ngroups), dim3(256), 0, st,
                      src, (long)c.n, dst, (long)c.n, rows, c.n, c.S, R, c.rec32,

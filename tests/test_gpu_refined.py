@@ -110,6 +110,20 @@ def test_adi_step_refined(chx, orc, n, dt, passes):
     assert rel(c.cpu().numpy(), orc.ch_step(c0, L, L, 1.0, 0.01, dt)) < TARGET
 
 
+# Rows whose chunks fill a workgroup or do not, one or more to a workgroup, in
+# whole and part groups; one and four (segment, chunk) pairs to a block
+@pytest.mark.parametrize("ny,nx", [(32, 448), (352, 320), (1056, 192), (1056, 256), (1568, 960),
+                                   (64, 2048), (96, 8192)])
+def test_adi_step_refined_at_row_group_and_block_edges(chx, orc, ny, nx):
+    c0 = inputs.noise_field(ny, nx, 3)
+    h = chx.ch_create(nx, ny, L, L, 1.0, 0.01, 1e-8, dtype=chx.CHX_F32_REFINED, refine_passes=2)
+    c = torch.tensor(c0, device="cuda")
+    print(f"[case] refined ADI {ny}x{nx}", flush=True)
+    chx.ch_adi_step(h, c, nsteps=1)
+    torch.cuda.synchronize()
+    assert rel(c.cpu().numpy(), orc.ch_step(c0, L, L, 1.0, 0.01, 1e-8)) < TARGET
+
+
 def test_adi_refined_large_run_one_step(chx, orc):
     n = 8192
     c0 = inputs.mode_plus_noise(n, 5)
