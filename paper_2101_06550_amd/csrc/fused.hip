@@ -10,7 +10,7 @@
 // apart, 256 bytes of each per workgroup: 131088 systems, whose rows fall on
 // other channels, run 6 % faster) and the load and store phases of the one or
 // two workgroups that a CU holds.  262144 1D Cahn-Hilliard systems of 256, four
-// steps in a call: 0.30 ms (1.21 ms with a pass over memory per step); 131072
+// steps in a call: 0.27 ms (1.21 ms with a pass over memory per step); 131072
 // systems of 1000, an odd length: 0.447 ms.
 //
 // Thread (c, k) = (tid % L, tid / L) owns chunk k of system c: it loads the

@@ -6,8 +6,9 @@
 // FP64 or FP32 arrays (the arithmetic in the arrays' type).
 //
 // One workgroup (4 waves) owns a tile 64 vectors wide: 64 lanes of 16 bytes by
-// 16 rows where the rows divide into aligned vectors, 64 columns by 16 (FP64)
-// or 32 rows otherwise.  The tile and its halo are loaded once into LDS (premap applied
+// 16 rows where the rows divide into aligned vectors and are wide enough for
+// them (the rule is at launch_class), 64 columns by 16 (FP64) or 32 rows
+// otherwise.  The tile and its halo are loaded once into LDS (premap applied
 // on the way in), the tile's own columns a vector per lane and the few halo
 // columns by as many threads as there are; each thread then computes the
 // outputs of its columns in its wave's rows, walking down the input rows and

@@ -971,8 +971,8 @@ dim3 grid_of(int batch) { return dim3((unsigned)((batch + kThreads - 1) / kThrea
 //    4096 167 and 168 against 211 and 220).  Plain takes 36 and 77 at 256 x 64
 //    and 240 and 294 at 1000 x 64: it has nothing in flight while it computes.
 //    Shorter systems are over before it matters (56 x 64: 15.1 and 14.9
-//    against 13.9 and 17.0, 8 x 200: 10.7 and 7.3 against 10.6 and 6.7); past three waves a CU 4 are as good (100 x
-//    200000: 233 against 250).
+//    against 13.9 and 17.0, 8 x 200: 10.7 and 7.3 against 10.6 and 6.7);
+//    past three waves a CU 4 are as good (100 x 200000: 233 against 250).
 //  - few periodic systems likewise: twice 31 and 31 us, plain 24 and 47 (tri of
 //    100 x 64), 39 and 39, 36 and 46 (penta).
 //  - groups of 4 rows for the pentadiagonal below half a wave per SIMD, where
